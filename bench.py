@@ -71,7 +71,7 @@ def kernel_source_hash():
     import re
 
     h = hashlib.sha256()
-    for f in ("blco_device.hip", "blco_kernels.h"):
+    for f in ("blco_device.hip", "blco_kernels.h", "blco_win.h"):
         with open(os.path.join(ROOT, "paper_2201_12523_amd", "csrc", f)) as fh:
             text = re.sub(r"/\*.*?\*/", "", fh.read(), flags=re.S)
         lines = (re.sub(r"//.*$", "", ln).rstrip() for ln in text.splitlines())
@@ -424,9 +424,10 @@ def summarize_skew(out, json_path, command):
 
 # --------------------------------------------------------------------------- helpers
 
-def win_kernel_name(R, N, ft="float", big=False, stash=True):
+def win_kernel_name(R, N, ft="float", big=False, stash=True, copies=False):
     """Template name of the window MTTKRP kernel the library launches for rank R
-    (stash: the mode's frequent rows are held in LDS)."""
+    (stash: the mode's frequent rows are held in LDS; copies: they are flushed to copies in
+    a workspace)."""
     lpn, rpl = (16, 1) if R <= 16 else (16, 2) if R <= 32 else (16, 4) if R <= 64 else (64, 2)
     b = lambda v: "true" if v else "false"
     # then: the fused CP-gradient walk (never for the plain MTTKRP), vector gathers of
@@ -435,6 +436,8 @@ def win_kernel_name(R, N, ft="float", big=False, stash=True):
     # R > 32)
     vec = ft != "float" and rpl > 1 and R % 2 == 0
     wpt = (4 if rpl == 4 else 2) if (not stash and lpn == 16 and N <= 5) else 1
+    if copies:
+        stash, wpt = True, 2
     return (f"k_mttkrp_win<{lpn}, {rpl}, {ft}, {N}, {b(big)}, {b(stash)}, false, {b(vec)}, "
             f"{wpt}>")
 
@@ -461,6 +464,9 @@ def mode_kernel(T, n, R, N, ft, dims):
     sf = 4 if ft == "float" else 2
     if T.resolution(n, R) == "hierarchical":
         return short_kernel_name(R, N, ft, big_factors(dims, R, sf, n, window=False))
+    dtype = "fp32" if ft == "float" else "bf16"
+    if T.workspace(n, R, dtype) > 0:
+        return win_kernel_name(R, N, ft, copies=True)
     return win_kernel_name(R, N, ft, big_factors(dims, R, sf, n), stash=T.stash_rows(n, R) > 0)
 
 

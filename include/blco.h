@@ -175,6 +175,25 @@ int blco_mttkrp_v(blco_tensor* t, int mode, const float* values, const void* con
                   void* stream);
 
 /*
+ * The three calls above with a workspace: device memory the caller lends the call
+ * (256-byte aligned, not overlapping anything else, contents undefined before and after,
+ * in use until the call's work on `stream` has run).  With the bytes blco_workspace gives
+ * for the mode, a long MTTKRP of a mode with frequent rows runs faster: it flushes those
+ * rows to copies in the workspace, which are then added to the output, instead of summing
+ * them in LDS.  A smaller or empty workspace (NULL, 0) is fine: what does not fit is not
+ * used.  values: as blco_mttkrp_v, or NULL for the tensor's own; scale, alpha: as
+ * blco_mttkrp_v (NULL and 1 for blco_mttkrp); accumulate != 0: out += the result.
+ * Errors: as the calls above, EINVAL (workspace NULL with bytes > 0, or misaligned).
+ */
+int blco_mttkrp_ws(blco_tensor* t, int mode, const float* values, const void* const* factors,
+                   int factor_dtype, int rank, const double* scale, double alpha, int accumulate,
+                   float* out, void* workspace, size_t workspace_bytes, void* stream);
+
+/* The most workspace bytes a blco_mttkrp_ws call of mode `mode` at rank `rank` uses, or with
+   mode -1 a blco_cp_grad_ws or blco_mttkrp_stream_all_ws call (0: none).  Errors: EINVAL. */
+int blco_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype, size_t* bytes);
+
+/*
  * Out-of-memory MTTKRP (Section 4.2): the non-zeros stay in pinned host
  * memory (placement PINNED) and are streamed through at least two device
  * staging buffers reused in turn; the copy of one chunk overlaps the kernel of
@@ -204,6 +223,14 @@ int blco_mttkrp_stream(blco_tensor* t, int mode, const void* const* factors, int
  */
 int blco_mttkrp_stream_all(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
                            float* const* outs, size_t device_budget_bytes, void* stream);
+
+/*
+ * blco_mttkrp_stream_all with a workspace as in blco_mttkrp_ws.  The workspace counts
+ * against the budget, and is not used where the budget leaves no room for it.
+ */
+int blco_mttkrp_stream_all_ws(blco_tensor* t, const void* const* factors, int factor_dtype,
+                              int rank, float* const* outs, size_t device_budget_bytes,
+                              void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * Sparse CP fit loss at the non-zeros (model of Section 2.2):
@@ -249,6 +276,13 @@ int blco_sampled_loss(blco_tensor* t, const void* const* factors, int factor_dty
 int blco_cp_grad(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
                  const double* scale, double alpha, float* residual, double* loss,
                  float* const* grads, size_t device_budget_bytes, void* stream);
+
+/* blco_cp_grad with a workspace as in blco_mttkrp_ws (PINNED placement: it counts against
+   the budget). */
+int blco_cp_grad_ws(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
+                    const double* scale, double alpha, float* residual, double* loss,
+                    float* const* grads, size_t device_budget_bytes, void* workspace,
+                    size_t workspace_bytes, void* stream);
 
 /*
  * blco_cp_grad without any device allocation, for callers that cannot allocate

@@ -31,7 +31,8 @@ PLACEMENTS = {"device": 0, "pinned": 1, "host": 2}
 STATUS = {0: "OK", -1: "EINVAL", -2: "ENOMEM", -3: "EDEVICE", -4: "ERANGE", -5: "EUNSUPPORTED"}
 
 EXPORTED = ["blco_build", "blco_mttkrp", "blco_mttkrp_acc", "blco_mttkrp_v", "blco_mttkrp_stream",
-            "blco_mttkrp_stream_all",
+            "blco_mttkrp_stream_all", "blco_mttkrp_ws", "blco_mttkrp_stream_all_ws",
+            "blco_cp_grad_ws", "blco_workspace",
             "blco_sampled_loss", "blco_cp_grad", "blco_cp_grad_noalloc", "blco_scale", "blco_cast_bf16", "blco_set_resolution", "blco_resolution",
             "blco_gram", "blco_cp_als", "blco_build_device",
             "blco_atomic_probe", "blco_gather_probe", "blco_frequent_rows", "blco_info", "blco_export", "blco_free",
@@ -91,6 +92,11 @@ def lib():
         L.blco_mttkrp_v.argtypes = [p, i32, p, p, i32, i32, p, ctypes.c_double, p, p]
         L.blco_mttkrp_stream.argtypes = [p, i32, p, i32, i32, p, ctypes.c_size_t, p]
         L.blco_mttkrp_stream_all.argtypes = [p, p, i32, i32, p, ctypes.c_size_t, p]
+        sz = ctypes.c_size_t
+        L.blco_mttkrp_ws.argtypes = [p, i32, p, p, i32, i32, p, ctypes.c_double, i32, p, p, sz, p]
+        L.blco_mttkrp_stream_all_ws.argtypes = [p, p, i32, i32, p, sz, p, sz, p]
+        L.blco_cp_grad_ws.argtypes = [p, p, i32, i32, p, ctypes.c_double, p, p, p, sz, p, sz, p]
+        L.blco_workspace.argtypes = [p, i32, i32, i32, ctypes.POINTER(sz)]
         L.blco_sampled_loss.argtypes = [p, p, i32, i32, p, p, p]
         L.blco_cast_bf16.argtypes = [p, p, i64, p]
         L.blco_cp_grad.argtypes = [p, p, i32, i32, p, ctypes.c_double, p, p, p, ctypes.c_size_t,
@@ -186,6 +192,14 @@ class BLCOTensor:
         c = ctypes.c_int(-1)
         _check(lib().blco_frequent_rows(self._h, int(mode), int(rank), ctypes.byref(c)))
         return c.value
+
+    def workspace(self, mode: int, rank: int, dtype: str = "fp32") -> int:
+        """Bytes of workspace a mode-`mode` MTTKRP at `rank` takes (mode -1: a call over every
+        mode); the functions of this module allocate it themselves."""
+        n = ctypes.c_size_t()
+        _check(lib().blco_workspace(self._h, int(mode), int(rank), BF16 if dtype == "bf16" else F32,
+                                    ctypes.byref(n)))
+        return n.value
 
     def export(self):
         """(keys uint64, values float32, block_ids uint64, block_starts int64) on the host."""
@@ -303,6 +317,22 @@ def _out(t, mode, R, out, device):
     return out
 
 
+def _workspace(t, mode, R, dt, device, stream):
+    """(tensor or None, pointer, bytes): the workspace a call of `mode` (-1: all) can use, from
+    torch's allocator in the stream's order; none where memory is short."""
+    need = ctypes.c_size_t()
+    _check(lib().blco_workspace(t.handle, mode, R, dt, ctypes.byref(need)))
+    if need.value == 0:
+        return None, None, 0
+    try:
+        # from the pool of the stream the call runs on: blocks there are reused in its order
+        with torch.cuda.stream(stream):
+            ws = torch.empty(need.value, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None, None, 0
+    return ws, ws.data_ptr(), need.value
+
+
 def _device_of(factors):
     for f in factors:
         if f is not None:
@@ -314,7 +344,9 @@ def mttkrp(t, mode, factors, out=None, stream=None):
     """Mode-``mode`` MTTKRP of an in-memory BLCO tensor; returns out (I_mode x R, float32)."""
     arr, dt, R, _keep = _factor_args(t, factors, mode)
     out = _out(t, mode, R, out, _device_of(factors))
-    _check(lib().blco_mttkrp(t.handle, mode, arr, dt, R, out.data_ptr(), _stream(stream)))
+    ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
+    _check(lib().blco_mttkrp_ws(t.handle, mode, None, arr, dt, R, None, 1.0, 0, out.data_ptr(), wp,
+                                wb, _stream(stream)))
     return out
 
 
@@ -322,7 +354,9 @@ def mttkrp_acc(t, mode, factors, out, stream=None):
     """out += mode-``mode`` MTTKRP (out is not cleared first)."""
     arr, dt, R, _keep = _factor_args(t, factors, mode)
     out = _out(t, mode, R, out, _device_of(factors))
-    _check(lib().blco_mttkrp_acc(t.handle, mode, arr, dt, R, out.data_ptr(), _stream(stream)))
+    ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
+    _check(lib().blco_mttkrp_ws(t.handle, mode, None, arr, dt, R, None, 1.0, 1, out.data_ptr(), wp,
+                                wb, _stream(stream)))
     return out
 
 
@@ -337,8 +371,9 @@ def mttkrp_v(t, mode, values, factors, out=None, scale=None, alpha=1.0, stream=N
         if scale.dtype != torch.float64 or scale.numel() != 1:
             raise ValueError("scale must be a one-element float64 device tensor")
         sp = scale.data_ptr()
-    _check(lib().blco_mttkrp_v(t.handle, mode, values.data_ptr(), arr, dt, R, sp, float(alpha),
-                               out.data_ptr(), _stream(stream)))
+    ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
+    _check(lib().blco_mttkrp_ws(t.handle, mode, values.data_ptr(), arr, dt, R, sp, float(alpha), 0,
+                                out.data_ptr(), wp, wb, _stream(stream)))
     return out
 
 
@@ -346,8 +381,15 @@ def mttkrp_stream(t, mode, factors, out=None, device_budget=8_000_000_000, strea
     """MTTKRP of a tensor in pinned host memory, streamed under a device-memory budget."""
     arr, dt, R, _keep = _factor_args(t, factors, mode)
     out = _out(t, mode, R, out, _device_of(factors))
-    _check(lib().blco_mttkrp_stream(t.handle, mode, arr, dt, R, out.data_ptr(),
-                                    int(device_budget), _stream(stream)))
+    ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
+    if wb == 0 or mode < 0:
+        _check(lib().blco_mttkrp_stream(t.handle, mode, arr, dt, R, out.data_ptr(),
+                                        int(device_budget), _stream(stream)))
+        return out
+    outs = (ctypes.c_void_p * len(t.dims))()
+    outs[mode] = out.data_ptr()
+    _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, outs, int(device_budget), wp, wb,
+                                           _stream(stream)))
     return out
 
 
@@ -364,8 +406,9 @@ def mttkrp_stream_all(t, factors, outs=None, device_budget=8_000_000_000, modes=
         outs[m] = _out(t, m, R, outs[m], dev)
     ptrs = (ctypes.c_void_p * len(t.dims))(*[outs[m].data_ptr() if m in modes else None
                                                for m in range(len(t.dims))])
-    _check(lib().blco_mttkrp_stream_all(t.handle, arr, dt, R, ptrs, int(device_budget),
-                                        _stream(stream)))
+    ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
+    _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, ptrs, int(device_budget), wp, wb,
+                                           _stream(stream)))
     return [outs[m] if m in modes else None for m in range(len(t.dims))]
 
 
@@ -407,9 +450,10 @@ def cp_grad(t, factors, grads=None, residual=None, loss=None, scale=None, alpha=
             raise ValueError("scale must be a one-element float64 device tensor")
         sp = scale.data_ptr()
     ptrs = (ctypes.c_void_p * N)(*[g.data_ptr() for g in grads])
-    _check(lib().blco_cp_grad(t.handle, arr, dt, R, sp, float(alpha),
-                              None if pinned else residual.data_ptr(), loss.data_ptr(), ptrs,
-                              int(device_budget), _stream(stream)))
+    ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
+    _check(lib().blco_cp_grad_ws(t.handle, arr, dt, R, sp, float(alpha),
+                                 None if pinned else residual.data_ptr(), loss.data_ptr(), ptrs,
+                                 int(device_budget), wp, wb, _stream(stream)))
     return loss, grads, (None if pinned else residual)
 
 

@@ -1,7 +1,8 @@
 """Compile the BLCO library for gfx950 into ``paper_2201_12523_amd/libblco.so``.
 
-Host builder (``csrc/blco_host.cpp``) with g++; device runtime and MTTKRP
-kernels (``csrc/blco_device.hip``), the CP-ALS driver (``csrc/blco_cpals.hip``) and
+Host builder (``csrc/blco_host.cpp``) with g++; device runtime and short-mode and loss
+kernels (``csrc/blco_device.hip``), the window MTTKRP kernel (``csrc/blco_win_*.hip``), the
+CP-ALS driver (``csrc/blco_cpals.hip``) and
 the GPU builder (``csrc/blco_build_gpu.hip``) and its sort and compaction
 (``csrc/blco_sort.hip``) with hipcc; linked with hipcc.  Run as
 ``python -m paper_2201_12523_amd.buildlib``.
@@ -17,6 +18,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libblco.so")
 BUILD_DIR = os.path.join(os.path.dirname(HERE), "_build")
+
+# device sources, compiled in parallel
+DEVICE_SOURCES = ["blco_win_f32", "blco_win_bf16", "blco_win_big", "blco_win_res", "blco_device",
+                  "blco_cpals", "blco_build_gpu", "blco_sort"]
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -37,29 +42,21 @@ def _run(cmd):
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     host_o = os.path.join(BUILD_DIR, "blco_host.o")
-    dev_o = os.path.join(BUILD_DIR, "blco_device.o")
-    als_o = os.path.join(BUILD_DIR, "blco_cpals.o")
-    gb_o = os.path.join(BUILD_DIR, "blco_build_gpu.o")
-    sort_o = os.path.join(BUILD_DIR, "blco_sort.o")
+    objs = [host_o]
     t = time.time()
     # the objects compile in parallel
     procs = [subprocess.Popen(["g++", "-std=c++17", "-O3", "-fPIC", "-Wall", "-c",
-                               os.path.join(CSRC, "blco_host.cpp"), "-o", host_o]),
-             subprocess.Popen([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "blco_device.hip"),
-                               "-o", dev_o]),
-             subprocess.Popen([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "blco_cpals.hip"),
-                               "-o", als_o]),
-             subprocess.Popen([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "blco_build_gpu.hip"),
-                               "-o", gb_o]),
-             subprocess.Popen([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, "blco_sort.hip"),
-                               "-o", sort_o])]
+                               os.path.join(CSRC, "blco_host.cpp"), "-o", host_o])]
+    for name in DEVICE_SOURCES:
+        objs.append(os.path.join(BUILD_DIR, name + ".o"))
+        procs.append(subprocess.Popen([HIPCC, *HIP_FLAGS, "-c",
+                                       os.path.join(CSRC, name + ".hip"), "-o", objs[-1]]))
     codes = [p.wait() for p in procs]
     if any(codes):
         raise subprocess.CalledProcessError(max(codes, key=abs), "compile")
     t1 = t2 = time.time() - t
     tmp = OUT + ".tmp"
-    t3 = _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", host_o, dev_o, als_o, gb_o, sort_o,
-               "-o", tmp, "-lpthread"])
+    t3 = _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp, "-lpthread"])
     os.replace(tmp, OUT)
     if verbose:
         print(f"built {OUT} (compile {t1:.1f}s, link {t3:.1f}s)", file=sys.stderr)

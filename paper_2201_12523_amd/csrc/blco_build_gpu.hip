@@ -232,7 +232,7 @@ int upload_to(T** dst, const T* src, size_t count, hipStream_t s, size_t* acc) {
 
 void release_tensor_arrays(blco_tensor* t) {
   for (void* p : {(void*)t->d_keys, (void*)t->d_vals, (void*)t->d_run_start,
-                  (void*)t->d_run_base, (void*)t->d_tile_run, (void*)t->d_hot})
+                  (void*)t->d_run_base, (void*)t->d_tile_run, (void*)t->d_hot, (void*)t->d_tab})
     if (p) (void)hipFree(p);
   t->d_keys = nullptr;
   t->d_vals = nullptr;
@@ -240,6 +240,7 @@ void release_tensor_arrays(blco_tensor* t) {
   t->d_run_base = nullptr;
   t->d_tile_run = nullptr;
   t->d_hot = nullptr;
+  t->d_tab = nullptr;
   free_host_arrays(t);
 }
 
@@ -511,11 +512,13 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
   // 5. frequent rows
   stage.mark(4, s);
   if ((rc = gpu_hot_rows(lp, nnz, hot_min, pool, s, t))) return rc;
+  make_row_tables(t);
   stage.mark(5, s);
   if ((rc = upload_to(&t->d_run_start, t->run_start.data(), t->run_start.size(), s, &acc)) ||
       (rc = upload_to(&t->d_run_base, t->run_base.data(), t->run_base.size(), s, &acc)) ||
       (rc = upload_to(&t->d_tile_run, t->tile_run.data(), t->tile_run.size(), s, &acc)) ||
-      (rc = upload_to(&t->d_hot, t->hot.data(), t->hot.size(), s, &acc)))
+      (rc = upload_to(&t->d_hot, t->hot.data(), t->hot.size(), s, &acc)) ||
+      (rc = upload_to(&t->d_tab, t->tab.data(), t->tab.size(), s, &acc)))
     return rc;
   HIPCHK(hipStreamSynchronize(s));
   stage.read(t->build_stage_ms);

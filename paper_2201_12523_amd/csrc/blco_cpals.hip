@@ -438,10 +438,13 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
   const size_t bytes_V = (size_t)R * R * sizeof(double);
   const size_t bytes_S = 3 * bytes_V;
   const size_t bytes_sc = 4 * sizeof(double) + sizeof(int) * 2;
+  size_t bytes_w = 0;   // the MTTKRPs' workspace
+  for (int m = 0; m < N; ++m)
+    bytes_w = std::max(bytes_w, blco::mttkrp_workspace(t, m, R, o.factor_dtype));
   const size_t bytes_h = o.factor_dtype == BLCO_BF16 ? (size_t)sumI * R * sizeof(uint16_t) : 0;
   auto align = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t total = align(bytes_M) + align(bytes_G) + align(bytes_V) + align(bytes_S) +
-                       align(bytes_sc) + align(bytes_h);
+                       align(bytes_sc) + align(bytes_h) + align(bytes_w);
   DevBuf ws;
   HIPCHK(hipMalloc(&ws.p, total));
   char* base = static_cast<char*>(ws.p);
@@ -457,6 +460,7 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
   int* dfb = reinterpret_cast<int*>(dsc + 4);
   base += align(bytes_sc);
   uint16_t* dh = bytes_h ? reinterpret_cast<uint16_t*>(base) : nullptr;
+  char* dw = bytes_w ? base + align(bytes_h) : nullptr;
   std::vector<const void*> mt(N);
   std::vector<uint16_t*> half(N, nullptr);
   {
@@ -491,7 +495,7 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
       const int64_t In = (int64_t)t->lay.dims[n];
       hipLaunchKernelGGL(k_pinv_v, dim3(1), dim3(kSolveThreads), 0, s, dG, N, n, R, dV, dS, dfb);
       HIPCHK(hipGetLastError());
-      if ((rc = blco_mttkrp(t, n, mt.data(), mdt, R, dM, s)) != BLCO_OK) return rc;
+      if ((rc = blco::mttkrp_with(t, n, mt.data(), mdt, R, dM, dw, bytes_w, s)) != BLCO_OK) return rc;
       const int per = 256 / R;
       const int64_t blocks = std::min<int64_t>((In + per - 1) / per, 4096);
       hipLaunchKernelGGL(k_apply_vinv, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(256), 0,

@@ -34,6 +34,7 @@
 
 #include "blco_internal.h"
 #include "blco_kernels.h"
+#include "blco_win.h"
 
 using namespace blco;
 
@@ -46,51 +47,10 @@ using namespace blco;
 
 // ====================================================================== device code
 
-template <typename FT>
-__device__ __forceinline__ float ld_factor(const void* A, size_t i);
-
-template <>
-__device__ __forceinline__ float ld_factor<float>(const void* A, size_t i) {
-  return static_cast<const float*>(A)[i];
-}
-
-template <>
-__device__ __forceinline__ float ld_factor<uint16_t>(const void* A, size_t i) {
-  return __uint_as_float((uint32_t)static_cast<const uint16_t*>(A)[i] << 16);
-}
-
-// Coordinates of one non-zero: kept bits by shift and mask, the rest from
-// the block key of the run that holds it (Figure 6b).
-template <int N>
-__device__ __forceinline__ void decode(const KParams& p, uint64_t key, int64_t gidx,
-                                       uint32_t (&c)[N]) {
-  uint32_t base[N];
-#pragma unroll
-  for (int m = 0; m < N; ++m) base[m] = 0;
-  if (p.multi) {
-    int run = p.tile_run[gidx >> 6];
-    while (gidx >= p.run_start[run + 1]) ++run;
-#pragma unroll
-    for (int m = 0; m < N; ++m) base[m] = p.run_base[(size_t)run * N + m];
-  }
-#pragma unroll
-  for (int m = 0; m < N; ++m) c[m] = ((uint32_t)(key >> p.shift[m]) & p.mask[m]) | base[m];
-}
-
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ float term_scale(const KParams& p) {
-  return p.scale_dev ? (float)((double)p.scale * p.scale_dev[0]) : p.scale;
-}
-
-// Zero-fill of an output (a kernel rather than a memset so the call can be captured).
-__global__ __launch_bounds__(256) void k_fill_zero(float* __restrict__ p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  int64_t stride = (int64_t)gridDim.x * 256;
+// Zero-fill of an output and of a second array (a kernel rather than a memset so the call
+// can be captured).
+__device__ __forceinline__ void zero_range(float* __restrict__ p, int64_t n, int64_t i,
+                                           int64_t stride) {
   if ((reinterpret_cast<uintptr_t>(p) & 15) == 0) {
     float4* q = reinterpret_cast<float4*>(p);
     int64_t n4 = n >> 2;
@@ -101,633 +61,29 @@ __global__ __launch_bounds__(256) void k_fill_zero(float* __restrict__ p, int64_
   }
 }
 
-constexpr int kWin = 1024;     // threads of the window kernel (non-zeros per window / WPT)
-constexpr int kWinRounds = 4;  // dispatch rounds of the persistent window kernel
-constexpr int kWinBits = 10;
-#ifndef BLCO_WIN_U
-#define BLCO_WIN_U 8
-#endif
-// minimum waves per SIMD requested from the compiler: 8 lets two 1024-thread
-// workgroups share a CU (measured about 1.7x faster than one)
-#ifndef BLCO_WIN_OCC
-#define BLCO_WIN_OCC 8
-#endif
+__global__ __launch_bounds__(256) void k_fill_zero(float* p, int64_t n, float* p2, int64_t n2) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  zero_range(p, n, i, stride);
+  if (n2 > 0) zero_range(p2, n2, i, stride);
+}
 
-constexpr int kBucketBits = 12;
-constexpr int kBuckets = 1 << kBucketBits;   // hash buckets per 1024-non-zero window
-
-// In-place exclusive prefix sum of NB counters in LDS by a workgroup of NT
-// threads (NB a multiple of NT): per-thread serial sums, a wave scan by
-// cross-lane shifts, and one LDS pass over the per-wave totals.
-template <int NB, int NT>
-__device__ __forceinline__ void block_exclusive_scan(uint32_t* a, int tid, uint32_t* wsum) {
-  constexpr int PER = NB / NT;
-  uint32_t v[PER];
-  uint32_t tot = 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    v[i] = a[tid * PER + i];
-    tot += v[i];
-  }
-  const int lane = tid & 63;
-  uint32_t inc = tot;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_up((int)inc, off);
-    if (lane >= off) inc += o;
-  }
-  if (lane == 63) wsum[tid >> 6] = inc;
+// Adds the copies of frequent row hot[blockIdx.x] to the output (see k_mttkrp_win): each
+// thread sums every fourth copy of one rank in order, then the four partial sums meet.
+__global__ __launch_bounds__(kBlock) void k_hot_sum(const float* __restrict__ copy,
+                                                    const uint32_t* __restrict__ hot, int copies,
+                                                    int stride, int R, float* __restrict__ out) {
+  __shared__ float s_part[kBlock];
+  const int r = threadIdx.x & 63, q = threadIdx.x >> 6;   // R <= 64
+  const float* c = copy + (size_t)blockIdx.x * copies * stride;
+  float a = 0.f;
+  if (r < R)
+    for (int i = q; i < copies; i += 4) a += c[(size_t)i * stride + r];
+  s_part[threadIdx.x] = a;
   __syncthreads();
-  uint32_t wbase = 0;
-  for (int w = 0; w < (tid >> 6); ++w) wbase += wsum[w];
-  uint32_t run = wbase + inc - tot;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    a[tid * PER + i] = run;
-    run += v[i];
-  }
-  __syncthreads();
-}
-
-// Lane q of this lane's 16-lane row (DPP row_newbcast), and the value of the
-// lane q places further along the row (DPP row_shl).  q must fold to a
-// constant where they are called (unrolled loops).
-__device__ __forceinline__ uint32_t row_bcast(uint32_t v, int q) {
-  switch (q) {
-    case 0: return __builtin_amdgcn_update_dpp(0u, v, 0x150, 0xF, 0xF, false);
-    case 1: return __builtin_amdgcn_update_dpp(0u, v, 0x151, 0xF, 0xF, false);
-    case 2: return __builtin_amdgcn_update_dpp(0u, v, 0x152, 0xF, 0xF, false);
-    case 3: return __builtin_amdgcn_update_dpp(0u, v, 0x153, 0xF, 0xF, false);
-    case 4: return __builtin_amdgcn_update_dpp(0u, v, 0x154, 0xF, 0xF, false);
-    case 5: return __builtin_amdgcn_update_dpp(0u, v, 0x155, 0xF, 0xF, false);
-    case 6: return __builtin_amdgcn_update_dpp(0u, v, 0x156, 0xF, 0xF, false);
-    case 7: return __builtin_amdgcn_update_dpp(0u, v, 0x157, 0xF, 0xF, false);
-    case 8: return __builtin_amdgcn_update_dpp(0u, v, 0x158, 0xF, 0xF, false);
-    case 9: return __builtin_amdgcn_update_dpp(0u, v, 0x159, 0xF, 0xF, false);
-    case 10: return __builtin_amdgcn_update_dpp(0u, v, 0x15A, 0xF, 0xF, false);
-    case 11: return __builtin_amdgcn_update_dpp(0u, v, 0x15B, 0xF, 0xF, false);
-    case 12: return __builtin_amdgcn_update_dpp(0u, v, 0x15C, 0xF, 0xF, false);
-    case 13: return __builtin_amdgcn_update_dpp(0u, v, 0x15D, 0xF, 0xF, false);
-    case 14: return __builtin_amdgcn_update_dpp(0u, v, 0x15E, 0xF, 0xF, false);
-    default: return __builtin_amdgcn_update_dpp(0u, v, 0x15F, 0xF, 0xF, false);
-  }
-}
-__device__ __forceinline__ uint32_t row_shl(uint32_t v, int q) {
-  switch (q) {
-    case 1: return __builtin_amdgcn_update_dpp(0u, v, 0x101, 0xF, 0xF, false);
-    case 2: return __builtin_amdgcn_update_dpp(0u, v, 0x102, 0xF, 0xF, false);
-    case 3: return __builtin_amdgcn_update_dpp(0u, v, 0x103, 0xF, 0xF, false);
-    case 4: return __builtin_amdgcn_update_dpp(0u, v, 0x104, 0xF, 0xF, false);
-    case 5: return __builtin_amdgcn_update_dpp(0u, v, 0x105, 0xF, 0xF, false);
-    case 6: return __builtin_amdgcn_update_dpp(0u, v, 0x106, 0xF, 0xF, false);
-    case 7: return __builtin_amdgcn_update_dpp(0u, v, 0x107, 0xF, 0xF, false);
-    case 8: return __builtin_amdgcn_update_dpp(0u, v, 0x108, 0xF, 0xF, false);
-    case 9: return __builtin_amdgcn_update_dpp(0u, v, 0x109, 0xF, 0xF, false);
-    case 10: return __builtin_amdgcn_update_dpp(0u, v, 0x10A, 0xF, 0xF, false);
-    case 11: return __builtin_amdgcn_update_dpp(0u, v, 0x10B, 0xF, 0xF, false);
-    case 12: return __builtin_amdgcn_update_dpp(0u, v, 0x10C, 0xF, 0xF, false);
-    case 13: return __builtin_amdgcn_update_dpp(0u, v, 0x10D, 0xF, 0xF, false);
-    case 14: return __builtin_amdgcn_update_dpp(0u, v, 0x10E, 0xF, 0xF, false);
-    default: return __builtin_amdgcn_update_dpp(0u, v, 0x10F, 0xF, 0xF, false);
-  }
-}
-
-// target row of a record (field N - 1 of the record at LDS offset `at`)
-__device__ __forceinline__ uint32_t seg_target(const uint32_t* rec, int at, int mode, int N) {
-  (void)mode;
-  return rec[at + N - 1];
-}
-constexpr uint32_t kBufFlags = 0x00020000u;  // raw buffer resource word 3 (gfx9 family)
-
-// Factor-row gathers.  Raw buffer loads with a 32-bit byte offset (row * row
-// bytes + rank offset) when every factor is below 4 GiB: no 64-bit address
-// arithmetic, and the descriptor's size bound drops stray offsets.  Larger
-// factors take 64-bit global addresses (BIG).  (Structured, index-scaled
-// buffer loads would cover both but measured 1.5-2x slower on gfx950.)
-template <typename FT>
-__device__ __forceinline__ float ld_buf(__amdgpu_buffer_rsrc_t r, uint32_t off);
-template <>
-__device__ __forceinline__ float ld_buf<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
-template <>
-__device__ __forceinline__ float ld_buf<uint16_t>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0) << 16);
-}
-
-// fp32 gathers of the window kernel at four ranks per lane (33-64 ranks): a global load
-// from the factor's base (uniform, in scalar registers) plus the zero-extended 32-bit
-// byte offset.  That reaches all of 4 GiB, so a factor of exactly 4 GiB (2^24 rows of 64
-// ranks) keeps 32-bit offsets, where a buffer descriptor's 32-bit size stops one byte
-// short.  Measured on the 4-mode 200M-non-zero workload at R = 64: 17.5 -> 15.1 ms on the
-// mode that gathers such a factor (it took 64-bit addresses before), 15.7 -> 15.2 ms on
-// its other frequent-row mode; at two ranks per lane the same loads were 5% slower on the
-// frequent-row modes, so R <= 32 keeps buffer loads.
-__device__ __forceinline__ float ld_base(const void* A, uint32_t off) {
-  return *reinterpret_cast<const float*>(static_cast<const char*>(A) + off);
-}
-
-// RPL consecutive bf16 factor elements from byte offset off, widened to fp32: one
-// 4- or 8-byte buffer load when VEC (every run starts 4-byte aligned: R is even), else
-// RPL 2-byte loads.  Element k sits at the lower address, in the low half of its word.
-template <int RPL, bool VEC>
-__device__ __forceinline__ void ld_bf16_run(__amdgpu_buffer_rsrc_t r, uint32_t off,
-                                            float (&t)[RPL]) {
-  if constexpr (RPL == 2 && VEC) {
-    {
-      const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
-      t[0] = __uint_as_float(v << 16);
-      t[1] = __uint_as_float(v & 0xFFFF0000u);
-      return;
-    }
-  } else if constexpr (RPL == 4 && VEC) {
-    {
-      const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
-      t[0] = __uint_as_float(v[0] << 16);
-      t[1] = __uint_as_float(v[0] & 0xFFFF0000u);
-      t[2] = __uint_as_float(v[1] << 16);
-      t[3] = __uint_as_float(v[1] & 0xFFFF0000u);
-      return;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < RPL; ++k) t[k] = ld_buf<uint16_t>(r, off + 2u * (uint32_t)k);
-}
-
-// The same run through a 64-bit address (a factor of 4 GiB or more), which has no
-// bounds check: only elements with act[k] set (ranks below R) are read, so a run that
-// ends past the last row stays inside the factor.  VEC reads RPL / 2 four-byte words
-// (runs start 4-byte aligned and R is even, so a word is read whole or not at all).
-template <int RPL, bool VEC>
-__device__ __forceinline__ void ld_bf16_run_ptr(const uint16_t* src, const bool (&act)[RPL],
-                                                float (&t)[RPL]) {
-  if constexpr (VEC && RPL % 2 == 0) {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(src);
-#pragma unroll
-    for (int q = 0; q < RPL / 2; ++q) {
-      const uint32_t v = act[2 * q] ? w[q] : 0u;
-      t[2 * q] = __uint_as_float(v << 16);
-      t[2 * q + 1] = __uint_as_float(v & 0xFFFF0000u);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < RPL; ++k) t[k] = act[k] ? ld_factor<uint16_t>(src, (size_t)k) : 0.f;
-  }
-}
-
-// Adds a lane group's segment sums to one output row with contiguous-rank atomics
-// when each lane holds RPL consecutive ranks (lane l: ranks RPL*l .. RPL*l + RPL - 1 of
-// the slice): the j-th atomic of lane l adds rank l + j*LPN, fetched from the lane
-// holding it, so every atomic instruction covers LPN consecutive floats.  dst points
-// at the slice's first rank; ranks from nvalid on are not written.
-template <int RPL, int LPN>
-__device__ __forceinline__ void flush_packed(float* dst, const float (&a)[RPL], float scale,
-                                             int rl, int nvalid) {
-#pragma unroll
-  for (int j = 0; j < RPL; ++j) {
-    const int q = rl + j * LPN;
-    float v = 0.f;
-#pragma unroll
-    for (int s2 = 0; s2 < RPL; ++s2) {
-      const float t2 = __shfl(a[s2], q / RPL, LPN);
-      if (s2 == rl % RPL) v = t2;
-    }
-    if (q < nvalid) unsafeAtomicAdd(dst + q, v * scale);
-  }
-}
-
-// Frequent-row lookup of the window kernel: open addressing over kHotSlots
-// LDS slots holding (row, stash index); at most half full.
-constexpr int kHotSlots = 2 * blco::kHotMax;
-constexpr uint32_t kNoRow = 0xFFFFFFFFu;
-constexpr uint32_t kHotFlag = 0x80000000u;   // record target field: stash index follows
-
-__device__ __forceinline__ uint32_t hot_hash(uint32_t row) {
-  return (row * 0x9E3779B1u) >> (32 - 9);   // 9 bits: kHotSlots = 512
-}
-
-__device__ __forceinline__ int hot_lookup(const uint32_t* keys, const uint32_t* idx, uint32_t row) {
-  uint32_t h = hot_hash(row);
-  for (int probe = 0; probe < kHotSlots; ++probe) {
-    const uint32_t k = keys[h];
-    if (k == row) return (int)idx[h];
-    if (k == kNoRow) return -1;
-    h = (h + 1) & (kHotSlots - 1);
-  }
-  return -1;
-}
-
-// BLCO MTTKRP with register-based conflict resolution (Sections 5.1-5.2) over
-// windows of 1024 * WPT consecutive non-zeros; persistent workgroups take windows
-// in turn (see below)
-//   processing: WPT non-zeros per thread are loaded (the next window's load is
-//     issued before the current walk) and decoded by shift and mask; the
-//     window is grouped by target with a counting sort (LDS histogram with
-//     atomic ranks, exclusive scan, scatter) on a hash of the target, so each
-//     target's terms form one contiguous segment, and each grouped position
-//     gets a record: byte offsets of the other modes' factor rows, target,
-//     value;
-//   computing: groups of LPN lanes (RPL ranks per lane) walk LPN consecutive
-//     grouped positions each (records read from LDS, or for N = 3 held one
-//     per lane and passed along the group by DPP row broadcasts),
-//     gathering factor rows with buffer loads and
-//     summing the scaled Hadamard products in registers; a segment that ends
-//     inside the group is flushed once per rank; a segment that crosses into
-//     later groups is completed by the group it started in, from partial sums
-//     the later groups leave in LDS.
-// A flush is a device-scope atomic into the output, which MI355X performs at
-// the memory side (same-address updates serialise at about 32 ns), except for
-// the mode's frequent rows (found at build time): those get buckets of their
-// own, so each has exactly one segment per window, and its flush is a plain
-// add into the workgroup's LDS stash row; the stash goes to the output with
-// one atomic per (row, rank) when the workgroup ends.
-//
-// RES (the fused CP-gradient walk, one rank slice): the values are the data x_k,
-// and each position also gathers its target row, so the walk forms the model
-// xhat_k = sum_r prod_m A^(m)[i_m^k, r] (a sum over the 16 lanes of the group),
-// the residual e_k = x_k - xhat_k, which it writes to p.resid in BLCO order, and
-// sums e_k * prod_{m != mode} A^(m) instead of x_k * prod_{m != mode} A^(m).
-//
-// WPT: non-zeros per thread, so a window holds kWin * WPT non-zeros.  Two (for modes
-// without a stash) merge more terms per flush: on the 2^20-row and 1024-row modes of
-// the 4-mode 200M-non-zero tensor, 16% and 32% fewer row flushes than at one.  Four
-// (at R > 32) merge more again but need 145 KiB of LDS, one workgroup per CU: faster
-// at R = 64, where the walk has four ranks per lane to cover the gathers, slower at 32.
-template <int LPN, int RPL, typename FT, int N, bool BIG, bool STASH, bool RES = false,
-          bool VEC = false, int WPT = 1>
-__global__ __launch_bounds__(kWin, WPT >= 4 ? 4 : BLCO_WIN_OCC) void k_mttkrp_win(KParams p) {
-  constexpr int W = kWin * WPT;                 // non-zeros per window
-  constexpr int G = kWin / LPN;                 // groups of LPN lanes
-  constexpr int PPG = W / G;                    // grouped positions per group (= LPN * WPT)
-  static_assert(PPG <= 64, "a group's segment ends must fit one 64-bit word");
-  static_assert(WPT == 1 || (!STASH && !RES), "multi-non-zero windows: plain MTTKRP, no stash");
-  // hash buckets: 4096 per 1024 non-zeros, 6144 per 2048 (two workgroups per CU keep
-  // fitting in LDS), 12288 per 4096
-  constexpr int NB = WPT == 1 ? kBuckets : WPT == 2 ? kBuckets * 3 / 2 : kBuckets * 3;
-  // positions whose gathers are issued together: BLCO_WIN_U / RPL, except for
-  // 3-mode tensors at one or four ranks per lane, where 4 and 1 positions keep
-  // the registers from spilling and measured 8% and 3% faster; the fused
-  // residual walk also gathers the target row and keeps the value, the
-  // residual and the position of each, so it takes half as many (at four it
-  // spilled about 45 registers per lane; 4-mode 80M-non-zero CP gradient step
-  // 13.1 -> 12.0 ms)
-  constexpr int UW0 = (N == 3 && RPL == 1) ? 4 : (N == 3 && RPL == 4) ? 1 : BLCO_WIN_U / RPL;
-  constexpr int UW = RES ? (UW0 > 1 ? UW0 / 2 : 1) : UW0;
-  constexpr int U = PPG < UW ? PPG : UW;
-  // record fields: the other modes' row offsets, target, value; with RES also
-  // the target row's offset and the position in the window
-  constexpr int NF = RES ? N + 3 : N + 1;
-  constexpr int NP = NF <= 4 ? 4 : ((NF + 1) / 2) * 2;
-  static_assert(!RES || (LPN == 16 && !BIG), "fused residual walk: 16-lane groups, 32-bit offsets");
-  // bf16 factors: each lane holds RPL consecutive ranks, so one 4- or 8-byte load
-  // gathers them when R is even (VEC; measured 14% faster per mode on 200M
-  // non-zeros), 2-byte loads otherwise; fp32 keeps ranks LPN apart, whose 4-byte
-  // loads measured faster than 8- and 16-byte ones
-  constexpr bool PACKED = sizeof(FT) == 2 && RPL > 1;
-  static_assert(!VEC || PACKED, "vector gathers are for packed bf16 ranks");
-  // fp32 gathers at four ranks per lane: ld_base instead of buffer loads
-  constexpr bool BASE32 = sizeof(FT) == 4 && LPN == 16 && RPL == 4 && !RES && !BIG;
-  __shared__ __align__(16) uint32_t s_rec[W * NP];  // records by grouped position
-  __shared__ uint64_t s_end[W / 64];
-  // the histogram (processing) and the carry partial sums (computing) are never
-  // live at once: they share one array
-  constexpr int NHH = NB > kWin * RPL ? NB : kWin * RPL;
-  __shared__ __align__(16) uint32_t s_hist[NHH];
-  float* s_head = reinterpret_cast<float*>(s_hist);
-  __shared__ uint32_t s_wsum[kWin / 64];
-  extern __shared__ __align__(16) unsigned char s_dyn_win[];
-  // frequent rows in the stash; without STASH one window per workgroup
-  const int K = STASH ? p.nhot : 0;
-  const int R = p.R;
-  float* s_stash = reinterpret_cast<float*>(s_dyn_win);   // K x R
-  uint32_t* s_hkey = reinterpret_cast<uint32_t*>(s_stash + (size_t)K * R);
-  uint32_t* s_hidx = s_hkey + kHotSlots;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int64_t nwin = (p.n + W - 1) / W;
-  if (K > 0) {
-    for (int i = tid; i < K * R; i += kWin) s_stash[i] = 0.f;
-    for (int i = tid; i < kHotSlots; i += kWin) s_hkey[i] = kNoRow;
-    __syncthreads();
-    if (tid < K) {
-      const uint32_t row = p.hot[tid];
-      uint32_t h = hot_hash(row);
-      for (int probe = 0; probe < kHotSlots; ++probe) {
-        if (atomicCAS(&s_hkey[h], kNoRow, row) == kNoRow) {
-          s_hidx[h] = (uint32_t)tid;
-          break;
-        }
-        h = (h + 1) & (kHotSlots - 1);
-      }
-    }
-  }
-  // windows of this workgroup: blockIdx.x, blockIdx.x + gridDim.x, ...
-  const int64_t wstep = gridDim.x;
-  // the first window's non-zeros of this thread: window positions tid + i * kWin
-  uint64_t nkey[WPT];
-  float nx[WPT];
-#pragma unroll
-  for (int i = 0; i < WPT; ++i) {
-    nkey[i] = 0;
-    nx[i] = 0.f;
-    const int64_t k = (int64_t)blockIdx.x * W + tid + i * kWin;
-    if ((int64_t)blockIdx.x < nwin && k < p.n) {
-      nkey[i] = p.keys[k];
-      nx[i] = p.vals[k];
-    }
-  }
-  constexpr int NO = N > 1 ? N - 1 : 1;          // other modes
-  __amdgpu_buffer_rsrc_t rs[NO];
-  const void* ap[NO];
-#pragma unroll
-  for (int j = 0; j + 1 < N; ++j) {
-    const int m = (j < p.mode) ? j : j + 1;
-    ap[j] = p.A[m];
-    rs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.A[m]), 0, (int)p.abytes[m],
-                                              (int)kBufFlags);
-  }
-  // the target mode's factor (read by the fused residual walk only)
-  const __amdgpu_buffer_rsrc_t rs_t = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(p.A[RES ? p.mode : 0]), 0, RES ? (int)p.abytes[p.mode] : 0,
-      (int)kBufFlags);
-  const float scale = term_scale(p);
-  const int g = tid / LPN;
-  const int rl = tid % LPN;
-  const int p0 = g * PPG;
-  const uint64_t gmask = PPG >= 64 ? ~0ULL : ((1ULL << PPG) - 1);
-
-  for (int64_t win = blockIdx.x; win < nwin; win += wstep) {
-    const int64_t k0 = win * W;
-    const int nvalid = (int)min((int64_t)W, p.n - k0);
-
-    // ---- processing: decode, group by target
-    uint32_t c[WPT][N], tgt[WPT], tfield[WPT], bkt[WPT], rank[WPT];
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int wp = tid + i * kWin;   // position in the window
-      if (wp < nvalid) {
-        decode<N>(p, nkey[i], p.base + k0 + wp, c[i]);
-      } else {
-#pragma unroll
-        for (int m = 0; m < N; ++m) c[i][m] = 0;
-      }
-      tgt[i] = 0;
-#pragma unroll
-      for (int m = 0; m < N; ++m)
-        if (m == p.mode) tgt[i] = c[i][m];
-    }
-    for (int i = tid; i < NB; i += kWin) s_hist[i] = 0;
-    __syncthreads();   // also: the stash lookup is built, the previous window is done
-    // counting sort on a hash of the target; a frequent row has bucket = its
-    // stash index, the other targets share the remaining buckets (two targets
-    // sharing a bucket may interleave, which only splits a segment)
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const bool valid = tid + i * kWin < nvalid;
-      tfield[i] = tgt[i];
-      const int hs = (K > 0 && valid) ? hot_lookup(s_hkey, s_hidx, tgt[i]) : -1;
-      if (hs >= 0) {
-        bkt[i] = (uint32_t)hs;
-        tfield[i] = kHotFlag | (uint32_t)hs;
-      } else {
-        const uint32_t h = tgt[i] * 0x9E3779B1u;
-        bkt[i] = (uint32_t)K + (uint32_t)(((uint64_t)h * (uint32_t)(NB - K)) >> 32);
-      }
-      rank[i] = valid ? atomicAdd(&s_hist[bkt[i]], 1u) : 0u;
-    }
-    __syncthreads();
-    block_exclusive_scan<NB, kWin>(s_hist, tid, s_wsum);
-    // record at the grouped position: fields 0..N-2 the byte offsets (row
-    // indices when BIG) of the other modes' factor rows in ascending mode
-    // order, field N-1 the target field, field N the value; padding positions
-    // (nvalid and above) stay where they are
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int wp = tid + i * kWin;
-      const int pos = wp < nvalid ? (int)(s_hist[bkt[i]] + rank[i]) : wp;
-#pragma unroll
-      for (int j = 0; j + 1 < N; ++j) {
-        const uint32_t cj = (j < p.mode) ? c[i][j] : c[i][j + 1];
-        s_rec[pos * NP + j] = BIG ? cj : cj * p.rowbytes;
-      }
-      s_rec[pos * NP + N - 1] = tfield[i];
-      s_rec[pos * NP + N] = __float_as_uint(wp < nvalid ? nx[i] : 0.f);
-      if constexpr (RES) {
-        s_rec[pos * NP + N + 1] = tgt[i] * p.rowbytes;
-        s_rec[pos * NP + N + 2] = (uint32_t)wp;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int wp = tid + i * kWin;
-      const uint32_t t0 = s_rec[wp * NP + N - 1];
-      const bool end = (wp < nvalid) && (wp == nvalid - 1 || s_rec[(wp + 1) * NP + N - 1] != t0);
-      const uint64_t em = __ballot(end);
-      if (lane == 0) s_end[wp >> 6] = em;
-    }
-    // the next window's non-zeros, in flight during this walk
-    if constexpr (STASH) {
-#pragma unroll
-      for (int i = 0; i < WPT; ++i) {
-        const int64_t k = (win + wstep) * W + tid + i * kWin;
-        if (win + wstep < nwin && k < p.n) {
-          nkey[i] = p.keys[k];
-          nx[i] = p.vals[k];
-        }
-      }
-    }
-    __syncthreads();
-
-    // ---- computing: LPN lanes per group, RPL ranks per lane (lane j holds
-    // ranks j, j + LPN, ... for fp32 factors, ranks RPL*j .. RPL*j + RPL - 1 for
-    // bf16), each group walking LPN consecutive positions
-    const uint64_t endw = s_end[p0 >> 6] >> (p0 & 63);
-    const bool starts_before =
-        p0 > 0 && p0 < nvalid && !((s_end[(p0 - 1) >> 6] >> ((p0 - 1) & 63)) & 1);
-    const bool can_carry = p0 + PPG <= nvalid;
-    // 3-mode tensors with 16-lane groups (one DPP row per group): the walk
-    // takes record fields from registers.  Lane rl of a group starts with the
-    // record of the group's position rl; each step of U positions broadcasts
-    // lanes 0..U-1 of the row and then shifts the row down by U lanes.  (For
-    // other mode counts the extra registers cost more than the LDS reads save.)
-    constexpr bool kRowB = (LPN == 16) && (N == 3);
-    for (int r0 = 0; r0 < R; r0 += LPN * RPL) {
-      uint32_t myrec[kRowB ? NF : 1];
-      bool ract[RPL];
-      uint32_t loff[RPL];
-      float acc[RPL], carry[RPL];
-#pragma unroll
-      for (int k = 0; k < RPL; ++k) {
-        const int r = PACKED ? r0 + rl * RPL + k : r0 + rl + k * LPN;
-        ract[k] = r < R;
-        loff[k] = (uint32_t)(ract[k] ? r : 0) * (uint32_t)sizeof(FT);
-        acc[k] = 0.f;
-        carry[k] = 0.f;
-      }
-      bool first = true, has_carry = false;
-      for (int q0 = 0; q0 < PPG; q0 += U) {
-        if constexpr (kRowB) {
-          // the records of the next LPN positions, one per lane
-          if (q0 % LPN == 0) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) myrec[f] = s_rec[(p0 + q0 + rl) * NP + f];
-          }
-        }
-        float pr[U][RPL];
-        float ta[RES ? U : 1][RPL];
-        float xs[RES ? U : 1];
-        uint32_t wpos[RES ? U : 1];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          // the record of position q0 + u: from the row, or from LDS
-          uint32_t e[NF];
-#pragma unroll
-          for (int f = 0; f < NF; ++f)
-            if (f != N - 1) {
-              if constexpr (kRowB) e[f] = row_bcast(myrec[f], u);
-            }
-          const uint32_t* er = &s_rec[(p0 + q0 + u) * NP];
-          const float xv = __uint_as_float(kRowB ? e[N] : er[N]);
-#pragma unroll
-          for (int k = 0; k < RPL; ++k) pr[u][k] = RES ? 1.f : xv;
-          if constexpr (RES) {
-            xs[u] = xv;
-            const uint32_t toff = kRowB ? e[N + 1] : er[N + 1];
-            wpos[u] = kRowB ? e[N + 2] : er[N + 2];
-            if constexpr (PACKED) {
-              ld_bf16_run<RPL, VEC>(rs_t, toff + loff[0], ta[u]);
-            } else {
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) ta[u][k] = ld_buf<FT>(rs_t, toff + loff[k]);
-            }
-          }
-#pragma unroll
-          for (int j = 0; j + 1 < N; ++j) {
-            const uint32_t f = kRowB ? e[j] : er[j];
-            if constexpr (BIG && PACKED) {
-              const FT* rowp = static_cast<const FT*>(ap[j]) + (size_t)f * R;
-              float t3[RPL];
-              ld_bf16_run_ptr<RPL, VEC>(rowp + loff[0] / sizeof(FT), ract, t3);
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) pr[u][k] *= t3[k];
-            } else if constexpr (BIG) {
-              const FT* rowp = static_cast<const FT*>(ap[j]) + (size_t)f * R;
-#pragma unroll
-              for (int k = 0; k < RPL; ++k)
-                pr[u][k] *= ld_factor<FT>(rowp, (size_t)(loff[k] / sizeof(FT)));
-            } else if constexpr (PACKED) {
-              float t3[RPL];
-              ld_bf16_run<RPL, VEC>(rs[j], f + loff[0], t3);
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) pr[u][k] *= t3[k];
-            } else if constexpr (BASE32) {
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) pr[u][k] *= ld_base(ap[j], f + loff[k]);
-            } else {
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) pr[u][k] *= ld_buf<FT>(rs[j], f + loff[k]);
-            }
-          }
-        }
-        if constexpr (RES) {
-          // model at each position (sum over the group's 16 lanes), residual, and
-          // the residual-scaled product of the other modes' rows
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            float part = 0.f;
-#pragma unroll
-            for (int k = 0; k < RPL; ++k)
-              if (ract[k]) part += pr[u][k] * ta[u][k];
-#pragma unroll
-            for (int off = LPN / 2; off > 0; off >>= 1) part += __shfl_xor(part, off);
-            const float ev = xs[u] - part;
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) pr[u][k] *= ev;
-            if (rl == 0 && (int)wpos[u] < nvalid) p.resid[k0 + wpos[u]] = ev;
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = q0 + u;
-#pragma unroll
-          for (int k = 0; k < RPL; ++k) acc[k] += pr[u][k];
-          const bool seg_end = (endw >> q) & 1;
-          if (seg_end || (q == PPG - 1 && can_carry)) {
-            if (first && starts_before) {
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) s_head[tid * RPL + k] = acc[k];
-            } else if (seg_end) {
-              const uint32_t tf = kRowB ? row_bcast(myrec[N - 1], u)
-                                        : seg_target(s_rec, (p0 + q) * NP, p.mode, N);
-              if (K > 0 && (tf & kHotFlag)) {
-                float* srow = s_stash + (size_t)(tf & ~kHotFlag) * R + r0 + (PACKED ? rl * RPL : rl);
-#pragma unroll
-                for (int k = 0; k < RPL; ++k)
-                  if (ract[k]) srow[PACKED ? k : k * LPN] += acc[k];
-              } else {
-                const size_t row = (size_t)tf * R;
-                if constexpr (PACKED) {
-                  flush_packed<RPL, LPN>(p.out + row + r0, acc, scale, rl, R - r0);
-                } else {
-#pragma unroll
-                  for (int k = 0; k < RPL; ++k)
-                    if (ract[k]) unsafeAtomicAdd(p.out + row + r0 + rl + k * LPN, acc[k] * scale);
-                }
-              }
-            } else {
-#pragma unroll
-              for (int k = 0; k < RPL; ++k) carry[k] = acc[k];
-              has_carry = true;
-            }
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) acc[k] = 0.f;
-            first = false;
-          }
-        }
-        if constexpr (kRowB) {
-#pragma unroll
-          for (int f = 0; f < NF; ++f) myrec[f] = row_shl(myrec[f], U);
-        }
-      }
-      __syncthreads();
-      if (has_carry) {
-        // this group owns a segment that continues into the next groups
-        for (int g2 = g + 1; g2 < G; ++g2) {
-          const int q2 = g2 * PPG;
-#pragma unroll
-          for (int k = 0; k < RPL; ++k) carry[k] += s_head[(g2 * LPN + rl) * RPL + k];
-          if ((s_end[q2 >> 6] >> (q2 & 63)) & gmask) break;
-        }
-        const uint32_t tf = seg_target(s_rec, (p0 + PPG - 1) * NP, p.mode, N);
-        if (K > 0 && (tf & kHotFlag)) {
-          float* srow = s_stash + (size_t)(tf & ~kHotFlag) * R + r0 + (PACKED ? rl * RPL : rl);
-#pragma unroll
-          for (int k = 0; k < RPL; ++k)
-            if (ract[k]) srow[PACKED ? k : k * LPN] += carry[k];
-        } else {
-          const size_t row = (size_t)tf * R;
-          if constexpr (PACKED) {
-            flush_packed<RPL, LPN>(p.out + row + r0, carry, scale, rl, R - r0);
-          } else {
-#pragma unroll
-            for (int k = 0; k < RPL; ++k)
-              if (ract[k]) unsafeAtomicAdd(p.out + row + r0 + rl + k * LPN, carry[k] * scale);
-          }
-        }
-      }
-      __syncthreads();
-    }
-    if constexpr (!STASH) break;
-  }
-  // ---- the stash of frequent rows: one atomic per (row, rank) that received a term
-  if (K > 0) {
-    __syncthreads();
-    for (int i = tid; i < K * R; i += kWin) {
-      const float v = s_stash[i];
-      const int hr = i / R;
-      if (v != 0.f) unsafeAtomicAdd(p.out + (size_t)p.hot[hr] * R + (i - hr * R), v * scale);
-    }
+  if (q == 0 && r < R) {
+    const float v = (s_part[r] + s_part[64 + r]) + (s_part[128 + r] + s_part[192 + r]);
+    if (v != 0.f) out[(size_t)hot[blockIdx.x] * R + r] += v;
   }
 }
 
@@ -1190,99 +546,6 @@ __global__ __launch_bounds__(256) void k_scale(float* __restrict__ x, int64_t n,
 
 // ====================================================================== dispatch
 
-typedef void (*KernelFn)(KParams);
-
-template <int LPN, int RPL, typename FT, bool BIG, bool STASH, bool VEC>
-static KernelFn pick_win_s(int N) {
-  switch (N) {
-    case 1: return k_mttkrp_win<LPN, RPL, FT, 1, BIG, STASH, false, VEC>;
-    case 2: return k_mttkrp_win<LPN, RPL, FT, 2, BIG, STASH, false, VEC>;
-    case 3: return k_mttkrp_win<LPN, RPL, FT, 3, BIG, STASH, false, VEC>;
-    case 4: return k_mttkrp_win<LPN, RPL, FT, 4, BIG, STASH, false, VEC>;
-    case 5: return k_mttkrp_win<LPN, RPL, FT, 5, BIG, STASH, false, VEC>;
-    case 6: return k_mttkrp_win<LPN, RPL, FT, 6, BIG, STASH, false, VEC>;
-    case 7: return k_mttkrp_win<LPN, RPL, FT, 7, BIG, STASH, false, VEC>;
-    default: return k_mttkrp_win<LPN, RPL, FT, 8, BIG, STASH, false, VEC>;
-  }
-}
-
-// windows of 2048 or 4096 non-zeros (two or four per thread; no stash), up to 5 modes
-constexpr int kWideMaxN = 5;
-template <int LPN, int RPL, typename FT, bool BIG, bool VEC, int WPT>
-static KernelFn pick_win_wide(int N) {
-  switch (N) {
-    case 1: return k_mttkrp_win<LPN, RPL, FT, 1, BIG, false, false, VEC, WPT>;
-    case 2: return k_mttkrp_win<LPN, RPL, FT, 2, BIG, false, false, VEC, WPT>;
-    case 3: return k_mttkrp_win<LPN, RPL, FT, 3, BIG, false, false, VEC, WPT>;
-    case 4: return k_mttkrp_win<LPN, RPL, FT, 4, BIG, false, false, VEC, WPT>;
-    default: return k_mttkrp_win<LPN, RPL, FT, 5, BIG, false, false, VEC, WPT>;
-  }
-}
-
-// Non-zeros per thread of the window kernel: for a plain MTTKRP without a stash over
-// 16-lane groups and at most kWideMaxN modes, two at R <= 32 and four at 32 < R <= 64
-// (four ranks per lane); else one.
-static int win_wpt(int N, int R, bool stash, bool resid) {
-  if (stash || resid || R > 64 || N > kWideMaxN) return 1;
-  return R > 32 ? 4 : 2;
-}
-
-// VEC (vector gathers of packed bf16 ranks) only where the ranks are packed: bf16
-// factors, two or more ranks per lane, and an even R
-template <int LPN, int RPL, typename FT, bool BIG>
-static KernelFn pick_win(int N, int R, bool stash) {
-  // the wide window of this rank layout (win_wpt's rule: four ranks per lane take four)
-  constexpr int WW = RPL == 4 ? 4 : 2;
-  const bool wide = win_wpt(N, R, stash, false) > 1;
-  if constexpr (sizeof(FT) == 2 && RPL > 1) {
-    if (R % 2 == 0) {
-      if constexpr (LPN == 16)
-        if (wide) return pick_win_wide<LPN, RPL, FT, BIG, true, WW>(N);
-      return stash ? pick_win_s<LPN, RPL, FT, BIG, true, true>(N)
-                   : pick_win_s<LPN, RPL, FT, BIG, false, true>(N);
-    }
-  }
-  if constexpr (LPN == 16)
-    if (wide) return pick_win_wide<LPN, RPL, FT, BIG, false, WW>(N);
-  return stash ? pick_win_s<LPN, RPL, FT, BIG, true, false>(N)
-               : pick_win_s<LPN, RPL, FT, BIG, false, false>(N);
-}
-
-// the fused residual walk (16-lane groups, one rank slice of at most 64, 32-bit offsets)
-template <int RPL, typename FT, bool STASH, bool VEC>
-static KernelFn pick_res_s(int N) {
-  switch (N) {
-    case 1: return k_mttkrp_win<16, RPL, FT, 1, false, STASH, true, VEC>;
-    case 2: return k_mttkrp_win<16, RPL, FT, 2, false, STASH, true, VEC>;
-    case 3: return k_mttkrp_win<16, RPL, FT, 3, false, STASH, true, VEC>;
-    case 4: return k_mttkrp_win<16, RPL, FT, 4, false, STASH, true, VEC>;
-    case 5: return k_mttkrp_win<16, RPL, FT, 5, false, STASH, true, VEC>;
-    case 6: return k_mttkrp_win<16, RPL, FT, 6, false, STASH, true, VEC>;
-    case 7: return k_mttkrp_win<16, RPL, FT, 7, false, STASH, true, VEC>;
-    default: return k_mttkrp_win<16, RPL, FT, 8, false, STASH, true, VEC>;
-  }
-}
-
-template <int RPL, typename FT>
-static KernelFn pick_res(int N, int R, bool stash) {
-  if constexpr (sizeof(FT) == 2 && RPL > 1) {
-    if (R % 2 == 0)
-      return stash ? pick_res_s<RPL, FT, true, true>(N) : pick_res_s<RPL, FT, false, true>(N);
-  }
-  return stash ? pick_res_s<RPL, FT, true, false>(N) : pick_res_s<RPL, FT, false, false>(N);
-}
-
-template <typename FT>
-static KernelFn select_res_t(int N, int R, bool stash) {
-  if (R <= 16) return pick_res<1, FT>(N, R, stash);
-  if (R <= 32) return pick_res<2, FT>(N, R, stash);
-  return pick_res<4, FT>(N, R, stash);
-}
-
-static KernelFn select_res(int N, int R, int fdt, bool stash) {
-  return fdt == BLCO_F32 ? select_res_t<float>(N, R, stash) : select_res_t<uint16_t>(N, R, stash);
-}
-
 typedef void (*ShortFn)(KParams, int64_t);
 
 template <int RPL, typename FT, bool BIG, bool VEC>
@@ -1380,23 +643,6 @@ static KernelFn pick_loss(int N, int R) {
   return pick_loss_v<RPL, FT, BIG, false>(N);
 }
 
-// window kernel shape (lanes per non-zero x ranks per lane), chosen by measurement on
-// the Zipf workloads: R <= 16: 16 x 1; R <= 32: 16 x 2 (8 x 4 was 1.8x slower);
-// R <= 64: 16 x 4 (10% faster than 32 x 2); larger: 64 x 2 per pass over the rank
-template <typename FT, bool BIG>
-static KernelFn select_win_t(int N, int R, bool stash) {
-  if (R <= 16) return pick_win<16, 1, FT, BIG>(N, R, stash);
-  if (R <= 32) return pick_win<16, 2, FT, BIG>(N, R, stash);
-  if (R <= 64) return pick_win<16, 4, FT, BIG>(N, R, stash);
-  return pick_win<64, 2, FT, BIG>(N, R, stash);
-}
-
-static KernelFn select_win(int N, int R, int fdt, bool big, bool stash) {
-  if (fdt == BLCO_F32)
-    return big ? select_win_t<float, true>(N, R, stash) : select_win_t<float, false>(N, R, stash);
-  return big ? select_win_t<uint16_t, true>(N, R, stash) : select_win_t<uint16_t, false>(N, R, stash);
-}
-
 template <typename FT, bool BIG>
 static KernelFn select_loss_t(int N, int R) {
   if (R <= 16) return pick_loss<1, FT, BIG>(N, R);
@@ -1443,9 +689,9 @@ static size_t kernel_static_lds(const void* f) {
   return v;
 }
 
-// LDS per window-kernel workgroup: half a CU's (two resident workgroups),
-// at most the per-workgroup limit; read once per device.
-static size_t win_lds_budget() {
+// LDS a workgroup may use on the current device: a CU's, at most the per-workgroup limit;
+// read once per device.
+static size_t cu_lds() {
   static size_t cached[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 64 * 1024;
@@ -1457,7 +703,22 @@ static size_t win_lds_budget() {
     if (hipDeviceGetAttribute(&blk, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
         blk <= 0)
       blk = 64 * 1024;
-    cached[dev] = std::min<size_t>((size_t)cu / 2, (size_t)blk);
+    cached[dev] = std::min<size_t>((size_t)cu, (size_t)blk);
+  }
+  return cached[dev];
+}
+
+// LDS per window-kernel workgroup where two share a CU.
+static size_t win_lds_budget() {
+  static size_t cached[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 64 * 1024;
+  if (!cached[dev]) {
+    int cu = 0;
+    if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
+            hipSuccess || cu <= 0)
+      cu = 64 * 1024;
+    cached[dev] = std::min<size_t>((size_t)cu / 2, cu_lds());
   }
   return cached[dev];
 }
@@ -1484,10 +745,13 @@ static void fill_params(const blco_tensor* t, KParams* p) {
   p->scale = 1.0f;
 }
 
-static int fill_zero(float* out, int64_t n, hipStream_t s) {
-  if (n <= 0) return BLCO_OK;
-  int64_t blocks = std::min<int64_t>((n / 4 + 255) / 256 + 1, 8192);
-  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, out, n);
+static int fill_zero(float* out, int64_t n, hipStream_t s, float* out2 = nullptr,
+                     int64_t n2 = 0) {
+  const int64_t most = std::max(n, n2);
+  if (most <= 0) return BLCO_OK;
+  int64_t blocks = std::min<int64_t>((most / 4 + 255) / 256 + 1, 8192);
+  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, out,
+                     std::max<int64_t>(n, 0), out2, n2);
   HIPCHK(hipGetLastError());
   return BLCO_OK;
 }
@@ -1507,6 +771,38 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
   int sw = 0;
   const int res = resolve(t, mode, rank, &sw);
   return res < 0 ? res : BLCO_OK;
+}
+
+// Window of the window kernel over n non-zeros without a stash, as k_mttkrp_win's WPT:
+// the smallest window that needs no more windows than the device has compute units, up
+// to the largest that pays in a long launch (2048 non-zeros; 4096 at R > 32, where four
+// ranks per lane cover the gathers of the one workgroup per CU it allows).  A short
+// launch is bound by the latency of one window: with 1000 x 500 x 300 uniform indices,
+// 30k non-zeros took 16.1 us in windows of 2048 (43 us in windows of 4096 at R = 64) and
+// take 6 us (9 us) in windows of 256.  More windows than compute units cost more than they
+// save, in row flushes and in the chain of same-row flushes of a skewed mode: 250k power-law
+// non-zeros at R = 16 take 23, 17, 13 and 18 us in windows of 256, 512, 1024 and 2048.
+//
+// At R > 32 a window of 2048 leaves two workgroups per CU and is the faster where rows
+// repeat (5M non-zeros of 2000 x 1000 x 500, R = 64: 0.13 and 0.18 ms per mode; 5 modes,
+// R = 35: 0.30 and 0.41 ms); one of 4096 merges more where they do not, on flat modes
+// (50M non-zeros of 2^24 x 2^22 x 2^20 x 2^10, R = 64 bf16, its last two: 4.37 and 2.80 ms in
+// windows of 2048, 3.83 and 2.48 ms).
+static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n) {
+  if (R > 64 || N > kWideMaxN) return 1;
+  // the fused residual walk's records hold one field more: at N = 5 two windows of 2048 no
+  // longer share a CU, and at R > 32 its walk has no registers for four per thread
+  const int most = resid ? (N <= 4 ? 2 : 1) : R > 32 && R % 16 == 0 && flat ? 4 : 2;
+  if (big) return most;
+  const int64_t cus = device_cus();
+  for (int w : {-4, -2, 1, 2})
+    if (w == most || n <= (w < 0 ? kWin / -w : kWin * w) * cus) return w;
+  return most;
+}
+
+static KernelFn select_win(int N, int R, int fdt, bool big, bool stash, int wpt) {
+  if (big) return select_win_big(N, R, fdt, stash, wpt);
+  return fdt == BLCO_F32 ? select_win_f32(N, R, stash, wpt) : select_win_bf16(N, R, stash, wpt);
 }
 
 // Frequent rows of the target mode that the window kernel `f` keeps in its
@@ -1530,14 +826,113 @@ static int stash_rows(const blco_tensor* t, int mode, int rank, KernelFn f) {
   return K;
 }
 
-// Launch the MTTKRP kernel over [lo, lo + n) of the tensor given by keys/vals.
+// Whether mode `mode` at rank `rank` may take hot copies (see k_mttkrp_win) instead of the
+// full stash, which is tied to windows of 1024 non-zeros: 2048 merge about as much without
+// its look-up and its resident workgroups.  An explicit threshold at build time keeps the
+// full stash.
+static bool copies_ok(const blco_tensor* t, int mode, int rank, bool big) {
+  return !t->hot_forced && !big && t->lay.N <= kWideMaxN && rank <= 64 && t->d_tab &&
+         t->lay.dims[mode] * (uint64_t)rank <= (1ULL << 31);
+}
+
+// Whether a mode has rows worth keeping apart: not where the rows beyond the recorded ones
+// are about as frequent as they are (every row then has equally long chains of atomics).
+static bool has_frequent_rows(const blco_tensor* t, int mode) {
+  if (t->nhot[mode] <= 0 || !t->d_hot) return false;
+  const uint64_t* cnt = t->hot_cnt.data() + (size_t)mode * (kHotMax + 1);
+  return t->hot_forced || cnt[t->nhot[mode]] * 4 <= cnt[0];
+}
+
+// A launch of at most this many windows needs no copies: its hottest rows see no more
+// atomics than the full stash's own flushes would make.
+constexpr int64_t kCopyMinWindows = 2048;
+constexpr int kCopyMax = 64;   // most copies of a row
+
+// Copies of each frequent row: at most about 4096 additions to one (the sums are then no
+// further from 64 bits than with the full stash, measured on the 50M- and 200M-non-zero
+// power-law tensors; more copies cost more to clear and add up).
+static int copy_count(int64_t nwin) {
+  int c = 1;
+  while (c < kCopyMax && (int64_t)c * 4096 < nwin) c *= 2;
+  return c;
+}
+
+static int copy_stride(int rank) { return (rank + 15) / 16 * 16; }   // whole 64-byte lines
+
+static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool window,
+                        bool resid);
+
+// The window kernel a launch over n non-zeros takes: its instantiation, windows, frequent
+// rows in LDS and the slots of their look-up table.
+struct WinPlan {
+  KernelFn f;
+  int wpt;
+  int64_t nwin;
+  int stash;     // rows in the full stash
+  int copies;    // copies of each row in the row table (0: none)
+  size_t bytes;  // workspace of the copies
+};
+
+// room: bytes of workspace the call has; copies that do not fit it are not taken, and the
+// mode falls back to the full stash where that applies.
+static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int fdt, bool big, bool resid,
+                        int64_t n, size_t room) {
+  const int N = t->lay.N;
+  auto pick = [&](bool stash, int w) {
+    return resid ? select_res(N, rank, fdt, stash, w) : select_win(N, rank, fdt, big, stash, w);
+  };
+  auto windows = [&](int w) {
+    const int64_t W = w < 0 ? kWin / -w : (int64_t)kWin * w;
+    return (n + W - 1) / W;
+  };
+  const bool frequent = has_frequent_rows(t, mode);
+  WinPlan w = {nullptr, win_wpt(N, rank, resid, big, !frequent, n), 0, 0, 0, 0};
+  // one non-zero per thread (the residual walk at N = 5): -1 is the form with copies
+  const int lw = w.wpt == 1 ? -1 : w.wpt;
+  const bool few = windows(lw) <= kCopyMinWindows;
+  if (frequent && copies_ok(t, mode, rank, big) && (few || (lw != -1 || resid))) {
+    if (few) {
+      w.f = pick(false, w.wpt);
+      w.nwin = windows(w.wpt);
+      return w;
+    }
+    const int c = copy_count(windows(lw));
+    const size_t bytes = sizeof(float) * (size_t)t->nhot[mode] * c * copy_stride(rank);
+    if (bytes <= room) {
+      w.f = pick(true, lw);
+      w.wpt = lw;
+      w.nwin = windows(lw);
+      w.copies = c;
+      w.bytes = bytes;
+      return w;
+    }
+  }
+  if (frequent) {
+    w.f = pick(true, 1);
+    w.stash = stash_rows(t, mode, rank, w.f);
+    if (w.stash > 0) w.wpt = 1;
+  }
+  if (w.stash == 0) w.f = pick(false, w.wpt);
+  w.nwin = windows(w.wpt);
+  return w;
+}
+
+// Workspace of a call: device memory the caller lends it (may be empty).
+struct Work {
+  char* p = nullptr;
+  size_t bytes = 0;
+};
+
+// Launch the MTTKRP kernel over [lo, lo + n) of the tensor given by keys/vals, clearing the
+// output first if `clear`.
 // With resid != nullptr the fused residual walk runs instead (the caller has
 // checked fused_mode_ok): resid[0, n) receives the residual of each non-zero.
 static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float* vals,
                          int64_t lo, int64_t n, int mode, const void* const* factors, int fdt,
                          int rank, float scale, const double* scale_dev, float* out,
-                         hipStream_t s, float* resid = nullptr) {
-  if (n <= 0) return BLCO_OK;
+                         hipStream_t s, const Work& ws, bool clear, float* resid = nullptr) {
+  const int64_t clear_n = clear ? (int64_t)t->lay.dims[mode] * rank : 0;
+  if (n <= 0) return fill_zero(out, clear_n, s);
   KParams p;
   fill_params(t, &p);
   p.keys = keys;
@@ -1552,19 +947,12 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
   p.scale_dev = scale_dev;
   const size_t fsz = factor_elem_bytes(fdt);
   p.rowbytes = (uint32_t)((size_t)rank * fsz);
-  // factors below 4 GiB are gathered with 32-bit byte offsets, larger ones
-  // with 64-bit addresses; the window kernel's fp32 gathers at 33-64 ranks
-  // (ld_base) also take a factor of exactly 4 GiB with 32-bit offsets
-  const bool row_big = (size_t)rank * fsz >= (1ULL << 31);
-  size_t other = 0;
   for (int m = 0; m < t->lay.N; ++m) {
     const size_t bytes = (size_t)t->lay.dims[m] * rank * fsz;
     p.abytes[m] = (uint32_t)std::min<size_t>(bytes, 0xFFFFFFFFull);
-    if (m != mode) other = std::max(other, bytes);
   }
-  const bool big = row_big || other > 0xFFFFFFFFull;
-  const bool base32 = fdt == BLCO_F32 && rank > 32 && rank <= 64 && !resid;
-  const bool big_win = row_big || other > (base32 ? (1ULL << 32) : 0xFFFFFFFFull);
+  const bool big = big_gathers(t, mode, rank, fdt, false, false);
+  const bool big_win = big_gathers(t, mode, rank, fdt, true, resid != nullptr);
   int sw = 0;
   const int res = resolve(t, mode, rank, &sw);
   if (res < 0) return res;
@@ -1573,12 +961,16 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
     return set_error(BLCO_EUNSUPPORTED, "fused residual walk on mode %d", mode);
   p.resid = resid;
   if (res == BLCO_RES_HIERARCHICAL) {
+    int rc = fill_zero(out, clear_n, s);
+    if (rc) return rc;
     p.short_rows = (uint32_t)t->lay.dims[mode];
     p.short_width = sw;
     const int slices = (rank + sw - 1) / sw;
-    // two resident workgroups per CU over all slices; each takes an equal range
+    // two resident workgroups per CU over all slices; each takes an equal range of at
+    // least one batch (four batches left a short launch on a few CUs: 100k non-zeros,
+    // R = 32, 200 rows: 26 us with four, 10 us with one)
     const int64_t want = std::max<int64_t>(device_cus() * 2 / slices, 1);
-    int64_t per = std::max<int64_t>((n + want - 1) / want, (int64_t)kShortB * 4);
+    int64_t per = std::max<int64_t>((n + want - 1) / want, (int64_t)kShortB);
     per = (per + kShortB - 1) / kShortB * kShortB;
     const int64_t nwg = (n + per - 1) / per;
     const size_t lds = short_lds(t->lay.N, t->lay.dims[mode], sw);
@@ -1588,22 +980,39 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
     return BLCO_OK;
   }
   {
-    const int N = t->lay.N;
-    KernelFn f = resid ? select_res(N, rank, fdt, true) : select_win(N, rank, fdt, big_win, true);
-    const int K = stash_rows(t, mode, rank, f);
+    const WinPlan w = plan_win(t, mode, rank, fdt, big_win, resid != nullptr, n, ws.bytes);
+    const KernelFn f = w.f;
+    const int K = w.stash;
+    const int64_t nwin = w.nwin;
     p.hot = t->d_hot + (size_t)mode * kHotMax;
     p.nhot = K;
-    if (K == 0) f = resid ? select_res(N, rank, fdt, false) : select_win(N, rank, fdt, big_win, false);
-    const int64_t nwin = (n + (int64_t)kWin * win_wpt(N, rank, K > 0, resid) - 1) /
-                         ((int64_t)kWin * win_wpt(N, rank, K > 0, resid));
+    if (w.copies) {
+      p.tab = t->d_tab + (size_t)mode * kTabWords;
+      float* copy = reinterpret_cast<float*>(ws.p);
+      p.copy_off = reinterpret_cast<char*>(copy) - reinterpret_cast<char*>(out);
+      p.copies = w.copies;
+      p.copy_stride = copy_stride(rank);
+      int rc = fill_zero(out, clear_n, s, copy, (int64_t)(w.bytes / sizeof(float)));
+      if (rc) return rc;
+    } else {
+      int rc = fill_zero(out, clear_n, s);
+      if (rc) return rc;
+    }
     const size_t dyn = K > 0 ? (size_t)K * rank * 4 + 2 * (size_t)kHotSlots * 4 : 0;
     // with a stash: persistent workgroups, kWinRounds times the resident count
-    // (two per CU), which balances the end of the launch (measured 1-2% faster
-    // than one round) at the cost of more stash flushes; without one: a
-    // workgroup per window (measured about 1% faster than persistent ones)
+    // (two per CU) in a long launch, which balances its end (1-2% faster than one round
+    // on 50M non-zeros); once the resident count in a shorter one, where the stash
+    // flushes count more (2M non-zeros, R = 16: 68 us and 58 us); without one: a
+    // workgroup per window (about 1% faster than persistent ones)
+    const int rounds = nwin >= 16 * 1024 ? kWinRounds : 1;
     const int64_t grid =
-        K > 0 ? std::min<int64_t>(nwin, (int64_t)device_cus() * 2 * kWinRounds) : nwin;
+        K > 0 ? std::min<int64_t>(nwin, (int64_t)device_cus() * 2 * rounds) : nwin;
     hipLaunchKernelGGL(f, dim3((unsigned)grid), dim3(kWin), dyn, s, p);
+    if (w.copies) {
+      HIPCHK(hipGetLastError());
+      hipLaunchKernelGGL(k_hot_sum, dim3((unsigned)t->nhot[mode]), dim3(kBlock), 0, s,
+                         (const float*)ws.p, p.hot, p.copies, p.copy_stride, rank, out);
+    }
   }
   HIPCHK(hipGetLastError());
   return BLCO_OK;
@@ -1654,7 +1063,9 @@ static void release_device(blco_tensor* t) {
   if (t->d_tile_run) (void)hipFree(t->d_tile_run);
   if (t->d_partials) (void)hipFree(t->d_partials);
   if (t->d_hot) (void)hipFree(t->d_hot);
+  if (t->d_tab) (void)hipFree(t->d_tab);
   t->d_hot = nullptr;
+  t->d_tab = nullptr;
   t->d_keys = nullptr;
   t->d_vals = nullptr;
   t->d_run_start = nullptr;
@@ -1700,6 +1111,7 @@ extern "C" int blco_build(int nmodes, const uint64_t* dims, int64_t nnz,
     return rc;
   }
   find_hot_rows(coords, nnz, hot_min, t);
+  make_row_tables(t);
   t->hot_forced = hot_forced;
   if (placement == BLCO_PLACE_HOST) {
     *out = t;
@@ -1720,6 +1132,7 @@ extern "C" int blco_build(int nmodes, const uint64_t* dims, int64_t nnz,
   if ((rc = upload(&t->d_run_base, t->run_base.data(), t->run_base.size(), &acc))) return fail(rc);
   if ((rc = upload(&t->d_tile_run, t->tile_run.data(), t->tile_run.size(), &acc))) return fail(rc);
   if ((rc = upload(&t->d_hot, t->hot.data(), t->hot.size(), &acc))) return fail(rc);
+  if ((rc = upload(&t->d_tab, t->tab.data(), t->tab.size(), &acc))) return fail(rc);
   if (placement == BLCO_PLACE_DEVICE) {
     if ((rc = upload(&t->d_keys, t->h_keys, (size_t)nnz, &acc))) return fail(rc);
     if ((rc = upload(&t->d_vals, t->h_vals, (size_t)nnz, &acc))) return fail(rc);
@@ -1730,44 +1143,101 @@ extern "C" int blco_build(int nmodes, const uint64_t* dims, int64_t nnz,
   return BLCO_OK;
 }
 
-extern "C" int blco_mttkrp_v(blco_tensor* t, int mode, const float* values,
-                             const void* const* factors, int factor_dtype, int rank,
-                             const double* scale, double alpha, float* out, void* stream) {
-  clear_error();
-  int rc = check_factor_args(t, mode, factors, factor_dtype, rank, out, false);
-  if (rc) return rc;
-  if (t->placement != BLCO_PLACE_DEVICE)
-    return set_error(BLCO_EINVAL, "in-memory MTTKRP needs a tensor placed on the device");
-  if (!values && t->nnz > 0) return set_error(BLCO_EINVAL, "values is NULL");
-  hipStream_t s = (hipStream_t)stream;
-  if ((rc = fill_zero(out, (int64_t)t->lay.dims[mode] * rank, s))) return rc;
-  return launch_mttkrp(t, t->d_keys, values, 0, t->nnz, mode, factors, factor_dtype, rank,
-                       (float)alpha, scale, out, s);
+// Whether a mode's launch gathers with 64-bit addresses in the window kernel / elsewhere:
+// factors below 4 GiB are gathered with 32-bit byte offsets, larger ones with 64-bit
+// addresses; the window kernel's fp32 gathers at 33-64 ranks (ld_base; not the fused
+// residual walk) also take a factor of exactly 4 GiB with 32-bit offsets.  An output of more
+// than 2^32 elements takes the window kernel's 64-bit form too (its records hold the output
+// row's first element in 32 bits).
+static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool window,
+                        bool resid) {
+  const size_t fsz = factor_elem_bytes(fdt);
+  if ((size_t)rank * fsz >= (1ULL << 31)) return true;
+  const bool base32 = window && fdt == BLCO_F32 && rank > 32 && rank <= 64 && !resid;
+  for (int m = 0; m < t->lay.N; ++m)
+    if (m != mode &&
+        (size_t)t->lay.dims[m] * rank * fsz > (base32 ? (1ULL << 32) : 0xFFFFFFFFull))
+      return true;
+  return window && (uint64_t)t->lay.dims[mode] * (uint64_t)rank > (1ULL << 32);
 }
 
-extern "C" int blco_mttkrp(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
-                           int rank, float* out, void* stream) {
-  clear_error();
+// Workspace the MTTKRP of mode `mode` over n non-zeros can use (0: none).
+static size_t mode_workspace(const blco_tensor* t, int mode, int rank, int fdt, bool resid,
+                             int64_t n) {
+  int sw = 0;
+  if (n <= 0 || resolve(t, mode, rank, &sw) != BLCO_RES_REGISTER) {
+    clear_error();
+    return 0;
+  }
+  return plan_win(t, mode, rank, fdt, big_gathers(t, mode, rank, fdt, true, resid), resid, n,
+                  ~(size_t)0)
+      .bytes;
+}
+
+// The in-memory MTTKRP calls, with an optional workspace.
+static int mttkrp_impl(blco_tensor* t, int mode, const float* values, const void* const* factors,
+                       int factor_dtype, int rank, const double* scale, double alpha,
+                       bool accumulate, float* out, const Work& ws, hipStream_t s) {
   int rc = check_factor_args(t, mode, factors, factor_dtype, rank, out, false);
   if (rc) return rc;
   if (t->placement != BLCO_PLACE_DEVICE)
     return set_error(BLCO_EINVAL, "in-memory MTTKRP needs a tensor placed on the device; "
                                   "use blco_mttkrp_stream for a pinned tensor");
-  hipStream_t s = (hipStream_t)stream;
-  if ((rc = fill_zero(out, (int64_t)t->lay.dims[mode] * rank, s))) return rc;
-  return launch_mttkrp(t, t->d_keys, t->d_vals, 0, t->nnz, mode, factors, factor_dtype, rank,
-                       1.0f, nullptr, out, s);
+  if (!values && t->nnz > 0) return set_error(BLCO_EINVAL, "values is NULL");
+  return launch_mttkrp(t, t->d_keys, values, 0, t->nnz, mode, factors, factor_dtype, rank,
+                       (float)alpha, scale, out, s, ws, !accumulate);
+}
+
+size_t blco::mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype) {
+  return mode_workspace(t, mode, rank, factor_dtype, false, t->nnz);
+}
+
+int blco::mttkrp_with(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
+                      int rank, float* out, void* ws, size_t ws_bytes, void* stream) {
+  return mttkrp_impl(t, mode, t->d_vals, factors, factor_dtype, rank, nullptr, 1.0, false, out,
+                     Work{static_cast<char*>(ws), ws_bytes}, (hipStream_t)stream);
+}
+
+static int make_work(void* ws, size_t bytes, Work* w) {
+  if (!ws && bytes > 0) return set_error(BLCO_EINVAL, "workspace is NULL");
+  if (reinterpret_cast<uintptr_t>(ws) & 255)
+    return set_error(BLCO_EINVAL, "workspace must be 256-byte aligned");
+  *w = Work{static_cast<char*>(ws), ws ? bytes : 0};
+  return BLCO_OK;
+}
+
+extern "C" int blco_mttkrp_v(blco_tensor* t, int mode, const float* values,
+                             const void* const* factors, int factor_dtype, int rank,
+                             const double* scale, double alpha, float* out, void* stream) {
+  clear_error();
+  return mttkrp_impl(t, mode, values, factors, factor_dtype, rank, scale, alpha, false, out,
+                     Work(), (hipStream_t)stream);
+}
+
+extern "C" int blco_mttkrp(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
+                           int rank, float* out, void* stream) {
+  clear_error();
+  return mttkrp_impl(t, mode, t ? t->d_vals : nullptr, factors, factor_dtype, rank, nullptr, 1.0,
+                     false, out, Work(), (hipStream_t)stream);
 }
 
 extern "C" int blco_mttkrp_acc(blco_tensor* t, int mode, const void* const* factors,
                                int factor_dtype, int rank, float* out, void* stream) {
   clear_error();
-  int rc = check_factor_args(t, mode, factors, factor_dtype, rank, out, false);
+  return mttkrp_impl(t, mode, t ? t->d_vals : nullptr, factors, factor_dtype, rank, nullptr, 1.0,
+                     true, out, Work(), (hipStream_t)stream);
+}
+
+extern "C" int blco_mttkrp_ws(blco_tensor* t, int mode, const float* values,
+                              const void* const* factors, int factor_dtype, int rank,
+                              const double* scale, double alpha, int accumulate, float* out,
+                              void* workspace, size_t workspace_bytes, void* stream) {
+  clear_error();
+  Work ws;
+  int rc = make_work(workspace, workspace_bytes, &ws);
   if (rc) return rc;
-  if (t->placement != BLCO_PLACE_DEVICE)
-    return set_error(BLCO_EINVAL, "in-memory MTTKRP needs a tensor placed on the device");
-  return launch_mttkrp(t, t->d_keys, t->d_vals, 0, t->nnz, mode, factors, factor_dtype, rank,
-                       1.0f, nullptr, out, (hipStream_t)stream);
+  return mttkrp_impl(t, mode, values ? values : (t ? t->d_vals : nullptr), factors, factor_dtype,
+                     rank, scale, alpha, accumulate != 0, out, ws, (hipStream_t)stream);
 }
 
 // Stream the pinned non-zeros once through two reused staging buffers and,
@@ -1858,13 +1328,13 @@ struct GradArgs {
 static int grad_range(blco_tensor* t, const GradArgs& g, const uint64_t* keys, const float* vals,
                       int64_t lo, int64_t n, const void* const* factors, int fdt, int rank,
                       float* const* outs, float* resid, double* part, int64_t* nparts,
-                      hipStream_t s) {
+                      hipStream_t s, const Work& ws, bool clear) {
   int rc;
   *nparts = 0;
   if (n <= 0) return BLCO_OK;
   if (g.m0 >= 0) {
     if ((rc = launch_mttkrp(t, keys, vals, lo, n, g.m0, factors, fdt, rank, g.scale, g.scale_dev,
-                            outs[g.m0], s, resid)))
+                            outs[g.m0], s, ws, clear, resid)))
       return rc;
     *nparts = (n + kSqPer - 1) / kSqPer;
     hipLaunchKernelGGL(k_sumsq, dim3((unsigned)*nparts), dim3(256), 0, s, (const float*)resid, n,
@@ -1877,7 +1347,7 @@ static int grad_range(blco_tensor* t, const GradArgs& g, const uint64_t* keys, c
   for (int m = 0; m < t->lay.N; ++m) {
     if (m == g.m0) continue;
     if ((rc = launch_mttkrp(t, keys, resid, lo, n, m, factors, fdt, rank, g.scale, g.scale_dev,
-                            outs[m], s)))
+                            outs[m], s, ws, clear)))
       return rc;
   }
   return BLCO_OK;
@@ -1890,7 +1360,7 @@ static int64_t grad_parts(int64_t n) {
 
 static int stream_modes(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
                         float* const* outs, size_t device_budget_bytes, hipStream_t s,
-                        const GradArgs* grad = nullptr) {
+                        Work ws, const GradArgs* grad = nullptr) {
   const Layout& L = t->lay;
   bool need[BLCO_MAX_MODES] = {};
   int nsel = 0;
@@ -1908,8 +1378,6 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
   }
   int rc;
   if (t->placement == BLCO_PLACE_DEVICE && grad) {
-    for (int m = 0; m < L.N; ++m)
-      if ((rc = fill_zero(outs[m], (int64_t)L.dims[m] * rank, s))) return rc;
     double* part = grad->partials;
     if (!part) {
       if ((rc = ensure_partials(t, grad_parts(t->nnz), s))) return rc;
@@ -1917,7 +1385,7 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     }
     int64_t np = 0;
     if ((rc = grad_range(t, *grad, t->d_keys, t->d_vals, 0, t->nnz, factors, factor_dtype, rank,
-                         outs, grad->resid, part, &np, s)))
+                         outs, grad->resid, part, &np, s, ws, true)))
       return rc;
     hipLaunchKernelGGL(k_reduce_loss, dim3(1), dim3(1024), 0, s, (const double*)part, np,
                        grad->loss);
@@ -1933,9 +1401,8 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
                        device_budget_bytes, fixed);
     for (int m = 0; m < L.N; ++m) {
       if (!outs[m]) continue;
-      if ((rc = fill_zero(outs[m], (int64_t)L.dims[m] * rank, s))) return rc;
       if ((rc = launch_mttkrp(t, t->d_keys, t->d_vals, 0, t->nnz, m, factors, factor_dtype, rank,
-                              1.0f, nullptr, outs[m], s)))
+                              1.0f, nullptr, outs[m], s, ws, true)))
         return rc;
     }
     t->stream_peak_bytes = fixed;
@@ -1947,6 +1414,9 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     return set_error(BLCO_EINVAL, "streaming needs a tensor in pinned host memory");
   // staging per non-zero: key and value, and the chunk's residual for the gradient
   const size_t per_nnz = sizeof(uint64_t) + sizeof(float) + (grad ? sizeof(float) : 0);
+  // a workspace counts against the budget, and is left out where the budget has no room
+  if (device_budget_bytes < fixed + ws.bytes + 2 * 64 * per_nnz) ws = Work();
+  fixed += ws.bytes;
   if (device_budget_bytes < fixed + 2 * 64 * per_nnz)
     return set_error(BLCO_ENOMEM, "budget %zu cannot hold factors + outputs + tables (%zu) and "
                                   "two staging buffers", device_budget_bytes, fixed);
@@ -2027,14 +1497,14 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     if (grad) {
       int64_t np = 0;
       if ((rc = grad_range(t, *grad, st.d_keys[b], st.d_vals[b], lo, cnt, factors, factor_dtype,
-                           rank, outs, st.d_res[b], t->d_partials + poff, &np, s)))
+                           rank, outs, st.d_res[b], t->d_partials + poff, &np, s, ws, false)))
         return rc;
       poff += np;
     } else {
       for (int m = 0; m < L.N; ++m) {
         if (!outs[m]) continue;
         if ((rc = launch_mttkrp(t, st.d_keys[b], st.d_vals[b], lo, cnt, m, factors, factor_dtype,
-                                rank, 1.0f, nullptr, outs[m], s)))
+                                rank, 1.0f, nullptr, outs[m], s, ws, false)))
           return rc;
       }
     }
@@ -2061,13 +1531,12 @@ extern "C" int blco_mttkrp_stream(blco_tensor* t, int mode, const void* const* f
   float* outs[BLCO_MAX_MODES] = {};
   outs[mode] = out;
   return stream_modes(t, factors, factor_dtype, rank, outs, device_budget_bytes,
-                      (hipStream_t)stream);
+                      (hipStream_t)stream, Work());
 }
 
-extern "C" int blco_mttkrp_stream_all(blco_tensor* t, const void* const* factors,
-                                      int factor_dtype, int rank, float* const* outs,
-                                      size_t device_budget_bytes, void* stream) {
-  clear_error();
+static int stream_all_impl(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
+                           float* const* outs, size_t device_budget_bytes, const Work& ws,
+                           hipStream_t stream) {
   if (!t) return set_error(BLCO_EINVAL, "tensor is NULL");
   if (!outs) return set_error(BLCO_EINVAL, "outs is NULL");
   float* o[BLCO_MAX_MODES] = {};
@@ -2089,8 +1558,27 @@ extern "C" int blco_mttkrp_stream_all(blco_tensor* t, const void* const* factors
       if (a < b + nb && b < a + na) return set_error(BLCO_EINVAL, "outs[%d] overlaps outs[%d]", m, j);
     }
   }
-  return stream_modes(t, factors, factor_dtype, rank, o, device_budget_bytes,
-                      (hipStream_t)stream);
+  return stream_modes(t, factors, factor_dtype, rank, o, device_budget_bytes, stream, ws);
+}
+
+extern "C" int blco_mttkrp_stream_all(blco_tensor* t, const void* const* factors,
+                                      int factor_dtype, int rank, float* const* outs,
+                                      size_t device_budget_bytes, void* stream) {
+  clear_error();
+  return stream_all_impl(t, factors, factor_dtype, rank, outs, device_budget_bytes, Work(),
+                         (hipStream_t)stream);
+}
+
+extern "C" int blco_mttkrp_stream_all_ws(blco_tensor* t, const void* const* factors,
+                                         int factor_dtype, int rank, float* const* outs,
+                                         size_t device_budget_bytes, void* workspace,
+                                         size_t workspace_bytes, void* stream) {
+  clear_error();
+  Work ws;
+  int rc = make_work(workspace, workspace_bytes, &ws);
+  if (rc) return rc;
+  return stream_all_impl(t, factors, factor_dtype, rank, outs, device_budget_bytes, ws,
+                         (hipStream_t)stream);
 }
 
 // ---- workspace of blco_cp_grad_noalloc: the fp64 partial sums of the loss live in
@@ -2125,7 +1613,7 @@ static int scratch_ptr(double** out) {
 static int cp_grad_impl(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
                         const double* scale, double alpha, float* residual, double* loss,
                         float* const* grads, size_t device_budget_bytes, void* stream,
-                        bool noalloc) {
+                        bool noalloc, const Work& work) {
   clear_error();
   if (!t) return set_error(BLCO_EINVAL, "tensor is NULL");
   if (!loss) return set_error(BLCO_EINVAL, "loss is NULL");
@@ -2184,7 +1672,7 @@ static int cp_grad_impl(blco_tensor* t, const void* const* factors, int factor_d
   g.resid = residual;
   g.loss = loss;
   g.partials = ws;
-  return stream_modes(t, factors, factor_dtype, rank, o, device_budget_bytes, s, &g);
+  return stream_modes(t, factors, factor_dtype, rank, o, device_budget_bytes, s, work, &g);
 }
 
 extern "C" int blco_cp_grad(blco_tensor* t, const void* const* factors, int factor_dtype,
@@ -2192,14 +1680,26 @@ extern "C" int blco_cp_grad(blco_tensor* t, const void* const* factors, int fact
                             double* loss, float* const* grads, size_t device_budget_bytes,
                             void* stream) {
   return cp_grad_impl(t, factors, factor_dtype, rank, scale, alpha, residual, loss, grads,
-                      device_budget_bytes, stream, false);
+                      device_budget_bytes, stream, false, Work());
+}
+
+extern "C" int blco_cp_grad_ws(blco_tensor* t, const void* const* factors, int factor_dtype,
+                               int rank, const double* scale, double alpha, float* residual,
+                               double* loss, float* const* grads, size_t device_budget_bytes,
+                               void* workspace, size_t workspace_bytes, void* stream) {
+  clear_error();
+  Work ws;
+  int rc = make_work(workspace, workspace_bytes, &ws);
+  if (rc) return rc;
+  return cp_grad_impl(t, factors, factor_dtype, rank, scale, alpha, residual, loss, grads,
+                      device_budget_bytes, stream, false, ws);
 }
 
 extern "C" int blco_cp_grad_noalloc(blco_tensor* t, const void* const* factors, int factor_dtype,
                                     int rank, const double* scale, double alpha, float* residual,
                                     double* loss, float* const* grads, void* stream) {
   return cp_grad_impl(t, factors, factor_dtype, rank, scale, alpha, residual, loss, grads, 0,
-                      stream, true);
+                      stream, true, Work());
 }
 
 extern "C" int blco_sampled_loss(blco_tensor* t, const void* const* factors, int factor_dtype,
@@ -2310,7 +1810,28 @@ extern "C" int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int*
   if (mode < 0 || mode >= t->lay.N)
     return set_error(BLCO_EINVAL, "mode %d outside 0..%d", mode, t->lay.N - 1);
   if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
-  *rows = stash_rows(t, mode, rank, select_win(t->lay.N, rank, BLCO_F32, false, true));
+  const WinPlan w = plan_win(t, mode, rank, BLCO_F32, false, false, std::max<int64_t>(t->nnz, 1), 0);
+  *rows = w.stash;
+  return BLCO_OK;
+}
+
+extern "C" int blco_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype,
+                              size_t* bytes) {
+  clear_error();
+  if (!t || !bytes) return set_error(BLCO_EINVAL, "tensor or bytes is NULL");
+  if (mode < -1 || mode >= t->lay.N)
+    return set_error(BLCO_EINVAL, "mode %d outside -1..%d", mode, t->lay.N - 1);
+  if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
+  if (factor_dtype != BLCO_F32 && factor_dtype != BLCO_BF16)
+    return set_error(BLCO_EINVAL, "factor dtype %d", factor_dtype);
+  size_t most = 0;
+  for (int m = 0; m < t->lay.N; ++m) {
+    if (mode >= 0 && m != mode) continue;
+    most = std::max(most, mode_workspace(t, m, rank, factor_dtype, false, t->nnz));
+    if (mode < 0 && fused_mode_ok(t, m, rank, factor_dtype))
+      most = std::max(most, mode_workspace(t, m, rank, factor_dtype, true, t->nnz));
+  }
+  *bytes = (most + 255) / 256 * 256;
   return BLCO_OK;
 }
 

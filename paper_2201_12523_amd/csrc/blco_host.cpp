@@ -388,6 +388,44 @@ void find_hot_rows(const uint32_t* const* coords, int64_t nnz, int64_t min_count
   for (auto& x : th) x.join();
 }
 
+void make_row_tables(blco_tensor* t) {
+  const int N = t->lay.N;
+  t->tab.assign((size_t)N * kTabWords, 0xFFFFFFFFu);
+  for (int n = 0; n < N; ++n) {
+    uint32_t* w = t->tab.data() + (size_t)n * kTabWords;
+    const uint32_t* hot = t->hot.data() + (size_t)n * kHotMax;
+    const int nh = t->nhot[n];
+    // a multiplier that keeps the most frequent 64 rows apart (about one in fifty does),
+    // or as many from the first as any of those tried
+    const int want = std::min(nh, 64);
+    uint32_t best = 0x9E3779B1u, m = 0x9E3779B1u;
+    int kept = -1;
+    for (int tries = 0; tries < 512 && kept < want; ++tries, m = m * 0x915F77F5u + 2u) {
+      uint64_t used[kTabSlots / 64] = {};
+      int k = 0;
+      for (; k < want; ++k) {
+        const uint32_t s = (hot[k] * m) >> (32 - kTabBits);
+        if ((used[s >> 6] >> (s & 63)) & 1) break;
+        used[s >> 6] |= 1ull << (s & 63);
+      }
+      if (k > kept) {
+        kept = k;
+        best = m;
+      }
+    }
+    // a row whose slot a more frequent one holds stays out of the table
+    w[0] = best;
+    uint8_t* idx = reinterpret_cast<uint8_t*>(w + 1 + kTabSlots);
+    for (int k = 0; k < nh; ++k) {
+      const uint32_t s = (hot[k] * best) >> (32 - kTabBits);
+      if (w[1 + s] == 0xFFFFFFFFu) {
+        w[1 + s] = hot[k];
+        idx[s] = (uint8_t)k;
+      }
+    }
+  }
+}
+
 void free_host_arrays(blco_tensor* t) {
   if (t->host_free) {
     if (t->h_keys) t->host_free(t->h_keys);

@@ -12,6 +12,12 @@ namespace blco {
 
 constexpr int kTile = 64;  // non-zeros per wave tile (one per lane of a wave64)
 constexpr int kHotMax = 256;  // frequent rows kept per mode
+// Table of a mode's frequent rows, as the window kernel's hot copies look them up: a
+// multiplier, kTabSlots rows (0xFFFFFFFF: empty; the row r is at slot
+// (r * multiplier) >> (32 - kTabBits)), and kTabSlots one-byte places in `hot`.
+constexpr int kTabBits = 9;
+constexpr int kTabSlots = 1 << kTabBits;
+constexpr int kTabWords = 1 + kTabSlots + kTabSlots / 4;
 constexpr int64_t kHotMinCount = 2048;  // default: a frequent row holds at least this many non-zeros
 
 // The bit map of a tensor (Sections 4.1-4.2).
@@ -81,6 +87,8 @@ struct blco_tensor {
   bool hot_forced = false;           // an explicit threshold: stash whatever fits
   double build_stage_ms[5] = {};     // blco_build_device stage times (blco_info_t)
   uint32_t* d_hot = nullptr;
+  std::vector<uint32_t> tab;         // N * kTabWords: row tables of the frequent rows
+  uint32_t* d_tab = nullptr;
 };
 
 namespace blco {
@@ -103,6 +111,9 @@ int host_build(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_t* co
 // reaches min_count (< 0: none).  Modes longer than 2^26 get none.
 void find_hot_rows(const uint32_t* const* coords, int64_t nnz, int64_t min_count, blco_tensor* t);
 
+// The row tables of the frequent rows (t->tab from t->hot and t->nhot).
+void make_row_tables(blco_tensor* t);
+
 void free_host_arrays(blco_tensor* t);
 
 // Bit map of a tensor (Sections 4.1-4.2); EUNSUPPORTED when the block key
@@ -113,6 +124,12 @@ int make_layout(int N, const uint64_t* dims, int key_bits, Layout* L);
 // block key (run_start without the final nnz; run_key their block keys).
 void finish_runs(const Layout& L, int64_t nnz, const std::vector<int64_t>& run_start,
                  const std::vector<uint64_t>& run_key, int64_t max_block_nnz, blco_tensor* t);
+
+// blco_mttkrp with a workspace of ws_bytes (256-byte aligned; may be empty), and the most of
+// it the call can use.  Defined in blco_device.hip.
+int mttkrp_with(blco_tensor* t, int mode, const void* const* factors, int factor_dtype, int rank,
+                float* out, void* ws, size_t ws_bytes, void* stream);
+size_t mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype);
 
 // Device sorting and compaction of the GPU builder (blco_sort.hip), ordered on
 // stream s (a hipStream_t, void* here so the host builder needs no HIP header).

@@ -1,5 +1,5 @@
-// Device kernels of the BLCO library (gfx950, wave64).  Included by
-// blco_device.hip only.
+// Launch parameters and kernel selection shared by the device translation units of the
+// BLCO library (gfx950, wave64).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -31,6 +31,10 @@ struct KParams {
   uint32_t mask[8];
   const uint32_t* hot;        // window kernel: frequent rows of the target mode
   int nhot;                   // window kernel: frequent rows held in the LDS stash
+  const uint32_t* tab;        // window kernel, hot copies: the target mode's row table
+  int64_t copy_off;           // ... bytes from out to the copies: copies x copy_stride floats per row
+  int copies;                 // ... copies of a row (a power of two)
+  int copy_stride;            // ... floats of one copy
   uint32_t short_rows;        // hierarchical kernel: target mode length
   int short_width;            // hierarchical kernel: ranks per slice
   uint32_t rowbytes;          // bytes of one factor row (R x element size)
@@ -38,5 +42,15 @@ struct KParams {
   float scale;                // host-side scale of every term
   const double* scale_dev;    // optional device-side scale (one double)
 };
+
+typedef void (*KernelFn)(KParams);
+
+// The window kernel for N modes, rank R: fp32 factors, bf16 factors, 64-bit gather
+// addresses (factor type fdt), and the fused CP-gradient walk.  stash: frequent rows in
+// LDS; wpt: window size (non-zeros per thread, or minus the threads per non-zero).
+KernelFn select_win_f32(int N, int R, bool stash, int wpt);
+KernelFn select_win_bf16(int N, int R, bool stash, int wpt);
+KernelFn select_win_big(int N, int R, int fdt, bool stash, int wpt);
+KernelFn select_res(int N, int R, int fdt, bool stash, int wpt);
 
 }  // namespace blco
