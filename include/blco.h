@@ -144,6 +144,24 @@ int blco_build_device(int nmodes, const uint64_t* dims, int64_t nnz,
                       const blco_build_opts* opts, void* stream, blco_tensor** out);
 
 /*
+ * blco_build_device in memory the caller provides (256-byte aligned device blocks; NULL and
+ * 0, or too small a block, for memory allocated by the call):
+ *   storage: holds the tensor's arrays (placement DEVICE) and must outlive the tensor and
+ *     the work queued on it; blco_free does not release it, and does not wait for work that
+ *     still reads it.  Parts that do not fit are allocated and released by the library.
+ *   workspace: used until the call returns.
+ * blco_build_device_sizes gives the bytes that hold everything but the run tables of a
+ * blocked tensor.  Result and errors as blco_build_device, EINVAL for a misaligned block.
+ */
+int blco_build_device_in(int nmodes, const uint64_t* dims, int64_t nnz,
+                         const uint32_t* const* coords, const float* values,
+                         const blco_build_opts* opts, void* storage, size_t storage_bytes,
+                         void* workspace, size_t workspace_bytes, void* stream, blco_tensor** out);
+int blco_build_device_sizes(int nmodes, const uint64_t* dims, int64_t nnz,
+                            const blco_build_opts* opts, size_t* storage_bytes,
+                            size_t* workspace_bytes);
+
+/*
  * Mode-`mode` MTTKRP (Eq. (1); Figure 3; Sections 5.1-5.2) of an in-memory
  * tensor (placement DEVICE):
  *   out[i, r] = sum over non-zeros k with i_mode = i of x_k * prod_{m != mode} A^(m)[i_m, r]

@@ -32,7 +32,7 @@ STATUS = {0: "OK", -1: "EINVAL", -2: "ENOMEM", -3: "EDEVICE", -4: "ERANGE", -5: 
 
 EXPORTED = ["blco_build", "blco_mttkrp", "blco_mttkrp_acc", "blco_mttkrp_v", "blco_mttkrp_stream",
             "blco_mttkrp_stream_all", "blco_mttkrp_ws", "blco_mttkrp_stream_all_ws",
-            "blco_cp_grad_ws", "blco_workspace",
+            "blco_cp_grad_ws", "blco_workspace", "blco_build_device_in", "blco_build_device_sizes",
             "blco_sampled_loss", "blco_cp_grad", "blco_cp_grad_noalloc", "blco_scale", "blco_cast_bf16", "blco_set_resolution", "blco_resolution",
             "blco_gram", "blco_cp_als", "blco_build_device",
             "blco_atomic_probe", "blco_gather_probe", "blco_frequent_rows", "blco_info", "blco_export", "blco_free",
@@ -108,6 +108,10 @@ def lib():
         L.blco_set_resolution.argtypes = [p, i32]
         L.blco_build_device.argtypes = [i32, p, i64, p, p, ctypes.POINTER(_Opts), p,
                                         ctypes.POINTER(p)]
+        L.blco_build_device_in.argtypes = [i32, p, i64, p, p, ctypes.POINTER(_Opts), p, sz, p, sz, p,
+                                           ctypes.POINTER(p)]
+        L.blco_build_device_sizes.argtypes = [i32, p, i64, ctypes.POINTER(_Opts),
+                                              ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.blco_gram.argtypes = [p, i32, i64, i32, p, p]
         L.blco_cp_als.argtypes = [p, p, i32, ctypes.POINTER(_CPALSOpts), p,
                                   ctypes.POINTER(_CPALSReport), p]
@@ -130,10 +134,26 @@ def _check(rc):
         raise BLCOError(rc, lib().blco_last_error().decode())
 
 
-def _stream(stream=None) -> int:
+def _stream(stream=None, t=None) -> int:
+    """The stream handle of a call.  A tensor whose arrays live in a torch allocation made on
+    another stream is recorded on this one, so that its memory is not reused before the
+    call's work has run."""
     if stream is None:
         stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream)
+    h = int(stream.cuda_stream)
+    if t is not None and t._storage is not None and h != t._storage_stream:
+        t._storage.record_stream(stream)
+    return h
+
+
+def _with_memory(call):
+    """call() again after torch has released its cached blocks, where device memory ran out
+    (the library's own allocations do not reach into torch's cache)."""
+    rc = call()
+    if rc == -2 and torch.cuda.is_available():
+        torch.cuda.empty_cache()
+        rc = call()
+    return rc
 
 
 RESOLUTIONS = {"auto": 0, "register": 1, "hierarchical": 2}
@@ -142,9 +162,11 @@ RESOLUTIONS = {"auto": 0, "register": 1, "hierarchical": 2}
 class BLCOTensor:
     """A BLCO tensor owned by the library (freed with the object)."""
 
-    def __init__(self, handle, dims):
+    def __init__(self, handle, dims, storage=None, storage_stream=0):
         self._h = ctypes.c_void_p(handle)
         self.dims = tuple(int(d) for d in dims)
+        self._storage = storage               # torch memory that holds the tensor's arrays
+        self._storage_stream = storage_stream
 
     @property
     def handle(self):
@@ -217,6 +239,7 @@ class BLCOTensor:
         if self._h is not None and self._h.value:
             lib().blco_free(self._h)
         self._h = None
+        self._storage = None
 
     def __del__(self):
         try:
@@ -276,9 +299,24 @@ def build_device(coords, values, dims, key_bits=64, max_block_nnz=1 << 27, place
     arr = (ctypes.c_void_p * N)(*[c.data_ptr() for c in keep])
     opts = _Opts(key_bits, max_block_nnz, PLACEMENTS[placement], int(hot_min_count))
     h = ctypes.c_void_p()
-    _check(lib().blco_build_device(N, d.ctypes.data, nnz, arr, v.data_ptr(), ctypes.byref(opts),
-                                   _stream(stream), ctypes.byref(h)))
-    return BLCOTensor(h.value, dims)
+    need_s, need_w = ctypes.c_size_t(), ctypes.c_size_t()
+    _check(lib().blco_build_device_sizes(N, d.ctypes.data, nnz, ctypes.byref(opts),
+                                         ctypes.byref(need_s), ctypes.byref(need_w)))
+    # the arrays and the workspace from the pool of the stream the build runs on
+    sh = _stream(stream)
+    storage = ws = None
+    with torch.cuda.stream(stream):
+        try:
+            if need_s.value:
+                storage = torch.empty(need_s.value, dtype=torch.uint8, device=dev)
+            ws = torch.empty(need_w.value, dtype=torch.uint8, device=dev)
+        except torch.cuda.OutOfMemoryError:
+            pass   # the library allocates what it was not given, or says what it could not
+    blk = lambda x: (None, 0) if x is None else (x.data_ptr(), x.numel())
+    _check(_with_memory(lambda: lib().blco_build_device_in(
+        N, d.ctypes.data, nnz, arr, v.data_ptr(), ctypes.byref(opts), *blk(storage), *blk(ws), sh,
+        ctypes.byref(h))))
+    return BLCOTensor(h.value, dims, storage, sh)
 
 
 def _factor_args(t, factors, mode_skip):
@@ -346,7 +384,7 @@ def mttkrp(t, mode, factors, out=None, stream=None):
     out = _out(t, mode, R, out, _device_of(factors))
     ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
     _check(lib().blco_mttkrp_ws(t.handle, mode, None, arr, dt, R, None, 1.0, 0, out.data_ptr(), wp,
-                                wb, _stream(stream)))
+                                wb, _stream(stream, t)))
     return out
 
 
@@ -356,7 +394,7 @@ def mttkrp_acc(t, mode, factors, out, stream=None):
     out = _out(t, mode, R, out, _device_of(factors))
     ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
     _check(lib().blco_mttkrp_ws(t.handle, mode, None, arr, dt, R, None, 1.0, 1, out.data_ptr(), wp,
-                                wb, _stream(stream)))
+                                wb, _stream(stream, t)))
     return out
 
 
@@ -373,7 +411,7 @@ def mttkrp_v(t, mode, values, factors, out=None, scale=None, alpha=1.0, stream=N
         sp = scale.data_ptr()
     ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
     _check(lib().blco_mttkrp_ws(t.handle, mode, values.data_ptr(), arr, dt, R, sp, float(alpha), 0,
-                                out.data_ptr(), wp, wb, _stream(stream)))
+                                out.data_ptr(), wp, wb, _stream(stream, t)))
     return out
 
 
@@ -384,12 +422,12 @@ def mttkrp_stream(t, mode, factors, out=None, device_budget=8_000_000_000, strea
     ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
     if wb == 0 or mode < 0:
         _check(lib().blco_mttkrp_stream(t.handle, mode, arr, dt, R, out.data_ptr(),
-                                        int(device_budget), _stream(stream)))
+                                        int(device_budget), _stream(stream, t)))
         return out
     outs = (ctypes.c_void_p * len(t.dims))()
     outs[mode] = out.data_ptr()
     _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, outs, int(device_budget), wp, wb,
-                                           _stream(stream)))
+                                           _stream(stream, t)))
     return out
 
 
@@ -408,7 +446,7 @@ def mttkrp_stream_all(t, factors, outs=None, device_budget=8_000_000_000, modes=
                                                for m in range(len(t.dims))])
     ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
     _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, ptrs, int(device_budget), wp, wb,
-                                           _stream(stream)))
+                                           _stream(stream, t)))
     return [outs[m] if m in modes else None for m in range(len(t.dims))]
 
 
@@ -422,7 +460,7 @@ def sampled_loss(t, factors, residual=None, loss=None, stream=None):
     if loss is None:
         loss = torch.empty((), dtype=torch.float64, device=dev)
     _check(lib().blco_sampled_loss(t.handle, arr, dt, R, residual.data_ptr(), loss.data_ptr(),
-                                   _stream(stream)))
+                                   _stream(stream, t)))
     return loss, residual
 
 
@@ -453,7 +491,7 @@ def cp_grad(t, factors, grads=None, residual=None, loss=None, scale=None, alpha=
     ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
     _check(lib().blco_cp_grad_ws(t.handle, arr, dt, R, sp, float(alpha),
                                  None if pinned else residual.data_ptr(), loss.data_ptr(), ptrs,
-                                 int(device_budget), wp, wb, _stream(stream)))
+                                 int(device_budget), wp, wb, _stream(stream, t)))
     return loss, grads, (None if pinned else residual)
 
 
@@ -471,7 +509,7 @@ def cp_grad_noalloc(t, factors, grads, residual, loss, scale=None, alpha=1.0, st
         sp = scale.data_ptr()
     ptrs = (ctypes.c_void_p * N)(*[g.data_ptr() for g in grads])
     _check(lib().blco_cp_grad_noalloc(t.handle, arr, dt, R, sp, float(alpha), residual.data_ptr(),
-                                      loss.data_ptr(), ptrs, _stream(stream)))
+                                      loss.data_ptr(), ptrs, _stream(stream, t)))
     return loss, grads, residual
 
 
@@ -552,8 +590,9 @@ def cp_als(t, factors, max_iters=25, tol=1e-5, storage="fp32", stream=None):
     opts = _CPALSOpts(int(max_iters), float(tol), BF16 if storage == "bf16" else F32)
     fits = np.zeros(int(max_iters), dtype=np.float64)
     rep = _CPALSReport()
-    _check(lib().blco_cp_als(t.handle, arr, R, ctypes.byref(opts), fits.ctypes.data,
-                             ctypes.byref(rep), _stream(stream)))
+    sh = _stream(stream, t)
+    _check(_with_memory(lambda: lib().blco_cp_als(t.handle, arr, R, ctypes.byref(opts),
+                                                  fits.ctypes.data, ctypes.byref(rep), sh)))
     return fits[:rep.iters].tolist(), {"iters": rep.iters, "pinv_fallbacks": rep.pinv_fallbacks}
 
 

@@ -51,52 +51,141 @@ struct LinParams {
   int T;
 };
 
+// First bad non-zero, and the AND and OR of the low and high index words: what the host
+// reads once the non-zeros are linearized.
+struct LinResult {
+  unsigned long long bad, lo_and, lo_or, hi_and, hi_or;
+};
+
+constexpr int kEncBytes = 8;   // K <= 64
+
+// Byte tables of the bit map, and the cleared LinResult.  dep[((m * 4 + k) * 256 + v) * 2 +
+// {0, 1}]: the (lo, hi) index bits of byte k of a mode-m coordinate holding v;
+// enc[k * 256 + v]: key bits of byte k of an index holding v.
+__global__ __launch_bounds__(256) void k_tables(LinParams p, uint64_t* __restrict__ dep,
+                                                uint64_t* __restrict__ enc,
+                                                LinResult* __restrict__ res) {
+  const int v = threadIdx.x;
+  if (blockIdx.x == 0 && v == 0) *res = LinResult{~0ull, ~0ull, 0ull, ~0ull, 0ull};
+  const int nd = p.N * 4;
+  if ((int)blockIdx.x < nd) {
+    const int m = blockIdx.x / 4, k = blockIdx.x % 4;
+    uint64_t xl = 0, xh = 0;
+    for (int j = 0; j < 8; ++j) {
+      const int bj = 8 * k + j;
+      if (!((v >> j) & 1) || bj >= p.b[m]) continue;
+      const int q = p.pos[m][bj];
+      if (q < 64)
+        xl |= 1ull << q;
+      else
+        xh |= 1ull << (q - 64);
+    }
+    dep[((size_t)blockIdx.x * 256 + v) * 2] = xl;
+    dep[((size_t)blockIdx.x * 256 + v) * 2 + 1] = xh;
+    return;
+  }
+  const int k = blockIdx.x - nd;
+  uint64_t x = 0;
+  for (int m = 0; m < p.N; ++m)
+    for (int j = 0; j < p.b[m]; ++j) {
+      const int q = (int)p.pos[m][j] - 8 * k;   // bit j of mode m is bit q of this byte
+      if (q >= 0 && q < 8 && 8 * k + q < p.K && ((v >> q) & 1)) x |= 1ull << (p.s[m] + j);
+    }
+  enc[(size_t)k * 256 + v] = x;
+}
+
 // ALTO index of every non-zero (lo: bits 0..63; hi: bits 64..127, or hi32: bits
-// 64..95 of an index of at most 96 bits; or neither); *bad = smallest non-zero
-// number with a coordinate out of range.
-// dep[((m * 4 + k) * 256 + v) * 2 + {0, 1}]: the (lo, hi) index bits of byte k of a
-// mode-m coordinate holding v.  Without a high part the lo halves of the table are
-// staged in LDS (N * 8 KiB of dynamic LDS), once per workgroup of a grid that
+// 64..95 of an index of at most 96 bits; or neither); res: the smallest non-zero number
+// with a coordinate out of range, and the AND and OR of the index words (the sorts skip
+// digits they show to be constant).  Without a high part the lo halves of the deposit table
+// are staged in LDS (N * 8 KiB of dynamic LDS), once per workgroup of a grid that
 // strides over the non-zeros.
 __global__ __launch_bounds__(256) void k_linearize(LinParams p, int64_t n,
                                                    const uint64_t* __restrict__ dep,
                                                    uint64_t* __restrict__ lo,
                                                    uint64_t* __restrict__ hi,
                                                    uint32_t* __restrict__ hi32,
-                                                   unsigned long long* __restrict__ bad) {
+                                                   LinResult* __restrict__ res) {
   extern __shared__ uint64_t s_dep[];   // [(m * 4 + k) * 256 + v], lo halves (no high part)
+  __shared__ unsigned long long s_red[4][4];
   const bool wide = hi || hi32;
   if (!wide) {
     for (int j = threadIdx.x; j < p.N * 4 * 256; j += 256) s_dep[j] = dep[2 * j];
     __syncthreads();
   }
+  unsigned long long red[4] = {~0ull, 0ull, ~0ull, 0ull};
   const int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
-  uint64_t l = 0, h = 0;
-  for (int m = 0; m < p.N; ++m) {
-    uint32_t c = p.coords[m][i];
-    if ((uint64_t)c >= p.dims[m]) {
-      atomicMin(bad, (unsigned long long)i);
-      c = 0;
-    }
-    if (!wide) {
-      const uint64_t* d = s_dep + (size_t)m * 4 * 256;
+    uint64_t l = 0, h = 0;
+    for (int m = 0; m < p.N; ++m) {
+      uint32_t c = p.coords[m][i];
+      if ((uint64_t)c >= p.dims[m]) {
+        atomicMin(&res->bad, (unsigned long long)i);
+        c = 0;
+      }
+      if (!wide) {
+        const uint64_t* d = s_dep + (size_t)m * 4 * 256;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) l |= d[k * 256 + ((c >> (8 * k)) & 255u)];
-    } else {
-      const uint64_t* d = dep + (size_t)m * 4 * 256 * 2;
+        for (int k = 0; k < 4; ++k) l |= d[k * 256 + ((c >> (8 * k)) & 255u)];
+      } else {
+        const uint64_t* d = dep + (size_t)m * 4 * 256 * 2;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t v = (c >> (8 * k)) & 255u;
-        l |= d[(k * 256 + v) * 2];
-        h |= d[(k * 256 + v) * 2 + 1];
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t v = (c >> (8 * k)) & 255u;
+          l |= d[(k * 256 + v) * 2];
+          h |= d[(k * 256 + v) * 2 + 1];
+        }
       }
     }
+    lo[i] = l;
+    if (hi) hi[i] = h;
+    if (hi32) hi32[i] = (uint32_t)h;
+    red[0] &= l;
+    red[1] |= l;
+    red[2] &= h;
+    red[3] |= h;
   }
-  lo[i] = l;
-  if (hi) hi[i] = h;
-  if (hi32) hi32[i] = (uint32_t)h;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const unsigned long long o = __shfl_xor(red[q], off, 64);
+      red[q] = q & 1 ? (red[q] | o) : (red[q] & o);
+    }
   }
+  if ((threadIdx.x & 63) == 0)
+    for (int q = 0; q < 4; ++q) s_red[threadIdx.x >> 6][q] = red[q];
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const int q = threadIdx.x;
+    unsigned long long x = s_red[0][q];
+    for (int w = 1; w < 4; ++w) x = q & 1 ? (x | s_red[w][q]) : (x & s_red[w][q]);
+    unsigned long long* dst = q == 0 ? &res->lo_and : q == 1 ? &res->lo_or
+                                                  : q == 2 ? &res->hi_and : &res->hi_or;
+    if (q & 1)
+      atomicOr(dst, x);
+    else
+      atomicAnd(dst, x);
+  }
+}
+
+// Run that holds the first non-zero of each 64-non-zero tile: the last run starting at or
+// before it.
+__global__ __launch_bounds__(256) void k_tile_run(const int64_t* __restrict__ run_start,
+                                                  int64_t nruns, int64_t ntiles,
+                                                  int32_t* __restrict__ tile_run) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= ntiles) return;
+  const int64_t e = i * kTile;
+  int64_t a = 0, b = nruns;   // run_start[a] <= e < run_start[b]
+  while (b - a > 1) {
+    const int64_t m = (a + b) / 2;
+    if (run_start[m] <= e)
+      a = m;
+    else
+      b = m;
+  }
+  tile_run[i] = (int32_t)a;
 }
 
 // Keys and block keys in sorted order, from the sorted index (slo: bits 0..63;
@@ -104,7 +193,6 @@ __global__ __launch_bounds__(256) void k_linearize(LinParams p, int64_t n,
 // bit below K into its mode's field through a byte table (enc[k][v]: key bits of
 // byte k holding v); the block key is the index above bit K.  The values are
 // already in place: the sorts moved them.
-constexpr int kEncBytes = 8;   // K <= 64
 __global__ __launch_bounds__(256) void k_encode(int64_t n, int K, const uint64_t* __restrict__ enc,
                                                 const uint64_t* __restrict__ slo,
                                                 const uint64_t* __restrict__ shi,
@@ -171,8 +259,6 @@ __global__ __launch_bounds__(256) void k_runs(const uint32_t* __restrict__ sorte
   cnt[r] = (uint32_t)(e - a);
 }
 
-__global__ void k_fill_u64(unsigned long long* p, unsigned long long v) { *p = v; }
-
 unsigned grid_of(int64_t n) { return (unsigned)std::max<int64_t>((n + 255) / 256, 1); }
 
 constexpr unsigned kStrideGrid = 2048;   // workgroups of grid-stride kernels (8 per CU)
@@ -203,37 +289,64 @@ struct StageEvents {
   }
 };
 
-// device allocations released on every return path
+// Device memory of one build: taken in turn from the block the caller lends, and
+// allocated where that has no room (released on every return path).  reuse() starts over
+// in the block: what was taken before is dead for work queued from then on.
 struct Pool {
   std::vector<void*> ptrs;
+  char* block = nullptr;
+  size_t bytes = 0, at = 0;
   ~Pool() {
     for (void* p : ptrs) (void)hipFree(p);
   }
+  void reuse() { at = 0; }
   template <typename T>
   int get(T** out, size_t count) {
+    const size_t need = std::max<size_t>(count, 1) * sizeof(T);
+    if (at <= bytes && need <= bytes - at) {
+      *out = reinterpret_cast<T*>(block + at);
+      at += (need + 255) / 256 * 256;
+      return BLCO_OK;
+    }
     void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T)) != hipSuccess)
-      return set_error(BLCO_ENOMEM, "device allocation of %zu bytes failed",
-                       std::max<size_t>(count, 1) * sizeof(T));
+    if (hipMalloc(&p, need) != hipSuccess)
+      return set_error(BLCO_ENOMEM, "device allocation of %zu bytes failed", need);
     ptrs.push_back(p);
     *out = static_cast<T*>(p);
     return BLCO_OK;
   }
 };
 
+// The tensor's own arrays: from the caller's storage while it has room, else allocated.
+struct Home {
+  blco_tensor* t;
+  size_t at = 0;
+  template <typename T>
+  int get(T** dst, size_t count, size_t* acc) {
+    const size_t need = sizeof(T) * std::max<size_t>(count, 1);
+    if (t->storage && at <= t->storage_bytes && need <= t->storage_bytes - at) {
+      *dst = reinterpret_cast<T*>(t->storage + at);
+      at += (need + 255) / 256 * 256;
+    } else {
+      HIPCHK(hipMalloc((void**)dst, need));
+    }
+    *acc += need;
+    return BLCO_OK;
+  }
+};
+
 template <typename T>
-int upload_to(T** dst, const T* src, size_t count, hipStream_t s, size_t* acc) {
-  const size_t bytes = sizeof(T) * std::max<size_t>(count, 1);
-  HIPCHK(hipMalloc((void**)dst, bytes));
+int upload_to(Home& home, T** dst, const T* src, size_t count, hipStream_t s, size_t* acc) {
+  int rc = home.get(dst, count, acc);
+  if (rc) return rc;
   if (count) HIPCHK(hipMemcpyAsync(*dst, src, sizeof(T) * count, hipMemcpyHostToDevice, s));
-  *acc += bytes;
   return BLCO_OK;
 }
 
 void release_tensor_arrays(blco_tensor* t) {
   for (void* p : {(void*)t->d_keys, (void*)t->d_vals, (void*)t->d_run_start,
                   (void*)t->d_run_base, (void*)t->d_tile_run, (void*)t->d_hot, (void*)t->d_tab})
-    if (p) (void)hipFree(p);
+    if (t->owned(p)) (void)hipFree(p);
   t->d_keys = nullptr;
   t->d_vals = nullptr;
   t->d_run_start = nullptr;
@@ -312,9 +425,8 @@ int gpu_hot_rows(const LinParams& lp, int64_t nnz, int64_t min_count, Pool& pool
 
 int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_t* const* coords,
                     const float* values, int key_bits, int64_t cap, int64_t hot_min,
-                    hipStream_t s, blco_tensor* t) {
-  int rc = make_layout(nmodes, dims, key_bits, &t->lay);
-  if (rc) return rc;
+                    hipStream_t s, void* ws_block, size_t ws_bytes, blco_tensor* t) {
+  int rc;
   const Layout& L = t->lay;
   t->nnz = nnz;
   t->max_block_nnz = cap;
@@ -332,6 +444,9 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
     for (int j = 0; j < L.b[m]; ++j) lp.pos[m][j] = (uint8_t)L.pos[m][j];
   }
   Pool pool;
+  pool.block = static_cast<char*>(ws_block);
+  pool.bytes = ws_bytes;
+  Home home{t};
   StageEvents stage;
   stage.mark(0, s);
   const bool wide = L.T > 64;
@@ -340,11 +455,14 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
   // over the high bits moves the values and the low bits; one of at most 64 bits
   // carries the values through its one sort
   const bool mid = wide && L.T <= 96;
-  uint64_t *lo, *lo2, *hi = nullptr, *his = nullptr, *hif = nullptr, *bkey;
+  const bool blocked = L.S > 0;   // without block bits every block key is 0: none are written
+  uint64_t *lo, *lo2, *hi = nullptr, *his = nullptr, *hif = nullptr, *bkey = nullptr;
   uint32_t *h32 = nullptr, *h32s = nullptr, *h32f = nullptr, *vs = nullptr, *tv2 = nullptr;
-  unsigned long long* bad;
-  if ((rc = pool.get(&lo, nnz)) || (rc = pool.get(&lo2, nnz)) || (rc = pool.get(&bkey, nnz)) ||
-      (rc = pool.get(&bad, 1)))
+  LinResult* res;
+  uint64_t *d_dep, *d_enc;
+  if ((rc = pool.get(&res, 1)) || (rc = pool.get(&d_dep, (size_t)L.N * 4 * 256 * 2)) ||
+      (rc = pool.get(&d_enc, (size_t)kEncBytes * 256)) || (rc = pool.get(&lo, nnz)) ||
+      (rc = pool.get(&lo2, nnz)) || (blocked && (rc = pool.get(&bkey, nnz))))
     return rc;
   if (wide && ((rc = pool.get(&vs, nnz)) || (rc = pool.get(&tv2, nnz))))
     return rc;
@@ -355,35 +473,18 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
                        (rc = pool.get(&hif, nnz))))
     return rc;
   // 1. linearize, through per-byte deposit tables
-  std::vector<uint64_t> dep((size_t)L.N * 4 * 256 * 2, 0);
-  for (int m = 0; m < L.N; ++m)
-    for (int k = 0; k < 4; ++k)
-      for (int v = 0; v < 256; ++v) {
-        uint64_t xl = 0, xh = 0;
-        for (int j = 0; j < 8; ++j) {
-          const int bj = 8 * k + j;
-          if (!((v >> j) & 1) || bj >= L.b[m]) continue;
-          const int q = L.pos[m][bj];
-          if (q < 64)
-            xl |= 1ULL << q;
-          else
-            xh |= 1ULL << (q - 64);
-        }
-        dep[(((size_t)m * 4 + k) * 256 + v) * 2] = xl;
-        dep[(((size_t)m * 4 + k) * 256 + v) * 2 + 1] = xh;
-      }
-  uint64_t* d_dep;
-  if ((rc = pool.get(&d_dep, dep.size()))) return rc;
-  HIPCHK(hipMemcpyAsync(d_dep, dep.data(), dep.size() * 8, hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(1), 0, s, bad, ~0ULL);
+  hipLaunchKernelGGL(k_tables, dim3(L.N * 4 + kEncBytes), dim3(256), 0, s, lp, d_dep, d_enc, res);
+  HIPCHK(hipGetLastError());
   if (nnz > 0)
     hipLaunchKernelGGL(k_linearize, dim3(std::min<unsigned>(grid_of(nnz), kStrideGrid)), dim3(256),
                        wide ? 0 : (size_t)L.N * 4 * 256 * sizeof(uint64_t), s, lp, nnz, d_dep, lo,
-                       mid ? nullptr : hi, h32, bad);
+                       mid ? nullptr : hi, h32, res);
   HIPCHK(hipGetLastError());
-  unsigned long long first_bad = ~0ULL;
-  HIPCHK(hipMemcpyAsync(&first_bad, bad, 8, hipMemcpyDeviceToHost, s));
+  LinResult lin;
+  HIPCHK(hipMemcpyAsync(&lin, res, sizeof(lin), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  const unsigned long long first_bad = lin.bad;
+  const uint64_t lo_bits[2] = {lin.lo_and, lin.lo_or}, hi_bits[2] = {lin.hi_and, lin.hi_or};
   if (first_bad != ~0ULL) {
     const int64_t i = (int64_t)first_bad;
     for (int m = 0; m < L.N; ++m) {
@@ -398,9 +499,9 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
   // 2. stable sort along the encoding line
   stage.mark(1, s);
   size_t acc = 0;
-  HIPCHK(hipMalloc((void**)&t->d_keys, sizeof(uint64_t) * std::max<int64_t>(nnz, 1)));
-  HIPCHK(hipMalloc((void**)&t->d_vals, sizeof(float) * std::max<int64_t>(nnz, 1)));
-  acc += (sizeof(uint64_t) + sizeof(float)) * (size_t)std::max<int64_t>(nnz, 1);
+  if ((rc = home.get(&t->d_keys, (size_t)nnz, &acc)) ||
+      (rc = home.get(&t->d_vals, (size_t)nnz, &acc)))
+    return rc;
   if (nnz > 0) {
     const int nb0 = std::max(1, std::min(L.T, 64));
     uint64_t* tk;
@@ -413,7 +514,7 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
     uint32_t* v_out = reinterpret_cast<uint32_t*>(t->d_vals);
     if (!wide) {
       // at most 64 index bits: the values travel with the keys into the tensor
-      if ((rc = radix_sort_u64(lo, v_in, lo2, v_out, tk, tv, nnz, nb0, ws, s))) return rc;
+      if ((rc = radix_sort_u64(lo, v_in, lo2, v_out, tk, tv, nnz, nb0, ws, s, lo_bits))) return rc;
     } else {
       // the low 64 bits, moving the values and the high bits; then the high bits,
       // moving the values (into the tensor) and the low bits
@@ -432,7 +533,7 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
         v1.out64 = his;
         v1.tmp64 = tk2;
       }
-      if ((rc = radix_sort_u64_vals(lo, lo2, tk, v1, nnz, nb0, ws, s))) return rc;
+      if ((rc = radix_sort_u64_vals(lo, lo2, tk, v1, nnz, nb0, ws, s, lo_bits))) return rc;
       SortVals v2 = {};
       v2.in32[0] = vs;
       v2.out32[0] = v_out;
@@ -441,39 +542,17 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
       v2.out64 = lo;   // the unsorted low bits are no longer needed
       v2.tmp64 = tk;
       if (mid) {
-        if ((rc = radix_sort_u32_vals(h32s, h32f, tv, v2, nnz, L.T - 64, ws, s))) return rc;
+        if ((rc = radix_sort_u32_vals(h32s, h32f, tv, v2, nnz, L.T - 64, ws, s, hi_bits)))
+          return rc;
       } else {
-        if ((rc = radix_sort_u64_vals(his, hif, tk2, v2, nnz, L.T - 64, ws, s))) return rc;
+        if ((rc = radix_sort_u64_vals(his, hif, tk2, v2, nnz, L.T - 64, ws, s, hi_bits)))
+          return rc;
       }
       std::swap(lo, lo2);   // lo2: the low bits in the final order
     }
   }
   // 3. re-encode in sorted order; keys and values go straight into the tensor
   stage.mark(2, s);
-  std::vector<uint64_t> enc((size_t)kEncBytes * 256, 0);
-  {
-    int owner_mode[128], owner_bit[128];
-    for (int m = 0; m < L.N; ++m)
-      for (int j = 0; j < L.b[m]; ++j) {
-        owner_mode[L.pos[m][j]] = m;
-        owner_bit[L.pos[m][j]] = j;
-      }
-    for (int k = 0; k < kEncBytes; ++k)
-      for (int v = 0; v < 256; ++v) {
-        uint64_t x = 0;
-        for (int j = 0; j < 8; ++j) {
-          const int q = 8 * k + j;
-          if (!((v >> j) & 1) || q >= L.K) continue;
-          x |= 1ULL << (L.s[owner_mode[q]] + owner_bit[q]);
-        }
-        enc[(size_t)k * 256 + v] = x;
-      }
-  }
-  uint64_t* d_enc;
-  if ((rc = pool.get(&d_enc, enc.size()))) return rc;
-  HIPCHK(hipMemcpyAsync(d_enc, enc.data(), enc.size() * 8, hipMemcpyHostToDevice, s));
-  // without block bits every block key is 0: no block keys to write or scan
-  const bool blocked = L.S > 0;
   if (nnz > 0) {
     hipLaunchKernelGGL(k_encode, dim3(grid_of(nnz)), dim3(256), 0, s, nnz, L.K, d_enc, lo2,
                        wide && !mid ? hif : nullptr, mid ? h32f : nullptr, t->d_keys,
@@ -508,30 +587,69 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
     HIPCHK(hipMemcpyAsync(run_key.data(), keys_at, 8 * nruns, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
   }
-  finish_runs(L, nnz, run_start, run_key, cap, t);
+  finish_runs(L, nnz, run_start, run_key, cap, t, false);
   // 5. frequent rows
   stage.mark(4, s);
+  pool.reuse();
   if ((rc = gpu_hot_rows(lp, nnz, hot_min, pool, s, t))) return rc;
   make_row_tables(t);
   stage.mark(5, s);
-  if ((rc = upload_to(&t->d_run_start, t->run_start.data(), t->run_start.size(), s, &acc)) ||
-      (rc = upload_to(&t->d_run_base, t->run_base.data(), t->run_base.size(), s, &acc)) ||
-      (rc = upload_to(&t->d_tile_run, t->tile_run.data(), t->tile_run.size(), s, &acc)) ||
-      (rc = upload_to(&t->d_hot, t->hot.data(), t->hot.size(), s, &acc)) ||
-      (rc = upload_to(&t->d_tab, t->tab.data(), t->tab.size(), s, &acc)))
+  if ((rc = upload_to(home, &t->d_hot, t->hot.data(), t->hot.size(), s, &acc)) ||
+      (rc = upload_to(home, &t->d_tab, t->tab.data(), t->tab.size(), s, &acc)) ||
+      (rc = upload_to(home, &t->d_run_start, t->run_start.data(), t->run_start.size(), s, &acc)) ||
+      (rc = upload_to(home, &t->d_run_base, t->run_base.data(), t->run_base.size(), s, &acc)))
     return rc;
+  if (blocked && nnz > 0) {
+    const int64_t ntiles = (nnz + kTile - 1) / kTile;
+    if ((rc = home.get(&t->d_tile_run, (size_t)ntiles, &acc))) return rc;
+    hipLaunchKernelGGL(k_tile_run, dim3(grid_of(ntiles)), dim3(256), 0, s,
+                       (const int64_t*)t->d_run_start, (int64_t)t->run_start.size() - 1, ntiles,
+                       t->d_tile_run);
+    HIPCHK(hipGetLastError());
+  }
   HIPCHK(hipStreamSynchronize(s));
   stage.read(t->build_stage_ms);
   t->device_bytes = acc;
   return BLCO_OK;
 }
 
+size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Workspace of a build: the larger of what linearizing, sorting and run detection hold
+// together and what the frequent-row counts hold.
+size_t build_workspace(const Layout& L, int64_t nnz) {
+  const size_t n = (size_t)std::max<int64_t>(nnz, 1);
+  const bool wide = L.T > 64, mid = wide && L.T <= 96;
+  size_t a = 1024 + up256((size_t)L.N * 4 * 256 * 16) + up256((size_t)kEncBytes * 256 * 8);
+  a += 2 * up256(8 * n);                                     // lo, lo2
+  a += up256(8 * n) + up256(4 * n) + up256(4 * sort_workspace_words(nnz));   // spares
+  if (wide) a += 2 * up256(4 * n);
+  if (mid) a += 3 * up256(4 * n);
+  if (wide && !mid) a += 4 * up256(8 * n);
+  if (L.S > 0)   // block keys, flags, run starts
+    a += 2 * up256(8 * n) + up256(n) + up256(4 * select_workspace_words(nnz)) + (1 << 20);
+  const size_t smp = std::min<size_t>(n, (size_t)2 << 22);
+  const size_t b = 8 * up256(4 * smp) + up256(smp) + up256(8 * smp) +
+                   up256(4 * std::max(sort_workspace_words((int64_t)smp),
+                                      select_workspace_words((int64_t)smp)));
+  return std::max(a, b);
+}
+
+// Storage of a tensor's arrays (the run tables of a blocked tensor, whose size the data
+// decide, are allocated apart where they do not fit the slack).
+size_t build_storage(const Layout& L, int64_t nnz) {
+  const size_t n = (size_t)std::max<int64_t>(nnz, 1);
+  return up256(8 * n) + up256(4 * n) + up256((n + kTile - 1) / kTile * 4) +
+         up256((size_t)L.N * kHotMax * 4) + up256((size_t)L.N * kTabWords * 4) + 4096;
+}
+
 }  // namespace
 
-extern "C" int blco_build_device(int nmodes, const uint64_t* dims, int64_t nnz,
-                                 const uint32_t* const* coords, const float* values,
-                                 const blco_build_opts* opts, void* stream, blco_tensor** out) {
-  clear_error();
+static int build_device_impl(int nmodes, const uint64_t* dims, int64_t nnz,
+                             const uint32_t* const* coords, const float* values,
+                             const blco_build_opts* opts, void* storage, size_t storage_bytes,
+                             void* workspace, size_t workspace_bytes, void* stream,
+                             blco_tensor** out) {
   if (!out) return set_error(BLCO_EINVAL, "out is NULL");
   *out = nullptr;
   if (nmodes < 1 || nmodes > BLCO_MAX_MODES)
@@ -570,7 +688,14 @@ extern "C" int blco_build_device(int nmodes, const uint64_t* dims, int64_t nnz,
     delete t;
     return set_error(BLCO_EDEVICE, "hipGetDevice failed");
   }
-  int rc = build_on_device(nmodes, dims, nnz, coords, values, key_bits, cap, hot_min, s, t);
+  int rc = make_layout(nmodes, dims, key_bits, &t->lay);
+  if (rc == BLCO_OK && storage && placement == BLCO_PLACE_DEVICE) {
+    t->storage = static_cast<char*>(storage);
+    t->storage_bytes = storage_bytes;
+  }
+  if (rc == BLCO_OK)
+    rc = build_on_device(nmodes, dims, nnz, coords, values, key_bits, cap, hot_min, s, workspace,
+                         workspace_bytes, t);
   if (rc == BLCO_OK && placement == BLCO_PLACE_PINNED) {
     // the non-zeros move to pinned host memory for streaming
     const size_t n1 = (size_t)std::max<int64_t>(nnz, 1);
@@ -597,5 +722,53 @@ extern "C" int blco_build_device(int nmodes, const uint64_t* dims, int64_t nnz,
     return rc;
   }
   *out = t;
+  return BLCO_OK;
+}
+
+extern "C" int blco_build_device(int nmodes, const uint64_t* dims, int64_t nnz,
+                                 const uint32_t* const* coords, const float* values,
+                                 const blco_build_opts* opts, void* stream, blco_tensor** out) {
+  clear_error();
+  return build_device_impl(nmodes, dims, nnz, coords, values, opts, nullptr, 0, nullptr, 0, stream,
+                           out);
+}
+
+extern "C" int blco_build_device_in(int nmodes, const uint64_t* dims, int64_t nnz,
+                                    const uint32_t* const* coords, const float* values,
+                                    const blco_build_opts* opts, void* storage,
+                                    size_t storage_bytes, void* workspace, size_t workspace_bytes,
+                                    void* stream, blco_tensor** out) {
+  clear_error();
+  if ((!storage && storage_bytes) || (!workspace && workspace_bytes))
+    return set_error(BLCO_EINVAL, "storage or workspace is NULL");
+  if ((reinterpret_cast<uintptr_t>(storage) | reinterpret_cast<uintptr_t>(workspace)) & 255)
+    return set_error(BLCO_EINVAL, "storage and workspace must be 256-byte aligned");
+  return build_device_impl(nmodes, dims, nnz, coords, values, opts, storage, storage_bytes,
+                           workspace, workspace_bytes, stream, out);
+}
+
+extern "C" int blco_build_device_sizes(int nmodes, const uint64_t* dims, int64_t nnz,
+                                       const blco_build_opts* opts, size_t* storage_bytes,
+                                       size_t* workspace_bytes) {
+  clear_error();
+  if (!storage_bytes || !workspace_bytes) return set_error(BLCO_EINVAL, "a size is NULL");
+  if (nmodes < 1 || nmodes > BLCO_MAX_MODES)
+    return set_error(BLCO_EUNSUPPORTED, "nmodes %d outside 1..%d", nmodes, BLCO_MAX_MODES);
+  if (!dims) return set_error(BLCO_EINVAL, "dims is NULL");
+  if (nnz < 0) return set_error(BLCO_EINVAL, "nnz %lld < 0", (long long)nnz);
+  if (nnz >= ((int64_t)1 << 31) - 1)
+    return set_error(BLCO_EUNSUPPORTED, "the GPU builder takes fewer than 2^31 - 1 non-zeros");
+  for (int n = 0; n < nmodes; ++n) {
+    if (dims[n] < 1) return set_error(BLCO_EINVAL, "dims[%d] = 0", n);
+    if (dims[n] > (1ULL << 32))
+      return set_error(BLCO_EUNSUPPORTED, "dims[%d] = %llu > 2^32", n, (unsigned long long)dims[n]);
+  }
+  const int key_bits = opts ? opts->key_bits : 64;
+  if (key_bits < 1 || key_bits > 64) return set_error(BLCO_EINVAL, "key_bits %d outside 1..64", key_bits);
+  Layout L;
+  int rc = make_layout(nmodes, dims, key_bits, &L);
+  if (rc) return rc;
+  *storage_bytes = opts && opts->placement != BLCO_PLACE_DEVICE ? 0 : build_storage(L, nnz);
+  *workspace_bytes = build_workspace(L, nnz);
   return BLCO_OK;
 }

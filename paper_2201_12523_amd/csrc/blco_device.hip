@@ -1056,14 +1056,9 @@ static void release_device(blco_tensor* t) {
   }
   if (st.copy_stream) (void)hipStreamDestroy((hipStream_t)st.copy_stream);
   st = StreamState();
-  if (t->d_keys) (void)hipFree(t->d_keys);
-  if (t->d_vals) (void)hipFree(t->d_vals);
-  if (t->d_run_start) (void)hipFree(t->d_run_start);
-  if (t->d_run_base) (void)hipFree(t->d_run_base);
-  if (t->d_tile_run) (void)hipFree(t->d_tile_run);
-  if (t->d_partials) (void)hipFree(t->d_partials);
-  if (t->d_hot) (void)hipFree(t->d_hot);
-  if (t->d_tab) (void)hipFree(t->d_tab);
+  for (void* q : {(void*)t->d_keys, (void*)t->d_vals, (void*)t->d_run_start, (void*)t->d_run_base,
+                  (void*)t->d_tile_run, (void*)t->d_partials, (void*)t->d_hot, (void*)t->d_tab})
+    if (t->owned(q)) (void)hipFree(q);
   t->d_hot = nullptr;
   t->d_tab = nullptr;
   t->d_keys = nullptr;

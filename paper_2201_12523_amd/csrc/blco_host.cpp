@@ -166,7 +166,8 @@ static Rec* radix_sort(Rec* a, Rec* b, int64_t n, int T, int nt) {
 // Blocks (runs split to max_block_nnz), per-run high bits of every mode, and
 // the tile -> run table, from the runs of equal block key (Section 4.2).
 void finish_runs(const Layout& L, int64_t nnz, const std::vector<int64_t>& run_start,
-                 const std::vector<uint64_t>& run_key, int64_t max_block_nnz, blco_tensor* t) {
+                 const std::vector<uint64_t>& run_key, int64_t max_block_nnz, blco_tensor* t,
+                 bool tiles) {
   const int N = L.N;
   t->run_start = run_start;
   t->run_start.push_back(nnz);
@@ -187,7 +188,12 @@ void finish_runs(const Layout& L, int64_t nnz, const std::vector<int64_t>& run_s
       for (int j = 0; j < L.h[n]; ++j) hi |= ((run_key[r] >> (L.pos[n][L.w[n] + j] - L.K)) & 1ULL) << j;
       t->run_base[(size_t)r * N + n] = (uint32_t)(hi << L.w[n]);
     }
-  // tile -> run of its first non-zero
+  // tile -> run of its first non-zero; the kernels read it only where there are several
+  // runs or block-key bits to add
+  t->tile_run.clear();
+  bool plain = nruns <= 1;
+  for (uint32_t b : t->run_base) plain = plain && b == 0;
+  if (plain || !tiles) return;
   int64_t ntiles = (nnz + kTile - 1) / kTile;
   t->tile_run.resize((size_t)ntiles);
   int64_t r = 0;

@@ -73,6 +73,12 @@ struct blco_tensor {
   int32_t* d_tile_run = nullptr;
   double* d_partials = nullptr;  // sampled-loss partial sums (one per tile group)
   int64_t partials_cap = 0;
+  // device arrays inside [storage, storage + storage_bytes) belong to the caller
+  char* storage = nullptr;
+  size_t storage_bytes = 0;
+  bool owned(const void* q) const {
+    return q && !(storage && (const char*)q >= storage && (const char*)q < storage + storage_bytes);
+  }
   size_t device_bytes = 0;
   blco::StreamState st;
   size_t stream_peak_bytes = 0;
@@ -121,9 +127,11 @@ void free_host_arrays(blco_tensor* t);
 int make_layout(int N, const uint64_t* dims, int key_bits, Layout* L);
 
 // Blocks, per-run high bits and tile -> run table from the runs of equal
-// block key (run_start without the final nnz; run_key their block keys).
+// block key (run_start without the final nnz; run_key their block keys; tiles: whether the
+// tile table is wanted).
 void finish_runs(const Layout& L, int64_t nnz, const std::vector<int64_t>& run_start,
-                 const std::vector<uint64_t>& run_key, int64_t max_block_nnz, blco_tensor* t);
+                 const std::vector<uint64_t>& run_key, int64_t max_block_nnz, blco_tensor* t,
+                 bool tiles = true);
 
 // blco_mttkrp with a workspace of ws_bytes (256-byte aligned; may be empty), and the most of
 // it the call can use.  Defined in blco_device.hip.
@@ -140,11 +148,12 @@ size_t mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dty
 // them must be zero), with u32 values when vin != NULL: (kin, vin) -> (kout, vout),
 // the input is only read, (ktmp, vtmp) are spares of n entries, ws holds
 // sort_workspace_words(n) words.  The u32 form can sort descending (on the
-// complemented key, still stable).
+// complemented key, still stable).  andor: the bitwise AND and OR of all keys where the
+// caller has them (host; the sort then waits for nothing).
 size_t sort_workspace_words(int64_t n);
 int radix_sort_u64(const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
                    uint64_t* ktmp, uint32_t* vtmp, int64_t n, int bits, unsigned int* ws,
-                   void* s);
+                   void* s, const uint64_t* andor = nullptr);
 int radix_sort_u32(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout,
                    uint32_t* ktmp, uint32_t* vtmp, int64_t n, int bits, bool descending,
                    unsigned int* ws, void* s);
@@ -161,9 +170,11 @@ struct SortVals {
   uint64_t* tmp64;
 };
 int radix_sort_u64_vals(const uint64_t* kin, uint64_t* kout, uint64_t* ktmp, const SortVals& v,
-                        int64_t n, int bits, unsigned int* ws, void* s);
+                        int64_t n, int bits, unsigned int* ws, void* s,
+                        const uint64_t* andor = nullptr);
 int radix_sort_u32_vals(const uint32_t* kin, uint32_t* kout, uint32_t* ktmp, const SortVals& v,
-                        int64_t n, int bits, unsigned int* ws, void* s);
+                        int64_t n, int bits, unsigned int* ws, void* s,
+                        const uint64_t* andor = nullptr);
 
 // The indices i < n with flag[i] != 0, ascending, into out; their number into
 // *count (host).  ws holds select_workspace_words(n) words.

@@ -389,7 +389,7 @@ unsigned grid256(int64_t n) { return (unsigned)std::max<int64_t>((n + 255) / 256
 
 template <typename K, bool DESC>
 int sort_impl(const K* kin, K* kout, K* ktmp, const SortVals& v, int64_t n, int bits,
-              unsigned int* ws, hipStream_t s) {
+              unsigned int* ws, hipStream_t s, const uint64_t* known = nullptr) {
   const int nv = v.in32[0] ? (v.in32[1] ? 2 : 1) : 0;
   const bool v64 = v.in64 != nullptr;
   if (n <= 0) return BLCO_OK;
@@ -405,15 +405,20 @@ int sort_impl(const K* kin, K* kout, K* ktmp, const SortVals& v, int64_t n, int 
   unsigned int* tot = ws + 4;                                             // 256
   unsigned int* dbase = tot + kDigits;                                    // 256
   unsigned int* tc = dbase + kDigits;                                     // 256 * ntiles
-  // which digits vary: AND and OR of every key
-  const unsigned long long init[2] = {~0ull, 0ull};
-  SORT_HIPCHK(hipMemcpyAsync(andor, init, sizeof(init), hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL((k_sort_bits<K>), dim3((unsigned)std::min<int64_t>(grid256(n), 1024)),
-                     dim3(256), 0, s, kin, n, andor);
-  SORT_HIPCHK(hipGetLastError());
+  // which digits vary: AND and OR of every key, from the caller or from a pass over them
   unsigned long long ao[2] = {0, 0};
-  SORT_HIPCHK(hipMemcpyAsync(ao, andor, sizeof(ao), hipMemcpyDeviceToHost, s));
-  SORT_HIPCHK(hipStreamSynchronize(s));
+  if (known) {
+    ao[0] = known[0];
+    ao[1] = known[1];
+  } else {
+    const unsigned long long init[2] = {~0ull, 0ull};
+    SORT_HIPCHK(hipMemcpyAsync(andor, init, sizeof(init), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL((k_sort_bits<K>), dim3((unsigned)std::min<int64_t>(grid256(n), 1024)),
+                       dim3(256), 0, s, kin, n, andor);
+    SORT_HIPCHK(hipGetLastError());
+    SORT_HIPCHK(hipMemcpyAsync(ao, andor, sizeof(ao), hipMemcpyDeviceToHost, s));
+    SORT_HIPCHK(hipStreamSynchronize(s));
+  }
   std::vector<int> passes;
   for (int p = 0; p < npass; ++p)
     if (((ao[0] ^ ao[1]) >> (8 * p)) & 255ull) passes.push_back(p);
@@ -495,9 +500,9 @@ static SortVals one_value(const uint32_t* vin, uint32_t* vout, uint32_t* vtmp) {
 
 int radix_sort_u64(const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
                    uint64_t* ktmp, uint32_t* vtmp, int64_t n, int bits, unsigned int* ws,
-                   void* s) {
+                   void* s, const uint64_t* andor) {
   return sort_impl<uint64_t, false>(kin, kout, ktmp, one_value(vin, vout, vtmp), n, bits, ws,
-                                    (hipStream_t)s);
+                                    (hipStream_t)s, andor);
 }
 
 int radix_sort_u32(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout,
@@ -510,13 +515,13 @@ int radix_sort_u32(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uin
 }
 
 int radix_sort_u64_vals(const uint64_t* kin, uint64_t* kout, uint64_t* ktmp, const SortVals& v,
-                        int64_t n, int bits, unsigned int* ws, void* s) {
-  return sort_impl<uint64_t, false>(kin, kout, ktmp, v, n, bits, ws, (hipStream_t)s);
+                        int64_t n, int bits, unsigned int* ws, void* s, const uint64_t* andor) {
+  return sort_impl<uint64_t, false>(kin, kout, ktmp, v, n, bits, ws, (hipStream_t)s, andor);
 }
 
 int radix_sort_u32_vals(const uint32_t* kin, uint32_t* kout, uint32_t* ktmp, const SortVals& v,
-                        int64_t n, int bits, unsigned int* ws, void* s) {
-  return sort_impl<uint32_t, false>(kin, kout, ktmp, v, n, bits, ws, (hipStream_t)s);
+                        int64_t n, int bits, unsigned int* ws, void* s, const uint64_t* andor) {
+  return sort_impl<uint32_t, false>(kin, kout, ktmp, v, n, bits, ws, (hipStream_t)s, andor);
 }
 
 size_t select_workspace_words(int64_t n) {
