@@ -345,7 +345,8 @@ int upload_to(Home& home, T** dst, const T* src, size_t count, hipStream_t s, si
 
 void release_tensor_arrays(blco_tensor* t) {
   for (void* p : {(void*)t->d_keys, (void*)t->d_vals, (void*)t->d_run_start,
-                  (void*)t->d_run_base, (void*)t->d_tile_run, (void*)t->d_hot, (void*)t->d_tab})
+                  (void*)t->d_run_base, (void*)t->d_tile_run, (void*)t->d_hot, (void*)t->d_tab,
+                  (void*)t->d_group})
     if (t->owned(p)) (void)hipFree(p);
   t->d_keys = nullptr;
   t->d_vals = nullptr;
@@ -354,6 +355,7 @@ void release_tensor_arrays(blco_tensor* t) {
   t->d_tile_run = nullptr;
   t->d_hot = nullptr;
   t->d_tab = nullptr;
+  t->d_group = nullptr;
   free_host_arrays(t);
 }
 
@@ -607,9 +609,13 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
                        t->d_tile_run);
     HIPCHK(hipGetLastError());
   }
+  if (t->placement == BLCO_PLACE_DEVICE &&
+      (rc = home.get(&t->d_group, (size_t)L.N * kGroupBuckets, &acc)))
+    return rc;
+  t->device_bytes = acc;
+  if (t->placement == BLCO_PLACE_DEVICE && (rc = make_groups(t, s))) return rc;
   HIPCHK(hipStreamSynchronize(s));
   stage.read(t->build_stage_ms);
-  t->device_bytes = acc;
   return BLCO_OK;
 }
 
@@ -640,7 +646,8 @@ size_t build_workspace(const Layout& L, int64_t nnz) {
 size_t build_storage(const Layout& L, int64_t nnz) {
   const size_t n = (size_t)std::max<int64_t>(nnz, 1);
   return up256(8 * n) + up256(4 * n) + up256((n + kTile - 1) / kTile * 4) +
-         up256((size_t)L.N * kHotMax * 4) + up256((size_t)L.N * kTabWords * 4) + 4096;
+         up256((size_t)L.N * kHotMax * 4) + up256((size_t)L.N * kTabWords * 4) +
+         up256((size_t)L.N * kGroupBuckets * 4) + 4096;
 }
 
 }  // namespace

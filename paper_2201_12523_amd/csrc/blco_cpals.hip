@@ -495,7 +495,7 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
       const int64_t In = (int64_t)t->lay.dims[n];
       hipLaunchKernelGGL(k_pinv_v, dim3(1), dim3(kSolveThreads), 0, s, dG, N, n, R, dV, dS, dfb);
       HIPCHK(hipGetLastError());
-      if ((rc = blco::mttkrp_with(t, n, mt.data(), mdt, R, dM, dw, bytes_w, s)) != BLCO_OK) return rc;
+      if ((rc = blco::mttkrp_careful(t, n, mt.data(), mdt, R, dM, dw, bytes_w, s)) != BLCO_OK) return rc;
       const int per = 256 / R;
       const int64_t blocks = std::min<int64_t>((In + per - 1) / per, 4096);
       hipLaunchKernelGGL(k_apply_vinv, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(256), 0,

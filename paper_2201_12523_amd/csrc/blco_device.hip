@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -61,27 +62,158 @@ __device__ __forceinline__ void zero_range(float* __restrict__ p, int64_t n, int
   }
 }
 
-__global__ __launch_bounds__(256) void k_fill_zero(float* p, int64_t n, float* p2, int64_t n2) {
+// What a call does before its main kernel, in one launch: clears the output and the hot
+// copies, copies factors into rows of Rp elements (zeros from R on), and sets the cursors
+// of the grouping to the buckets' starts.
+struct PrepParams {
+  float* zero[2];
+  int64_t nzero[2];
+  int npad;                // factors to copy
+  const void* src[8];
+  void* dst[8];
+  int64_t rows[8];
+  int R, Rp;
+  const uint32_t* starts;  // kGroupBuckets, or NULL
+  uint32_t* cursor;
+};
+
+template <typename E>
+__device__ __forceinline__ void pad_rows(const E* __restrict__ src, E* __restrict__ dst,
+                                         int64_t rows, int R, int Rp, int64_t i, int64_t stride) {
+  struct alignas(4 * sizeof(E)) Four { E v[4]; };
+  const int q4 = Rp / 4;
+  for (int64_t j = i; j < rows * q4; j += stride) {
+    const int64_t row = j / q4;
+    const int c = (int)(j - row * q4) * 4;
+    Four f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f.v[k] = c + k < R ? src[row * R + c + k] : E(0);
+    reinterpret_cast<Four*>(dst)[j] = f;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_prep(PrepParams p, int bf16) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * 256;
-  zero_range(p, n, i, stride);
-  if (n2 > 0) zero_range(p2, n2, i, stride);
+  for (int z = 0; z < 2; ++z)
+    if (p.nzero[z] > 0) zero_range(p.zero[z], p.nzero[z], i, stride);
+  for (int m = 0; m < p.npad; ++m) {
+    if (bf16)
+      pad_rows(static_cast<const uint16_t*>(p.src[m]), static_cast<uint16_t*>(p.dst[m]), p.rows[m],
+               p.R, p.Rp, i, stride);
+    else
+      pad_rows(static_cast<const float*>(p.src[m]), static_cast<float*>(p.dst[m]), p.rows[m], p.R,
+               p.Rp, i, stride);
+  }
+  if (p.starts && i < kGroupBuckets) p.cursor[i] = p.starts[i];
+}
+
+// out (+)= the first R elements of every row of a padded output.
+__global__ __launch_bounds__(256) void k_unpad(const float* __restrict__ src, int64_t rows, int R,
+                                               int Rp, int add, float* __restrict__ out) {
+  const int64_t n = rows * R, stride = (int64_t)gridDim.x * 256;
+  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += stride) {
+    const int64_t row = j / R;
+    const float v = src[row * Rp + (j - row * R)];
+    out[j] = add ? out[j] + v : v;
+  }
+}
+
+// Bucket of a target row: equal ranges of rows.
+__device__ __forceinline__ uint32_t group_bucket(uint32_t row, uint32_t mul) {
+  return (uint32_t)(((uint64_t)row * mul) >> 32);
+}
+
+// Non-zeros of each bucket of one mode (a tensor of one run without block bits).
+__global__ __launch_bounds__(256) void k_group_count(const uint64_t* __restrict__ keys, int64_t n,
+                                                     int shift, uint32_t mask, uint32_t mul,
+                                                     uint32_t* __restrict__ counts) {
+  __shared__ uint32_t s_c[kGroupBuckets];
+  for (int i = threadIdx.x; i < kGroupBuckets; i += 256) s_c[i] = 0;
+  __syncthreads();
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride)
+    atomicAdd(&s_c[group_bucket((uint32_t)(keys[i] >> shift) & mask, mul)], 1u);
+  __syncthreads();
+  for (int i = threadIdx.x; i < kGroupBuckets; i += 256)
+    if (s_c[i]) atomicAdd(&counts[i], s_c[i]);
+}
+
+// counts -> starts, in place (one workgroup).
+__global__ __launch_bounds__(kGroupBuckets) void k_group_starts(uint32_t* __restrict__ c) {
+  __shared__ uint32_t s_c[kGroupBuckets];
+  __shared__ uint32_t s_wsum[kGroupBuckets / 64];
+  const int tid = threadIdx.x;
+  s_c[tid] = c[tid];
+  __syncthreads();
+  block_exclusive_scan<kGroupBuckets, kGroupBuckets>(s_c, tid, s_wsum);
+  c[tid] = s_c[tid];
+}
+
+// Moves keys and values to their target row's bucket.  Without it a mode whose rows hardly
+// repeat inside a window makes one memory-side atomic row-update per non-zero (4M non-zeros
+// of 300007 x 200003 x 100003, R = 100: 1.53 ms per mode, all of it atomics); in bucket
+// order a window holds few rows, each many times.  A workgroup takes kGroupPer keys per
+// thread, ranks them inside each bucket with LDS counters, reserves its places with one
+// atomic per bucket, and writes them where they go: runs of a bucket are short, but the
+// workgroups' runs adjoin, so the L2 completes the lines.
+constexpr int kGroupPer = 16;
+__global__ __launch_bounds__(1024) void k_group(const uint64_t* __restrict__ keys,
+                                                const float* __restrict__ vals, int64_t n,
+                                                int shift, uint32_t mask, uint32_t mul,
+                                                uint32_t* __restrict__ cursor,
+                                                uint64_t* __restrict__ gkeys,
+                                                float* __restrict__ gvals) {
+  __shared__ uint32_t s_c[kGroupBuckets];
+  const int tid = threadIdx.x;
+  static_assert(kGroupBuckets == 1024, "one bucket per thread");
+  s_c[tid] = 0;
+  const int64_t k0 = (int64_t)blockIdx.x * (1024 * kGroupPer) + tid;
+  uint64_t key[kGroupPer];
+  uint32_t at[kGroupPer];
+#pragma unroll
+  for (int i = 0; i < kGroupPer; ++i) {
+    const int64_t k = k0 + (int64_t)i * 1024;
+    key[i] = k < n ? keys[k] : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kGroupPer; ++i) {
+    const uint32_t b = group_bucket((uint32_t)(key[i] >> shift) & mask, mul);
+    at[i] = k0 + (int64_t)i * 1024 < n ? atomicAdd(&s_c[b], 1u) : 0u;
+  }
+  __syncthreads();
+  const uint32_t c = s_c[tid];
+  const uint32_t base = c ? atomicAdd(&cursor[tid], c) : 0u;
+  __syncthreads();
+  s_c[tid] = base;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kGroupPer; ++i) {
+    const int64_t k = k0 + (int64_t)i * 1024;
+    if (k < n) {
+      const uint32_t q = s_c[group_bucket((uint32_t)(key[i] >> shift) & mask, mul)] + at[i];
+      gkeys[q] = key[i];
+      gvals[q] = vals[k];
+    }
+  }
 }
 
 // Adds the copies of frequent row hot[blockIdx.x] to the output (see k_mttkrp_win): each
 // thread sums every fourth copy of one rank in order, then the four partial sums meet.
 __global__ __launch_bounds__(kBlock) void k_hot_sum(const float* __restrict__ copy,
                                                     const uint32_t* __restrict__ hot, int copies,
-                                                    int stride, int R, float* __restrict__ out) {
+                                                    int stride, int RV, int R,
+                                                    float* __restrict__ out) {
   __shared__ float s_part[kBlock];
-  const int r = threadIdx.x & 63, q = threadIdx.x >> 6;   // R <= 64
+  const int r = threadIdx.x & 63, q = threadIdx.x >> 6;   // RV <= 64
   const float* c = copy + (size_t)blockIdx.x * copies * stride;
   float a = 0.f;
-  if (r < R)
+  if (r < RV)
     for (int i = q; i < copies; i += 4) a += c[(size_t)i * stride + r];
   s_part[threadIdx.x] = a;
   __syncthreads();
-  if (q == 0 && r < R) {
+  if (q == 0 && r < RV) {
     const float v = (s_part[r] + s_part[64 + r]) + (s_part[128 + r] + s_part[192 + r]);
     if (v != 0.f) out[(size_t)hot[blockIdx.x] * R + r] += v;
   }
@@ -745,15 +877,23 @@ static void fill_params(const blco_tensor* t, KParams* p) {
   p->scale = 1.0f;
 }
 
-static int fill_zero(float* out, int64_t n, hipStream_t s, float* out2 = nullptr,
-                     int64_t n2 = 0) {
-  const int64_t most = std::max(n, n2);
+// One launch of k_prep, or none where there is nothing to do.
+static int prepare(const PrepParams& p, int fdt, hipStream_t s) {
+  int64_t most = p.starts ? kGroupBuckets * 4 : 0;
+  for (int z = 0; z < 2; ++z) most = std::max(most, p.nzero[z]);
+  for (int m = 0; m < p.npad; ++m) most = std::max(most, p.rows[m] * p.Rp);
   if (most <= 0) return BLCO_OK;
-  int64_t blocks = std::min<int64_t>((most / 4 + 255) / 256 + 1, 8192);
-  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, out,
-                     std::max<int64_t>(n, 0), out2, n2);
+  const int64_t blocks = std::min<int64_t>((most / 4 + 255) / 256 + 1, 8192);
+  hipLaunchKernelGGL(k_prep, dim3((unsigned)blocks), dim3(256), 0, s, p, fdt == BLCO_BF16 ? 1 : 0);
   HIPCHK(hipGetLastError());
   return BLCO_OK;
+}
+
+static int fill_zero(float* out, int64_t n, hipStream_t s) {
+  PrepParams p = {};
+  p.zero[0] = out;
+  p.nzero[0] = n;
+  return prepare(p, BLCO_F32, s);
 }
 
 static int check_factor_args(const blco_tensor* t, int mode, const void* const* factors, int fdt,
@@ -785,10 +925,17 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
 //
 // At R > 32 a window of 2048 leaves two workgroups per CU and is the faster where rows
 // repeat (5M non-zeros of 2000 x 1000 x 500, R = 64: 0.13 and 0.18 ms per mode; 5 modes,
-// R = 35: 0.30 and 0.41 ms); one of 4096 merges more where they do not, on flat modes
-// (50M non-zeros of 2^24 x 2^22 x 2^20 x 2^10, R = 64 bf16, its last two: 4.37 and 2.80 ms in
-// windows of 2048, 3.83 and 2.48 ms).
-static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n) {
+// R = 35: 0.30 and 0.41 ms); one of 4096 merges more where they do not, on flat modes with an
+// expected 0.3 flushes per non-zero or more (50M non-zeros of 2^24 x 2^22 x 2^20 x 2^10,
+// R = 64 bf16, its last two: 4.37 and 2.80 ms in windows of 2048, 3.83 and 2.48 ms) unless
+// their non-zeros were grouped (20M of 200003 x 100003 x 50021, the same: 2.64 and 3.15 ms).
+//
+// least: the smallest window taken.  A caller that amplifies the sums' rounding (CP-ALS
+// multiplies them by V^+) asks for larger ones: smaller windows put more terms of a row
+// through atomics, one after another, onto a sum that is nearly whole (power-law non-zeros,
+// 3 iterations, from 64 bits: 60k: factors 1.4e-5 in windows of 256 and 4e-6 in windows of
+// 1024; 20k: 4.9e-6 in windows of 1024 and 3.8e-6 in windows of 2048).
+static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n, int least) {
   if (R > 64 || N > kWideMaxN) return 1;
   // the fused residual walk's records hold one field more: at N = 5 two windows of 2048 no
   // longer share a CU, and at R > 32 its walk has no registers for four per thread
@@ -796,13 +943,14 @@ static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n) {
   if (big) return most;
   const int64_t cus = device_cus();
   for (int w : {-4, -2, 1, 2})
-    if (w == most || n <= (w < 0 ? kWin / -w : kWin * w) * cus) return w;
+    if (w == most || (w >= least && n <= (w < 0 ? kWin / -w : kWin * w) * cus)) return w;
   return most;
 }
 
-static KernelFn select_win(int N, int R, int fdt, bool big, bool stash, int wpt) {
+static KernelFn select_win(int N, int R, bool even, int fdt, bool big, bool stash, int wpt) {
   if (big) return select_win_big(N, R, fdt, stash, wpt);
-  return fdt == BLCO_F32 ? select_win_f32(N, R, stash, wpt) : select_win_bf16(N, R, stash, wpt);
+  return fdt == BLCO_F32 ? select_win_f32(N, R, stash, wpt)
+                         : select_win_bf16(N, R, even, stash, wpt);
 }
 
 // Frequent rows of the target mode that the window kernel `f` keeps in its
@@ -830,8 +978,8 @@ static int stash_rows(const blco_tensor* t, int mode, int rank, KernelFn f) {
 // full stash, which is tied to windows of 1024 non-zeros: 2048 merge about as much without
 // its look-up and its resident workgroups.  An explicit threshold at build time keeps the
 // full stash.
-static bool copies_ok(const blco_tensor* t, int mode, int rank, bool big) {
-  return !t->hot_forced && !big && t->lay.N <= kWideMaxN && rank <= 64 && t->d_tab &&
+static bool copies_ok(const blco_tensor* t, int mode, int rank, int ranks, bool big) {
+  return !t->hot_forced && !big && t->lay.N <= kWideMaxN && ranks <= 64 && t->d_tab &&
          t->lay.dims[mode] * (uint64_t)rank <= (1ULL << 31);
 }
 
@@ -862,6 +1010,20 @@ static int copy_stride(int rank) { return (rank + 15) / 16 * 16; }   // whole 64
 static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool window,
                         bool resid);
 
+// Expected row flushes per non-zero of mode `mode` in windows of W of n non-zeros, taken as
+// spread evenly over the index space: the window covers the index's lowest
+// log2(W * cells / n) bits, so mode m moves over 2^(its bits among them) rows.
+static double window_flushes(const blco_tensor* t, int mode, double W, double n) {
+  const Layout& L = t->lay;
+  double k = log2(W / n);
+  for (int m = 0; m < L.N; ++m) k += log2((double)L.dims[m]);
+  double bits = 0;
+  for (int j = 0; j < L.b[mode]; ++j)
+    bits += std::min(1.0, std::max(0.0, k - (double)L.pos[mode][j]));
+  const double rows = std::min((double)L.dims[mode], exp2(bits));
+  return rows * -expm1(-W / rows) / W;
+}
+
 // The window kernel a launch over n non-zeros takes: its instantiation, windows, frequent
 // rows in LDS and the slots of their look-up table.
 struct WinPlan {
@@ -873,31 +1035,37 @@ struct WinPlan {
   size_t bytes;  // workspace of the copies
 };
 
-// room: bytes of workspace the call has; copies that do not fit it are not taken, and the
-// mode falls back to the full stash where that applies.
-static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int fdt, bool big, bool resid,
-                        int64_t n, size_t room) {
+// rank: elements between output rows; ranks, gather: ranks and ranks to gather (more
+// where factors are padded); even: factor rows an even number of elements
+// apart.  room: bytes of workspace there are; copies that do not fit it are not taken, and
+// the mode falls back to the full stash where that applies.
+static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int ranks, int gather, bool even,
+                        int fdt, bool big, bool resid, int64_t n, size_t room, bool careful,
+                        bool grouped) {
   const int N = t->lay.N;
   auto pick = [&](bool stash, int w) {
-    return resid ? select_res(N, rank, fdt, stash, w) : select_win(N, rank, fdt, big, stash, w);
+    return resid ? select_res(N, gather, even, fdt, stash, w)
+                 : select_win(N, gather, even, fdt, big, stash, w);
   };
   auto windows = [&](int w) {
     const int64_t W = w < 0 ? kWin / -w : (int64_t)kWin * w;
     return (n + W - 1) / W;
   };
   const bool frequent = has_frequent_rows(t, mode);
-  WinPlan w = {nullptr, win_wpt(N, rank, resid, big, !frequent, n), 0, 0, 0, 0};
+  const bool flat = !frequent && !grouped &&
+                    window_flushes(t, mode, 2048.0, (double)t->nnz) >= 0.3;
+  WinPlan w = {nullptr, win_wpt(N, gather, resid, big, flat, n, careful ? (frequent ? 1 : 2) : -4), 0, 0, 0, 0};
   // one non-zero per thread (the residual walk at N = 5): -1 is the form with copies
   const int lw = w.wpt == 1 ? -1 : w.wpt;
   const bool few = windows(lw) <= kCopyMinWindows;
-  if (frequent && copies_ok(t, mode, rank, big) && (few || (lw != -1 || resid))) {
+  if (frequent && copies_ok(t, mode, rank, ranks, big) && (few || (lw != -1 || resid))) {
     if (few) {
       w.f = pick(false, w.wpt);
       w.nwin = windows(w.wpt);
       return w;
     }
     const int c = copy_count(windows(lw));
-    const size_t bytes = sizeof(float) * (size_t)t->nhot[mode] * c * copy_stride(rank);
+    const size_t bytes = sizeof(float) * (size_t)t->nhot[mode] * c * copy_stride(ranks);
     if (bytes <= room) {
       w.f = pick(true, lw);
       w.wpt = lw;
@@ -921,7 +1089,120 @@ static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int fdt, bool 
 struct Work {
   char* p = nullptr;
   size_t bytes = 0;
+  bool careful = false;   // windows of at least 2048, or 1024 with frequent rows (win_wpt)
 };
+
+static size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Elements between factor rows of a launch: the rank, or more where the factors are copied
+// into padded rows first, whose padding is gathered and multiplied like ranks.  Ranks that
+// do not fill the 16-lane groups mask lanes at every gather, rows that start inside 16 bytes
+// gather at half rate, and bf16 rows an odd number of elements apart take 2-byte loads.
+// Rows are padded to whole groups where they are few against the non-zeros; up to 32 ranks
+// also where they are not that few; and above, bf16 rows to 16 bytes only (longer rows are
+// more lines, and rows enough to miss the caches are bound by those).  4M non-zeros, all
+// modes, unpadded and padded, with the outputs padded as below: 2000 x 1000 x 500, fp32,
+// R = 10: 265 and 157 us; R = 28: 213 and 193; R = 35: 382 and 255; R = 97: 737 and 582;
+// bf16 R = 17: 416 and 188; R = 35: 756 and 351; 21007 x 9001 x 1501 x 367 x 31, R = 35: 1293
+// and 1060; R = 60: 1282 and 1127; 200000 x 100000 x 20000, R = 17: 553 and 482; R = 31: 635
+// and 490; bf16 R = 35: 952, to 40 712 and to 48 780; fp32 R = 50: 842, to 52 869 and to 64
+// 898.  The copy reads and writes every row once (about 0.06 us per thousand rows at R = 32).
+constexpr size_t kPadMax = (size_t)1 << 30;   // bytes of padded factors
+static int padded_rank(const blco_tensor* t, int mode, int rank, int fdt, bool all, int64_t n) {
+  uint64_t rows = 0;
+  for (int m = 0; m < t->lay.N; ++m)
+    if (all || m != mode) rows += t->lay.dims[m];
+  if (n < (1 << 18) || rows * 8 > (uint64_t)n) return rank;
+  int Rp = (rank + 15) / 16 * 16;
+  if (rank > 32 && rows * 32 > (uint64_t)n)
+    Rp = fdt == BLCO_BF16 && rank % 2 != 0 ? (rank + 7) / 8 * 8 : rank;
+  return rows * Rp * factor_elem_bytes(fdt) > kPadMax ? rank : Rp;
+}
+
+// Elements between the rows the window kernel flushes to: the rank, or whole 64-byte lines in
+// a workspace whose rows are then copied to the output (k_unpad).  Unpadded rows cross into
+// more lines and share them, and a line's atomics are performed one after another: 4M
+// non-zeros of 200000 x 100000 x 20000, all modes: R = 10: 502 and 371 us; R = 31: 635 and
+// 532; R = 97: 1594 and 1530.  Clearing and copying pay where the rows are few against the
+// non-zeros: R = 50 on the same tensor took 841 us, with all modes padded 870.
+static int padded_out(const blco_tensor* t, int mode, int rank, int64_t n) {
+  if (n < (1 << 18) || t->lay.dims[mode] * (rank > 32 ? 32 : 8) > (uint64_t)n) return rank;
+  return (rank + 15) / 16 * 16;
+}
+
+// Whether a launch over n non-zeros moves them to buckets of target rows first (k_group):
+// where the row flushes that saves, at the memory side's rate (about 52 ps per 64-byte line),
+// are worth twice the move (about 20 us and 18 ps per non-zero).  Only flat modes of
+// tensors of one run, whose buckets were counted at build time.  4M non-zeros of 300007 x
+// 200003 x 100003, all modes, as they lie and moved: R = 32: 1164 and 575 us; R = 48: 1747 and
+// 990; R = 100: 4459 and 2106, bf16 4396 and 1561; R = 16 is left as it is (flushes of one
+// line: 0.19 ms per mode).  20M of 200003 x 100003 x 50021, bf16 R = 64: 9144 and 2638.
+static bool group_pays(const blco_tensor* t, int mode, int rank, int64_t n) {
+  if (!t->d_group || !t->grouped[mode] || n != t->nnz) return false;
+  const double W = rank > 64 ? 1024 : 2048, N = (double)n;
+  const double lines = ceil(rank / 16.0) + (rank % 16 ? 0.5 : 0.0);
+  const double now = window_flushes(t, mode, rank > 32 && rank <= 64 ? 4096 : W, N);
+  // in bucket order: W non-zeros of the rows of W / (n / buckets) buckets, at least one
+  const double per = N / kGroupBuckets, I = (double)t->lay.dims[mode];
+  const double rows = std::max(1.0, I / kGroupBuckets * std::max(1.0, W / per));
+  const double then = std::min(now, rows * -expm1(-W / rows) / W + 1.0 / per);
+  return N * (now - then) * lines * 52e-12 > 2 * (20e-6 + N * 18e-12);
+}
+
+// How a call runs: padded factors (their row stride, 0: as they are) and output rows,
+// grouping, and the workspace that takes.
+struct CallPlan {
+  int pad;
+  int out;       // elements between flushed rows (the rank: the output itself)
+  bool group;
+  size_t copy_bytes;
+  size_t bytes;
+};
+
+static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int res, bool resid,
+                          int64_t n, size_t room) {
+  const int N = t->lay.N;
+  const size_t fsz = factor_elem_bytes(fdt);
+  CallPlan c = {0, rank, false, 0, 0};
+  const bool reg = res == BLCO_RES_REGISTER;
+  auto left = [&] { return room > c.bytes ? room - c.bytes : 0; };
+  const bool big = big_gathers(t, mode, rank, fdt, false, false) ||
+                   big_gathers(t, mode, rank, fdt, true, resid);
+  if (reg) {
+    c.copy_bytes = up256(plan_win(t, mode, rank, rank, rank, rank % 2 == 0, fdt,
+                                  big_gathers(t, mode, rank, fdt, true, resid), resid, n, room,
+                                  false, false)
+                             .bytes);
+    c.bytes = c.copy_bytes;
+  }
+  if (!big) {
+    const int Rp = padded_rank(t, mode, rank, fdt, resid, n);
+    size_t bytes = 0;
+    for (int m = 0; m < N; ++m)
+      if (m != mode || resid) bytes += up256((size_t)t->lay.dims[m] * Rp * fsz);
+    if (Rp != rank && bytes <= left()) {
+      c.pad = Rp;
+      c.bytes += bytes;
+    }
+  }
+  if (reg && !big) {
+    const int Ro = padded_out(t, mode, rank, n);
+    const size_t bytes = up256((size_t)t->lay.dims[mode] * Ro * sizeof(float));
+    if (Ro != rank && bytes <= left()) {
+      c.out = Ro;
+      c.bytes += bytes;
+    }
+  }
+  if (reg && !resid && !big && group_pays(t, mode, rank, n)) {
+    const size_t bytes =
+        up256(8 * (size_t)n) + up256(4 * (size_t)n) + up256(4 * (size_t)kGroupBuckets);
+    if (bytes <= left()) {
+      c.group = true;
+      c.bytes += bytes;
+    }
+  }
+  return c;
+}
 
 // Launch the MTTKRP kernel over [lo, lo + n) of the tensor given by keys/vals, clearing the
 // output first if `clear`.
@@ -933,24 +1214,21 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
                          hipStream_t s, const Work& ws, bool clear, float* resid = nullptr) {
   const int64_t clear_n = clear ? (int64_t)t->lay.dims[mode] * rank : 0;
   if (n <= 0) return fill_zero(out, clear_n, s);
+  const int N = t->lay.N;
   KParams p;
   fill_params(t, &p);
   p.keys = keys;
   p.vals = vals;
   p.base = lo;
   p.n = n;
-  for (int m = 0; m < t->lay.N; ++m) p.A[m] = factors[m];
+  for (int m = 0; m < N; ++m) p.A[m] = factors[m];
   p.out = out;
   p.R = rank;
   p.mode = mode;
   p.scale = scale;
   p.scale_dev = scale_dev;
+  p.resid = resid;
   const size_t fsz = factor_elem_bytes(fdt);
-  p.rowbytes = (uint32_t)((size_t)rank * fsz);
-  for (int m = 0; m < t->lay.N; ++m) {
-    const size_t bytes = (size_t)t->lay.dims[m] * rank * fsz;
-    p.abytes[m] = (uint32_t)std::min<size_t>(bytes, 0xFFFFFFFFull);
-  }
   const bool big = big_gathers(t, mode, rank, fdt, false, false);
   const bool big_win = big_gathers(t, mode, rank, fdt, true, resid != nullptr);
   int sw = 0;
@@ -959,9 +1237,33 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
   if (resid && (res != BLCO_RES_REGISTER || big || rank > 64 ||
                 (size_t)t->lay.dims[mode] * rank * fsz > 0xFFFFFFFFull))
     return set_error(BLCO_EUNSUPPORTED, "fused residual walk on mode %d", mode);
-  p.resid = resid;
+  const CallPlan cp = plan_call(t, mode, rank, fdt, res, resid != nullptr, n, ws.bytes);
+  // the workspace: hot copies, padded factors, grouped non-zeros and their cursors
+  PrepParams pre = {};
+  pre.zero[0] = out;
+  pre.nzero[0] = clear_n;
+  char* at = ws.p + cp.copy_bytes;
+  int stride = rank;
+  if (cp.pad) {
+    stride = cp.pad;
+    pre.R = rank;
+    pre.Rp = stride;
+    for (int m = 0; m < N; ++m) {
+      if (m == mode && !resid) continue;
+      pre.src[pre.npad] = factors[m];
+      pre.dst[pre.npad] = at;
+      pre.rows[pre.npad++] = (int64_t)t->lay.dims[m];
+      p.A[m] = at;
+      at += up256((size_t)t->lay.dims[m] * stride * fsz);
+    }
+  }
+  p.rowbytes = (uint32_t)((size_t)stride * fsz);
+  for (int m = 0; m < N; ++m) {
+    const size_t bytes = (size_t)t->lay.dims[m] * stride * fsz;
+    p.abytes[m] = (uint32_t)std::min<size_t>(bytes, 0xFFFFFFFFull);
+  }
   if (res == BLCO_RES_HIERARCHICAL) {
-    int rc = fill_zero(out, clear_n, s);
+    int rc = prepare(pre, fdt, s);
     if (rc) return rc;
     p.short_rows = (uint32_t)t->lay.dims[mode];
     p.short_width = sw;
@@ -973,48 +1275,80 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
     int64_t per = std::max<int64_t>((n + want - 1) / want, (int64_t)kShortB);
     per = (per + kShortB - 1) / kShortB * kShortB;
     const int64_t nwg = (n + per - 1) / per;
-    const size_t lds = short_lds(t->lay.N, t->lay.dims[mode], sw);
-    ShortFn f = select_short(t->lay.N, sw, rank, fdt, big);
+    const size_t lds = short_lds(N, t->lay.dims[mode], sw);
+    ShortFn f = select_short(N, sw, stride, fdt, big);
     hipLaunchKernelGGL(f, dim3((unsigned)nwg, (unsigned)slices), dim3(kShortB), lds, s, p, per);
     HIPCHK(hipGetLastError());
     return BLCO_OK;
   }
-  {
-    const WinPlan w = plan_win(t, mode, rank, fdt, big_win, resid != nullptr, n, ws.bytes);
-    const KernelFn f = w.f;
-    const int K = w.stash;
-    const int64_t nwin = w.nwin;
-    p.hot = t->d_hot + (size_t)mode * kHotMax;
-    p.nhot = K;
-    if (w.copies) {
-      p.tab = t->d_tab + (size_t)mode * kTabWords;
-      float* copy = reinterpret_cast<float*>(ws.p);
-      p.copy_off = reinterpret_cast<char*>(copy) - reinterpret_cast<char*>(out);
-      p.copies = w.copies;
-      p.copy_stride = copy_stride(rank);
-      int rc = fill_zero(out, clear_n, s, copy, (int64_t)(w.bytes / sizeof(float)));
-      if (rc) return rc;
-    } else {
-      int rc = fill_zero(out, clear_n, s);
-      if (rc) return rc;
-    }
-    const size_t dyn = K > 0 ? (size_t)K * rank * 4 + 2 * (size_t)kHotSlots * 4 : 0;
-    // with a stash: persistent workgroups, kWinRounds times the resident count
-    // (two per CU) in a long launch, which balances its end (1-2% faster than one round
-    // on 50M non-zeros); once the resident count in a shorter one, where the stash
-    // flushes count more (2M non-zeros, R = 16: 68 us and 58 us); without one: a
-    // workgroup per window (about 1% faster than persistent ones)
-    const int rounds = nwin >= 16 * 1024 ? kWinRounds : 1;
-    const int64_t grid =
-        K > 0 ? std::min<int64_t>(nwin, (int64_t)device_cus() * 2 * rounds) : nwin;
-    hipLaunchKernelGGL(f, dim3((unsigned)grid), dim3(kWin), dyn, s, p);
-    if (w.copies) {
-      HIPCHK(hipGetLastError());
-      hipLaunchKernelGGL(k_hot_sum, dim3((unsigned)t->nhot[mode]), dim3(kBlock), 0, s,
-                         (const float*)ws.p, p.hot, p.copies, p.copy_stride, rank, out);
-    }
+  // flushed rows in the workspace: their padding takes the sums of padded gathers (zeros)
+  float* rows = out;
+  const int ro = cp.out;
+  if (ro != rank) {
+    rows = reinterpret_cast<float*>(at);
+    at += up256((size_t)t->lay.dims[mode] * ro * sizeof(float));
+    pre.zero[0] = rows;
+    pre.nzero[0] = (int64_t)t->lay.dims[mode] * ro;
+    p.R = ro;
   }
+  if (cp.group) {
+    uint64_t* gk = reinterpret_cast<uint64_t*>(at);
+    at += up256(8 * (size_t)n);
+    float* gv = reinterpret_cast<float*>(at);
+    at += up256(4 * (size_t)n);
+    pre.starts = t->d_group + (size_t)mode * kGroupBuckets;
+    pre.cursor = reinterpret_cast<uint32_t*>(at);
+    p.keys = gk;
+    p.vals = gv;
+  }
+  p.RG = stride;
+  p.RV = std::max(rank, std::min(stride, ro));
+  p.out = rows;
+  const WinPlan w = plan_win(t, mode, ro, rank, stride, stride % 2 == 0, fdt, big_win,
+                             resid != nullptr, n, cp.copy_bytes, ws.careful, cp.group);
+  p.hot = t->d_hot + (size_t)mode * kHotMax;
+  p.nhot = w.stash;
+  if (w.copies) {
+    float* copy = reinterpret_cast<float*>(ws.p);
+    p.tab = t->d_tab + (size_t)mode * kTabWords;
+    p.copy_off = reinterpret_cast<char*>(copy) - reinterpret_cast<char*>(rows);
+    p.copies = w.copies;
+    p.copy_stride = copy_stride(rank);
+    pre.zero[1] = copy;
+    pre.nzero[1] = (int64_t)(w.bytes / sizeof(float));
+  }
+  int rc = prepare(pre, fdt, s);
+  if (rc) return rc;
+  if (cp.group) {
+    const int64_t per = 1024 * kGroupPer;
+    hipLaunchKernelGGL(k_group, dim3((unsigned)((n + per - 1) / per)), dim3(1024), 0, s, keys,
+                       vals, n, (int)p.shift[mode], p.mask[mode], t->group_mul[mode], pre.cursor,
+                       const_cast<uint64_t*>(p.keys), const_cast<float*>(p.vals));
+    HIPCHK(hipGetLastError());
+  }
+  const size_t dyn = w.stash > 0 ? (size_t)w.stash * ro * 4 + 2 * (size_t)kHotSlots * 4 : 0;
+  // with a stash: persistent workgroups, kWinRounds times the resident count
+  // (two per CU) in a long launch, which balances its end (1-2% faster than one round
+  // on 50M non-zeros); once the resident count in a shorter one, where the stash
+  // flushes count more (2M non-zeros, R = 16: 68 us and 58 us); without one: a
+  // workgroup per window (about 1% faster than persistent ones)
+  const int rounds = w.nwin >= 16 * 1024 ? kWinRounds : 1;
+  const int64_t grid =
+      w.stash > 0 ? std::min<int64_t>(w.nwin, (int64_t)device_cus() * 2 * rounds) : w.nwin;
+  hipLaunchKernelGGL(w.f, dim3((unsigned)grid), dim3(kWin), dyn, s, p);
   HIPCHK(hipGetLastError());
+  if (w.copies) {
+    hipLaunchKernelGGL(k_hot_sum, dim3((unsigned)t->nhot[mode]), dim3(kBlock), 0, s,
+                       (const float*)ws.p, p.hot, p.copies, p.copy_stride, rank, ro, rows);
+    HIPCHK(hipGetLastError());
+  }
+  if (ro != rank) {
+    const int64_t I = (int64_t)t->lay.dims[mode];
+    const int64_t blocks = std::min<int64_t>((I * rank + 255) / 256, 8192);
+    hipLaunchKernelGGL(k_unpad, dim3((unsigned)blocks), dim3(256), 0, s, (const float*)rows, I, rank,
+                       ro, clear ? 0 : 1, out);
+    HIPCHK(hipGetLastError());
+  }
   return BLCO_OK;
 }
 
@@ -1057,8 +1391,10 @@ static void release_device(blco_tensor* t) {
   if (st.copy_stream) (void)hipStreamDestroy((hipStream_t)st.copy_stream);
   st = StreamState();
   for (void* q : {(void*)t->d_keys, (void*)t->d_vals, (void*)t->d_run_start, (void*)t->d_run_base,
-                  (void*)t->d_tile_run, (void*)t->d_partials, (void*)t->d_hot, (void*)t->d_tab})
+                  (void*)t->d_tile_run, (void*)t->d_partials, (void*)t->d_hot, (void*)t->d_tab,
+                  (void*)t->d_group})
     if (t->owned(q)) (void)hipFree(q);
+  t->d_group = nullptr;
   t->d_hot = nullptr;
   t->d_tab = nullptr;
   t->d_keys = nullptr;
@@ -1067,6 +1403,44 @@ static void release_device(blco_tensor* t) {
   t->d_run_base = nullptr;
   t->d_tile_run = nullptr;
   t->d_partials = nullptr;
+}
+
+// Counts the buckets of the modes k_group may serve: flat modes of a device tensor of one run
+// without block-key bits, long enough to have several rows per bucket, whose windows hardly
+// repeat a row.
+int blco::make_groups(blco_tensor* t, void* stream) {
+  const Layout& L = t->lay;
+  if (!t->d_keys || t->nnz < kGroupMinNnz || t->nnz >= ((int64_t)1 << 32) ||
+      t->run_start.size() != 2 || L.S > 0)
+    return BLCO_OK;
+  bool any = false;
+  for (int m = 0; m < L.N; ++m) {
+    t->grouped[m] = L.dims[m] >= 4 * (uint64_t)kGroupBuckets && !has_frequent_rows(t, m) &&
+                    window_flushes(t, m, 2048.0, (double)t->nnz) >= 0.4;
+    any = any || t->grouped[m];
+  }
+  if (!any) return BLCO_OK;
+  hipStream_t s = (hipStream_t)stream;
+  if (!t->d_group) {
+    const size_t bytes = sizeof(uint32_t) * (size_t)L.N * kGroupBuckets;
+    HIPCHK(hipMalloc((void**)&t->d_group, bytes));
+    t->device_bytes += bytes;
+  }
+  int rc = fill_zero(reinterpret_cast<float*>(t->d_group), (int64_t)L.N * kGroupBuckets, s);
+  if (rc) return rc;
+  KParams p;
+  fill_params(t, &p);
+  for (int m = 0; m < L.N; ++m) {
+    if (!t->grouped[m]) continue;
+    t->group_mul[m] = (uint32_t)(((uint64_t)kGroupBuckets << 32) / L.dims[m]);
+    uint32_t* c = t->d_group + (size_t)m * kGroupBuckets;
+    hipLaunchKernelGGL(k_group_count, dim3(256), dim3(256), 0, s, (const uint64_t*)t->d_keys,
+                       t->nnz, (int)p.shift[m], p.mask[m], t->group_mul[m], c);
+    HIPCHK(hipGetLastError());
+    hipLaunchKernelGGL(k_group_starts, dim3(1), dim3(kGroupBuckets), 0, s, c);
+    HIPCHK(hipGetLastError());
+  }
+  return BLCO_OK;
 }
 
 // ====================================================================== C ABI
@@ -1134,6 +1508,13 @@ extern "C" int blco_build(int nmodes, const uint64_t* dims, int64_t nnz,
     free_host_arrays(t);
   }
   t->device_bytes = acc;
+  if (placement == BLCO_PLACE_DEVICE) {
+    if ((rc = make_groups(t, nullptr))) return fail(rc);
+    if (hipStreamSynchronize(nullptr) != hipSuccess) {
+      set_error(BLCO_EDEVICE, "bucket counts failed");
+      return fail(BLCO_EDEVICE);
+    }
+  }
   *out = t;
   return BLCO_OK;
 }
@@ -1160,13 +1541,12 @@ static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool 
 static size_t mode_workspace(const blco_tensor* t, int mode, int rank, int fdt, bool resid,
                              int64_t n) {
   int sw = 0;
-  if (n <= 0 || resolve(t, mode, rank, &sw) != BLCO_RES_REGISTER) {
+  const int res = n > 0 ? resolve(t, mode, rank, &sw) : BLCO_EINVAL;
+  if (res < 0) {
     clear_error();
     return 0;
   }
-  return plan_win(t, mode, rank, fdt, big_gathers(t, mode, rank, fdt, true, resid), resid, n,
-                  ~(size_t)0)
-      .bytes;
+  return plan_call(t, mode, rank, fdt, res, resid, n, ~(size_t)0 / 2).bytes;
 }
 
 // The in-memory MTTKRP calls, with an optional workspace.
@@ -1187,17 +1567,17 @@ size_t blco::mttkrp_workspace(const blco_tensor* t, int mode, int rank, int fact
   return mode_workspace(t, mode, rank, factor_dtype, false, t->nnz);
 }
 
-int blco::mttkrp_with(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
-                      int rank, float* out, void* ws, size_t ws_bytes, void* stream) {
+int blco::mttkrp_careful(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
+                         int rank, float* out, void* ws, size_t ws_bytes, void* stream) {
   return mttkrp_impl(t, mode, t->d_vals, factors, factor_dtype, rank, nullptr, 1.0, false, out,
-                     Work{static_cast<char*>(ws), ws_bytes}, (hipStream_t)stream);
+                     Work{static_cast<char*>(ws), ws_bytes, true}, (hipStream_t)stream);
 }
 
 static int make_work(void* ws, size_t bytes, Work* w) {
   if (!ws && bytes > 0) return set_error(BLCO_EINVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) & 255)
     return set_error(BLCO_EINVAL, "workspace must be 256-byte aligned");
-  *w = Work{static_cast<char*>(ws), ws ? bytes : 0};
+  *w = Work{static_cast<char*>(ws), ws ? bytes : 0, false};
   return BLCO_OK;
 }
 
@@ -1805,7 +2185,8 @@ extern "C" int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int*
   if (mode < 0 || mode >= t->lay.N)
     return set_error(BLCO_EINVAL, "mode %d outside 0..%d", mode, t->lay.N - 1);
   if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
-  const WinPlan w = plan_win(t, mode, rank, BLCO_F32, false, false, std::max<int64_t>(t->nnz, 1), 0);
+  const WinPlan w = plan_win(t, mode, rank, rank, rank, rank % 2 == 0, BLCO_F32, false, false,
+                             std::max<int64_t>(t->nnz, 1), 0, false);
   *rows = w.stash;
   return BLCO_OK;
 }

@@ -12,6 +12,8 @@ namespace blco {
 
 constexpr int kTile = 64;  // non-zeros per wave tile (one per lane of a wave64)
 constexpr int kHotMax = 256;  // frequent rows kept per mode
+constexpr int kGroupBuckets = 1024;            // target-row buckets of a grouped MTTKRP
+constexpr int64_t kGroupMinNnz = 1 << 20;      // fewer non-zeros are never grouped
 // Table of a mode's frequent rows, as the window kernel's hot copies look them up: a
 // multiplier, kTabSlots rows (0xFFFFFFFF: empty; the row r is at slot
 // (r * multiplier) >> (32 - kTabBits)), and kTabSlots one-byte places in `hot`.
@@ -95,6 +97,11 @@ struct blco_tensor {
   uint32_t* d_hot = nullptr;
   std::vector<uint32_t> tab;         // N * kTabWords: row tables of the frequent rows
   uint32_t* d_tab = nullptr;
+  // grouped MTTKRP: first non-zero of each bucket of a mode (N * kGroupBuckets), and the
+  // multiplier that gives a row's bucket
+  uint32_t* d_group = nullptr;
+  bool grouped[BLCO_MAX_MODES] = {};
+  uint32_t group_mul[BLCO_MAX_MODES] = {};
 };
 
 namespace blco {
@@ -133,11 +140,15 @@ void finish_runs(const Layout& L, int64_t nnz, const std::vector<int64_t>& run_s
                  const std::vector<uint64_t>& run_key, int64_t max_block_nnz, blco_tensor* t,
                  bool tiles = true);
 
-// blco_mttkrp with a workspace of ws_bytes (256-byte aligned; may be empty), and the most of
-// it the call can use.  Defined in blco_device.hip.
-int mttkrp_with(blco_tensor* t, int mode, const void* const* factors, int factor_dtype, int rank,
-                float* out, void* ws, size_t ws_bytes, void* stream);
+// blco_mttkrp with a workspace of ws_bytes (256-byte aligned; may be empty) for a caller that
+// amplifies the sums' rounding, and the most workspace the call can use.  Defined in
+// blco_device.hip.
+int mttkrp_careful(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
+                   int rank, float* out, void* ws, size_t ws_bytes, void* stream);
 size_t mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype);
+
+// Bucket counts for the grouped MTTKRP, queued on `stream` (a hipStream_t).
+int make_groups(blco_tensor* t, void* stream);
 
 // Device sorting and compaction of the GPU builder (blco_sort.hip), ordered on
 // stream s (a hipStream_t, void* here so the host builder needs no HIP header).

@@ -25,7 +25,9 @@ struct KParams {
   float* out;                 // MTTKRP: I_mode x R; loss: residual (nnz)
   float* resid;               // fused residual walk: residual of each non-zero (n)
   double* partials;           // loss: one fp64 partial sum per workgroup
-  int R;
+  int R;                      // MTTKRP: elements between output rows; loss: ranks
+  int RV;                     // window kernel: ranks to flush (R, or fewer: output padding)
+  int RG;                     // window kernel: ranks to gather (RV, or more: zeros)
   int mode;
   uint32_t shift[8];
   uint32_t mask[8];
@@ -37,7 +39,7 @@ struct KParams {
   int copy_stride;            // ... floats of one copy
   uint32_t short_rows;        // hierarchical kernel: target mode length
   int short_width;            // hierarchical kernel: ranks per slice
-  uint32_t rowbytes;          // bytes of one factor row (R x element size)
+  uint32_t rowbytes;          // bytes between factor rows
   uint32_t abytes[8];         // bytes of each factor matrix (clamped to 2^32 - 1)
   float scale;                // host-side scale of every term
   const double* scale_dev;    // optional device-side scale (one double)
@@ -45,12 +47,13 @@ struct KParams {
 
 typedef void (*KernelFn)(KParams);
 
-// The window kernel for N modes, rank R: fp32 factors, bf16 factors, 64-bit gather
-// addresses (factor type fdt), and the fused CP-gradient walk.  stash: frequent rows in
-// LDS; wpt: window size (non-zeros per thread, or minus the threads per non-zero).
+// The window kernel for N modes and R ranks to gather: fp32 factors, bf16 factors, 64-bit
+// gather addresses (factor type fdt), and the fused CP-gradient walk.  even: factor rows lie
+// an even number of elements apart (vector gathers of bf16 ranks); stash: frequent rows
+// apart; wpt: window size (non-zeros per thread, or minus the threads per non-zero).
 KernelFn select_win_f32(int N, int R, bool stash, int wpt);
-KernelFn select_win_bf16(int N, int R, bool stash, int wpt);
+KernelFn select_win_bf16(int N, int R, bool even, bool stash, int wpt);
 KernelFn select_win_big(int N, int R, int fdt, bool stash, int wpt);
-KernelFn select_res(int N, int R, int fdt, bool stash, int wpt);
+KernelFn select_res(int N, int R, bool even, int fdt, bool stash, int wpt);
 
 }  // namespace blco

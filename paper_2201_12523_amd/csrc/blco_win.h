@@ -409,9 +409,9 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
   // that is all the flush needs: one 32-bit add and a shifted 64-bit add instead of two
   // quarter-rate 64-bit multiplies per flush.  With hot copies a frequent row has the top
   // bit set (kHotFlag) over the first element of its copy; with RES, which also needs the
-  // row's offset, the field holds the row and kHotFlag.  The full stash's field holds
+  // row's offset, the field holds the row (and kHotFlag).  The full stash's field holds
   // the row, or kHotFlag and its stash index.
-  constexpr bool IDX = !BIG && (!STASH || (COPIES && !RES));
+  constexpr bool IDX = !BIG && !RES && (!STASH || COPIES);
   __shared__ __align__(16) uint32_t s_rec[W * NP];  // records by grouped position
   __shared__ uint64_t s_end[W / 64];
   // the histogram (processing) and the carry partial sums (computing) are never
@@ -440,6 +440,7 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
            (uint32_t)p.copy_stride;
   };
   const int R = p.R;
+  const int RV = p.RV, RG = p.RG;
   float* s_stash = reinterpret_cast<float*>(s_dyn_win);   // K x R
   uint32_t* s_hkey = reinterpret_cast<uint32_t*>(s_stash + (size_t)K * R);
   uint32_t* s_hidx = s_hkey + kHotSlots;
@@ -601,16 +602,16 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
     // other mode counts the extra registers cost more than the LDS reads save.)
     constexpr bool kRowB = (LPN == 16) && (N == 3) && !SMALL;
     // a frequent row's segment sums into its stash row (one owner per window)
-    auto stash_add = [&](uint32_t tf, const float (&a)[RPL], const bool (&act)[RPL], int r0) {
+    auto stash_add = [&](uint32_t tf, const float (&a)[RPL], int r0) {
       float* srow = s_stash + (size_t)(tf & ~kHotFlag) * R + r0 + (PACKED ? rl * RPL : rl);
 #pragma unroll
       for (int k = 0; k < RPL; ++k)
-        if (act[k]) srow[PACKED ? k : k * LPN] += a[k];
+        if (r0 + (PACKED ? rl * RPL + k : rl + k * LPN) < RV) srow[PACKED ? k : k * LPN] += a[k];
     };
     // adds a segment of target field tf to its row
-    auto flush = [&](uint32_t tf, const float (&a)[RPL], auto full_c, int r0) {
-      constexpr bool FULL = decltype(full_c)::value;
-      const int nvalid = min(R - r0, LPN * RPL);
+    auto flush = [&](uint32_t tf, const float (&a)[RPL], auto whole_c, int r0) {
+      constexpr bool WHOLE = decltype(whole_c)::value;
+      const int nv = min(RV - r0, LPN * RPL);
       if constexpr (COPIES) {
         const bool hot = tf & kHotFlag;
         uint32_t e = tf & ~kHotFlag;
@@ -619,20 +620,19 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
         // load of the chosen parameter at every flush, behind which the gathers wait
         float* base =
             reinterpret_cast<float*>(reinterpret_cast<char*>(p.out) + (hot ? p.copy_off : 0));
-        flush_row<RPL, LPN, PACKED, FULL>(base, e + (uint32_t)r0, a, scale, rl, nvalid);
+        flush_row<RPL, LPN, PACKED, WHOLE>(base, e + (uint32_t)r0, a, scale, rl, nv);
       } else if constexpr (IDX) {
-        flush_row<RPL, LPN, PACKED, FULL>(p.out, tf + (uint32_t)r0, a, scale, rl, nvalid);
+        flush_row<RPL, LPN, PACKED, WHOLE>(p.out, tf + (uint32_t)r0, a, scale, rl, nv);
       } else {
-        flush_row<RPL, LPN, PACKED, FULL>(p.out, (size_t)tf * R + r0, a, scale, rl, nvalid);
+        flush_row<RPL, LPN, PACKED, WHOLE>(p.out, (size_t)tf * R + r0, a, scale, rl, nv);
       }
     };
-    // one slice of LPN * RPL ranks from r0 on.  FULL: every rank of the slice exists, the
-    // output rows are 64-byte aligned and the factors fp32 in 16-lane groups, or bf16:
-    // gathers take the slice's ranks by immediate offsets from one address per row, and
-    // neither gathers nor flushes mask lanes.
-    auto walk = [&](auto full_c, auto r0_c) {
-      const int r0 = r0_c;
+    // one slice of LPN * RPL ranks from r0 on.  FULL: every rank of the slice can be
+    // gathered, by immediate offsets from one address per row and without masks.  WHOLE: also
+    // every one of them is an output rank, and output rows are 64-byte aligned.
+    auto walk = [&](auto full_c, auto whole_c, auto r0_c) {
       constexpr bool FULL = decltype(full_c)::value;
+      const int r0 = r0_c;
       EndT ew = endw;
       uint32_t myrec[kRowB ? NF : 1];
       bool ract[RPL];
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
 #pragma unroll
       for (int k = 0; k < RPL; ++k) {
         const int r = PACKED ? r0 + rl * RPL + k : r0 + rl + k * LPN;
-        ract[k] = r < R;
+        ract[k] = r < RG;
         loff[k] = (uint32_t)(FULL || ract[k] ? r : 0) * (uint32_t)sizeof(FT);
         acc[k] = 0.f;
         carry[k] = 0.f;
@@ -676,10 +676,7 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
             xs[u] = xv;
             constexpr int TF = TOFF ? N + 1 : N - 1;
             uint32_t toff = kRowB ? e[TF] : er[TF];
-            if constexpr (COPIES)
-              toff = (toff & ~kHotFlag) * p.rowbytes;
-            else if constexpr (!TOFF)
-              toff *= (uint32_t)sizeof(FT);
+            if constexpr (!TOFF) toff = (toff & (COPIES ? ~kHotFlag : ~0u)) * p.rowbytes;
             wpos[u] = kRowB ? e[NF - 1] : er[NF - 1];
             if constexpr (PACKED) {
               ld_bf16_run<RPL, VEC>(rs_t, toff + loff[0], ta[u]);
@@ -756,9 +753,9 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
               const uint32_t tf = kRowB ? row_bcast(myrec[kRowB ? N - 1 : 0], u)
                                         : seg_target(s_rec, (p0 + q) * NP, p.mode, N);
               if (FULLSTASH && K > 0 && (tf & kHotFlag)) {
-                stash_add(tf, acc, ract, r0);
+                stash_add(tf, acc, r0);
               } else {
-                flush(tf, acc, full_c, r0);
+                flush(tf, acc, whole_c, r0);
               }
             } else {
 #pragma unroll
@@ -786,25 +783,30 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
         }
         const uint32_t tf = seg_target(s_rec, (p0 + PPG - 1) * NP, p.mode, N);
         if (FULLSTASH && K > 0 && (tf & kHotFlag)) {
-          stash_add(tf, carry, ract, r0);
+          stash_add(tf, carry, r0);
         } else {
-          flush(tf, carry, full_c, r0);
+          flush(tf, carry, whole_c, r0);
         }
       }
       __syncthreads();
     };
-    const bool full_rows = R % 16 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 63) == 0;
+    using Yes = std::true_type;
+    using No = std::false_type;
     if constexpr (LPN == 16) {
-      // one slice (R <= 16 RPL): its first rank folds to 0
+      // one slice (RG <= 16 RPL): its first rank folds to 0
       using Zero = std::integral_constant<int, 0>;
-      bool full = false;
       if constexpr (!BIG && !FULLSTASH) {
-        full = full_rows && R == 16 * RPL;
-        if (full) walk(std::true_type{}, Zero{});
+        if (RG != 16 * RPL)
+          walk(No{}, No{}, Zero{});
+        else if (RV == RG && R % 16 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 63) == 0)
+          walk(Yes{}, Yes{}, Zero{});
+        else
+          walk(Yes{}, No{}, Zero{});
+      } else {
+        walk(No{}, No{}, Zero{});
       }
-      if (!full) walk(std::false_type{}, Zero{});
     } else {
-      for (int r0 = 0; r0 < R; r0 += LPN * RPL) walk(std::false_type{}, r0);
+      for (int r0 = 0; r0 < R; r0 += LPN * RPL) walk(No{}, No{}, r0);
     }
     if constexpr (!FULLSTASH) break;
   }
@@ -877,11 +879,12 @@ static KernelFn pick_win16(int N, bool stash, int wpt) {
 // the power-law workloads: R <= 16: 16 x 1; R <= 32: 16 x 2 (8 x 4 was 1.8x slower);
 // fp32 up to 48 without a stash: 16 x 3; R <= 64: 16 x 4 (10% faster than 32 x 2);
 // larger: 64 x 2 per pass over the rank.  A stash with wpt 1 is the full one.  VEC (vector gathers of packed bf16 ranks) only
-// where the ranks are packed: bf16 factors, two or more ranks per lane, and an even R.
+// where the ranks are packed: bf16 factors, two or more ranks per lane, and rows an even
+// number of elements apart.
 template <typename FT, bool BIG>
-static KernelFn select_win_t(int N, int R, bool stash, int wpt) {
+static KernelFn select_win_t(int N, int R, bool even, bool stash, int wpt) {
   constexpr bool H = sizeof(FT) == 2;
-  const bool vec = H && R % 2 == 0;
+  const bool vec = H && even;
   if (R <= 16) return pick_win16<1, FT, BIG, false>(N, stash, wpt);
   if (R <= 32)
     return vec ? pick_win16<2, FT, BIG, H>(N, stash, wpt) : pick_win16<2, FT, BIG, false>(N, stash, wpt);
@@ -909,9 +912,9 @@ static KernelFn pick_res(int N, bool stash, int wpt) {
 }
 
 template <typename FT>
-static KernelFn select_res_t(int N, int R, bool stash, int wpt) {
+static KernelFn select_res_t(int N, int R, bool even, bool stash, int wpt) {
   constexpr bool H = sizeof(FT) == 2;
-  const bool vec = H && R % 2 == 0;
+  const bool vec = H && even;
   if (R <= 16) return pick_res<1, FT, false>(N, stash, wpt);
   if (R <= 32) return vec ? pick_res<2, FT, H>(N, stash, wpt) : pick_res<2, FT, false>(N, stash, wpt);
   return vec ? pick_res<4, FT, H>(N, stash, wpt) : pick_res<4, FT, false>(N, stash, wpt);

@@ -2,5 +2,5 @@
 #include "blco_win.h"
 
 KernelFn blco::select_win_f32(int N, int R, bool stash, int wpt) {
-  return select_win_t<float, false>(N, R, stash, wpt);
+  return select_win_t<float, false>(N, R, false, stash, wpt);
 }
