@@ -2186,7 +2186,7 @@ extern "C" int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int*
     return set_error(BLCO_EINVAL, "mode %d outside 0..%d", mode, t->lay.N - 1);
   if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
   const WinPlan w = plan_win(t, mode, rank, rank, rank, rank % 2 == 0, BLCO_F32, false, false,
-                             std::max<int64_t>(t->nnz, 1), 0, false);
+                             std::max<int64_t>(t->nnz, 1), 0, false, false);
   *rows = w.stash;
   return BLCO_OK;
 }
