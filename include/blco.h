@@ -328,6 +328,10 @@ int blco_cp_grad_noalloc(blco_tensor* t, const void* const* factors, int factor_
  */
 int blco_scale(float* x, int64_t n, const double* scale, double alpha, void* stream);
 
+/* blco_scale of `count` arrays (0..BLCO_MAX_MODES) in one launch: x[i] of n[i] elements. */
+int blco_scale_all(int count, float* const* x, const int64_t* n, const double* scale,
+                   double alpha, void* stream);
+
 /*
  * Choose the conflict-resolution mechanism of every later MTTKRP call on t
  * (blco_mttkrp*, blco_mttkrp_stream*, the CP gradient), Sections 5.1-5.3:
@@ -386,6 +390,10 @@ int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int* rows);
 
 /* dst[i] = bf16(src[i]), round to nearest even (NaN stays NaN); device arrays. */
 int blco_cast_bf16(const float* src, uint16_t* dst, int64_t n, void* stream);
+
+/* blco_cast_bf16 of `count` arrays (0..BLCO_MAX_MODES) in one launch. */
+int blco_cast_bf16_all(int count, const float* const* src, uint16_t* const* dst, const int64_t* n,
+                       void* stream);
 
 /*
  * Gram matrix G = A^T A of a factor matrix (the factors of V in Algorithm 1):

@@ -34,6 +34,7 @@ EXPORTED = ["blco_build", "blco_mttkrp", "blco_mttkrp_acc", "blco_mttkrp_v", "bl
             "blco_mttkrp_stream_all", "blco_mttkrp_ws", "blco_mttkrp_stream_all_ws",
             "blco_cp_grad_ws", "blco_workspace", "blco_build_device_in", "blco_build_device_sizes",
             "blco_sampled_loss", "blco_cp_grad", "blco_cp_grad_noalloc", "blco_scale", "blco_cast_bf16", "blco_set_resolution", "blco_resolution",
+            "blco_scale_all", "blco_cast_bf16_all",
             "blco_gram", "blco_cp_als", "blco_build_device",
             "blco_atomic_probe", "blco_gather_probe", "blco_frequent_rows", "blco_info", "blco_export", "blco_free",
             "blco_last_error"]
@@ -99,6 +100,8 @@ def lib():
         L.blco_workspace.argtypes = [p, i32, i32, i32, ctypes.POINTER(sz)]
         L.blco_sampled_loss.argtypes = [p, p, i32, i32, p, p, p]
         L.blco_cast_bf16.argtypes = [p, p, i64, p]
+        L.blco_cast_bf16_all.argtypes = [i32, p, p, p, p]
+        L.blco_scale_all.argtypes = [i32, p, p, p, ctypes.c_double, p]
         L.blco_cp_grad.argtypes = [p, p, i32, i32, p, ctypes.c_double, p, p, p, ctypes.c_size_t,
                                    p]
         L.blco_cp_grad_noalloc.argtypes = [p, p, i32, i32, p, ctypes.c_double, p, p, p, p]
@@ -167,10 +170,18 @@ class BLCOTensor:
         self.dims = tuple(int(d) for d in dims)
         self._storage = storage               # torch memory that holds the tensor's arrays
         self._storage_stream = storage_stream
+        self._fixed = None                    # (nnz, placement): they never change
+        self._need = {}                       # workspace bytes by (mode, rank, dtype)
 
     @property
     def handle(self):
         return self._h
+
+    def _facts(self):
+        if self._fixed is None or self._h is None:
+            inf = self.info()
+            self._fixed = inf["nnz"], inf["placement"]
+        return self._fixed
 
     def info(self) -> dict:
         inf = _Info()
@@ -190,7 +201,7 @@ class BLCOTensor:
 
     @property
     def nnz(self) -> int:
-        return self.info()["nnz"]
+        return self._facts()[0]
 
     @property
     def nmodes(self) -> int:
@@ -202,6 +213,7 @@ class BLCOTensor:
         if resolution not in RESOLUTIONS:
             raise ValueError(f"resolution {resolution!r}: one of {sorted(RESOLUTIONS)}")
         _check(lib().blco_set_resolution(self._h, RESOLUTIONS[resolution]))
+        self._need = {}
 
     def resolution(self, mode: int, rank: int) -> str:
         """The mechanism a mode-`mode` MTTKRP at rank `rank` uses on the current device."""
@@ -319,25 +331,30 @@ def build_device(coords, values, dims, key_bits=64, max_block_nnz=1 << 27, place
     return BLCOTensor(h.value, dims, storage, sh)
 
 
+_DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _factor_args(t, factors, mode_skip):
     dt = None
     R = None
     ptrs = []
     keep = []
+    dims = t.dims
     for m, f in enumerate(factors):
-        if f is None or (mode_skip is not None and m == mode_skip and f is None):
+        if f is None:
             ptrs.append(None)
             continue
-        if not f.is_cuda or not f.is_contiguous() or f.dim() != 2:
+        shape = f.shape
+        if not f.is_cuda or not f.is_contiguous() or len(shape) != 2:
             raise ValueError(f"factor {m} must be a contiguous 2-D device tensor")
-        if f.shape[0] != t.dims[m]:
-            raise ValueError(f"factor {m} has {f.shape[0]} rows, mode length is {t.dims[m]}")
-        fd = {torch.float32: F32, torch.bfloat16: BF16}.get(f.dtype)
+        if shape[0] != dims[m]:
+            raise ValueError(f"factor {m} has {shape[0]} rows, mode length is {dims[m]}")
+        fd = _DTYPES.get(f.dtype)
         if fd is None:
             raise ValueError("factors must be float32 or bfloat16")
         if dt is None:
-            dt, R = fd, int(f.shape[1])
-        elif fd != dt or int(f.shape[1]) != R:
+            dt, R = fd, int(shape[1])
+        elif fd != dt or shape[1] != R:
             raise ValueError("all factors must share dtype and rank")
         ptrs.append(f.data_ptr())
         keep.append(f)
@@ -358,17 +375,23 @@ def _out(t, mode, R, out, device):
 def _workspace(t, mode, R, dt, device, stream):
     """(tensor or None, pointer, bytes): the workspace a call of `mode` (-1: all) can use, from
     torch's allocator in the stream's order; none where memory is short."""
-    need = ctypes.c_size_t()
-    _check(lib().blco_workspace(t.handle, mode, R, dt, ctypes.byref(need)))
-    if need.value == 0:
+    bytes_ = t._need.get((mode, R, dt)) if t._h is not None else None
+    if bytes_ is None:
+        need = ctypes.c_size_t()
+        _check(lib().blco_workspace(t.handle, mode, R, dt, ctypes.byref(need)))
+        bytes_ = t._need[(mode, R, dt)] = need.value
+    if bytes_ == 0:
         return None, None, 0
     try:
         # from the pool of the stream the call runs on: blocks there are reused in its order
-        with torch.cuda.stream(stream):
-            ws = torch.empty(need.value, dtype=torch.uint8, device=device)
+        if stream is None:
+            ws = torch.empty(bytes_, dtype=torch.uint8, device=device)
+        else:
+            with torch.cuda.stream(stream):
+                ws = torch.empty(bytes_, dtype=torch.uint8, device=device)
     except torch.cuda.OutOfMemoryError:
         return None, None, 0
-    return ws, ws.data_ptr(), need.value
+    return ws, ws.data_ptr(), bytes_
 
 
 def _device_of(factors):
@@ -477,7 +500,7 @@ def cp_grad(t, factors, grads=None, residual=None, loss=None, scale=None, alpha=
     if grads is None:
         grads = [None] * N
     grads = [_out(t, m, R, grads[m], dev) for m in range(N)]
-    pinned = t.info()["placement"] == PLACEMENTS["pinned"]
+    pinned = t._facts()[1] == PLACEMENTS["pinned"]
     if not pinned and residual is None:
         residual = torch.empty(max(t.nnz, 1), dtype=torch.float32, device=dev)
     if loss is None:
@@ -522,6 +545,29 @@ def scale_(x, scale, alpha=1.0, stream=None):
     _check(lib().blco_scale(x.data_ptr(), x.numel(), scale.data_ptr(), float(alpha),
                             _stream(stream)))
     return x
+
+
+def _arrays(xs):
+    """Pointers and lengths of tensors, as the calls over several arrays take them."""
+    return ((ctypes.c_void_p * len(xs))(*[x.data_ptr() for x in xs]),
+            (ctypes.c_int64 * len(xs))(*[x.numel() for x in xs]))
+
+
+def _scale_all(xs, scale):
+    """scale_ of every tensor of a list, in one launch."""
+    ptrs, n = _arrays(xs)
+    _check(lib().blco_scale_all(len(xs), ptrs, n, scale.data_ptr(), 1.0, _stream()))
+
+
+def _cast_all(xs):
+    """cast_bf16 of every tensor of a list, in one launch."""
+    for x in xs:
+        if x.dtype != torch.float32:
+            raise ValueError("x must be contiguous float32")
+    ys = [torch.empty(x.shape, dtype=torch.bfloat16, device=x.device) for x in xs]
+    src, n = _arrays(xs)
+    _check(lib().blco_cast_bf16_all(len(xs), src, _arrays(ys)[0], n, _stream()))
+    return ys
 
 
 def cast_bf16(x, stream=None):
@@ -614,12 +660,12 @@ class CPLoss(torch.autograd.Function):
     @staticmethod
     def forward(ctx, t, storage, *A):
         if storage == "bf16":
-            F = [cast_bf16(a.contiguous()) for a in A]
+            F = _cast_all([a.contiguous() for a in A])
         elif storage == "fp32":
             F = [a.contiguous() for a in A]
         else:
             raise ValueError("storage must be 'fp32' or 'bf16'")
-        pinned = t.info()["placement"] == PLACEMENTS["pinned"]
+        pinned = t._facts()[1] == PLACEMENTS["pinned"]
         if any(ctx.needs_input_grad[2:]) or pinned:
             loss, grads, _ = cp_grad(t, F, device_budget=CPLoss.device_budget)
             ctx.grads = grads
@@ -636,6 +682,5 @@ class CPLoss(torch.autograd.Function):
         g = g.contiguous()
         grads = ctx.grads
         ctx.grads = None
-        for x in grads:
-            scale_(x, g)
+        _scale_all(grads, g)
         return (None, None, *grads)
