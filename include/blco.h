@@ -383,8 +383,9 @@ int blco_gather_probe(const float* table, int64_t nrows, int rank, const uint32_
                       int64_t n, float* sink, void* stream);
 
 /* Rows of mode `mode` whose segment sums a register-based MTTKRP at rank
-   `rank` on the current device adds into its LDS stash of frequent rows (found
-   at build time) instead of the output, in *rows (0: none).  For inspection.
+   `rank` without a workspace on the current device adds into its LDS stash of
+   frequent rows (found at build time) instead of the output, in *rows (0: none).
+   For inspection.
    Errors: EINVAL. */
 int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int* rows);
 
@@ -441,6 +442,16 @@ typedef struct {
  */
 int blco_cp_als(blco_tensor* t, float* const* factors, int rank, const blco_cpals_opts* opts,
                 double* fits, blco_cpals_report* report, void* stream);
+
+/*
+ * blco_cp_als in device memory of the caller: ws_bytes at `workspace` (256-byte aligned), as
+ * many as blco_cp_als_size gives for the rank and factor type.  With fewer, or NULL, the call
+ * allocates its own.  The call waits for its work, so the memory is free when it returns.
+ */
+int blco_cp_als_in(blco_tensor* t, float* const* factors, int rank, const blco_cpals_opts* opts,
+                   double* fits, blco_cpals_report* report, void* workspace, size_t ws_bytes,
+                   void* stream);
+int blco_cp_als_size(const blco_tensor* t, int rank, int factor_dtype, size_t* bytes);
 
 /* Layout, sizes and last streaming call statistics of a tensor (waits for the
    last streaming call to finish when it has not been measured yet). */

@@ -34,7 +34,7 @@ EXPORTED = ["blco_build", "blco_mttkrp", "blco_mttkrp_acc", "blco_mttkrp_v", "bl
             "blco_mttkrp_stream_all", "blco_mttkrp_ws", "blco_mttkrp_stream_all_ws",
             "blco_cp_grad_ws", "blco_workspace", "blco_build_device_in", "blco_build_device_sizes",
             "blco_sampled_loss", "blco_cp_grad", "blco_cp_grad_noalloc", "blco_scale", "blco_cast_bf16", "blco_set_resolution", "blco_resolution",
-            "blco_scale_all", "blco_cast_bf16_all",
+            "blco_scale_all", "blco_cast_bf16_all", "blco_cp_als_in", "blco_cp_als_size",
             "blco_gram", "blco_cp_als", "blco_build_device",
             "blco_atomic_probe", "blco_gather_probe", "blco_frequent_rows", "blco_info", "blco_export", "blco_free",
             "blco_last_error"]
@@ -116,6 +116,8 @@ def lib():
         L.blco_build_device_sizes.argtypes = [i32, p, i64, ctypes.POINTER(_Opts),
                                               ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.blco_gram.argtypes = [p, i32, i64, i32, p, p]
+        L.blco_cp_als_in.argtypes = [p, p, i32, p, p, p, p, sz, p]
+        L.blco_cp_als_size.argtypes = [p, i32, i32, ctypes.POINTER(sz)]
         L.blco_cp_als.argtypes = [p, p, i32, ctypes.POINTER(_CPALSOpts), p,
                                   ctypes.POINTER(_CPALSReport), p]
         L.blco_resolution.argtypes = [p, i32, i32, ctypes.POINTER(ctypes.c_int)]
@@ -637,8 +639,19 @@ def cp_als(t, factors, max_iters=25, tol=1e-5, storage="fp32", stream=None):
     fits = np.zeros(int(max_iters), dtype=np.float64)
     rep = _CPALSReport()
     sh = _stream(stream, t)
-    _check(_with_memory(lambda: lib().blco_cp_als(t.handle, arr, R, ctypes.byref(opts),
-                                                  fits.ctypes.data, ctypes.byref(rep), sh)))
+    need, ws = ctypes.c_size_t(), None
+    if lib().blco_cp_als_size(t.handle, R, opts.factor_dtype, ctypes.byref(need)) == 0:
+        # from the pool of the stream the call runs on; the call itself says what is wrong
+        # with its arguments, and allocates where this cannot
+        try:
+            with torch.cuda.stream(stream):
+                ws = torch.empty(need.value, dtype=torch.uint8, device=factors[0].device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    wp, wb = (None, 0) if ws is None else (ws.data_ptr(), need.value)
+    _check(_with_memory(lambda: lib().blco_cp_als_in(t.handle, arr, R, ctypes.byref(opts),
+                                                     fits.ctypes.data, ctypes.byref(rep), wp, wb,
+                                                     sh)))
     return fits[:rep.iters].tolist(), {"iters": rep.iters, "pinv_fallbacks": rep.pinv_fallbacks}
 
 

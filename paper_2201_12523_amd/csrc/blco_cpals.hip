@@ -52,10 +52,6 @@ __global__ void k_zero_f64(double* p, int n) {
     p[i] = 0.0;
 }
 
-__global__ void k_zero_i32(int* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
-}
-
 // G += A^T A over this workgroup's rows: products in fp32 over kGramRows rows
 // at a time, sums in fp64; one fp64 atomic per entry per workgroup.
 template <typename FT>
@@ -198,16 +194,25 @@ __device__ bool gauss_jordan(double* a, int R, double tol, double* row, double* 
 // Otherwise: rank-revealing pivoted Cholesky P^T V P = L L^T (L: R x k, full
 // column rank), and V^+ = P L (L^T L)^-2 L^T P^T, with the matrices in `scratch`
 // (3 R x R).  `fallbacks` counts the calls that took the second route.
-__global__ __launch_bounds__(kSolveThreads) void k_pinv_v(const double* __restrict__ grams, int N,
+// Also clears the Gram of mode n, which V does not hold and the update that follows sums
+// anew, and *clear: a launch of 2 us each on their own.
+//
+// Bound by the R dependent elimination steps, each two barriers and an fp64 division long.  One
+// thread per entry: four entries each divide in turn (a whole run of three iterations over
+// three modes at R = 16: 585 us and 532 us), threads without one wait at the barriers.
+__global__ __launch_bounds__(kSolveThreads) void k_pinv_v(double* __restrict__ grams, int N,
                                                           int n, int R, double* __restrict__ vinv,
                                                           double* __restrict__ scratch,
-                                                          int* __restrict__ fallbacks) {
+                                                          int* __restrict__ fallbacks,
+                                                          double* __restrict__ clear) {
   __shared__ double s_a[kMaxRank * kMaxRank];
   __shared__ double s_row[kMaxRank], s_col[kMaxRank];
   __shared__ int s_perm[kMaxRank];
   __shared__ double s_tol;
   __shared__ int s_piv, s_rank;
   const int tid = threadIdx.x;
+  for (int e = tid; e < R * R; e += blockDim.x) grams[(size_t)n * R * R + e] = 0.0;
+  if (tid == 0) *clear = 0.0;
   hadamard(grams, N, n, R, s_a);
   __syncthreads();
   if (tid == 0) {
@@ -344,9 +349,11 @@ __global__ void k_fit(const double* __restrict__ grams, int N, int R, double* __
   }
 }
 
-int launch_gram(const void* A, int dtype, int64_t rows, int R, double* G, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(256), 0, s, G, R * R);
-  HIPCHK(hipGetLastError());
+// Threads of k_pinv_v's one workgroup: an entry of V each, where there are as many.
+int solve_threads(int R) { return std::min(kSolveThreads, (R * R + 63) / 64 * 64); }
+
+// G += A^T A
+int add_gram(const void* A, int dtype, int64_t rows, int R, double* G, hipStream_t s) {
   if (rows <= 0) return BLCO_OK;
   if (R <= 32) {
     // matrix cores: about 2048 waves, each over at least one flush block of rows
@@ -376,6 +383,12 @@ int launch_gram(const void* A, int dtype, int64_t rows, int R, double* G, hipStr
   return BLCO_OK;
 }
 
+int launch_gram(const void* A, int dtype, int64_t rows, int R, double* G, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(256), 0, s, G, R * R);
+  HIPCHK(hipGetLastError());
+  return add_gram(A, dtype, rows, R, G, s);
+}
+
 int launch_dot(const float* x, const float* y, int64_t n, double* out, hipStream_t s) {
   if (n <= 0) return BLCO_OK;
   const int64_t blocks = std::min<int64_t>((n + 255) / 256, 2048);
@@ -383,6 +396,34 @@ int launch_dot(const float* x, const float* y, int64_t n, double* out, hipStream
   HIPCHK(hipGetLastError());
   return BLCO_OK;
 }
+
+// Where CP-ALS keeps M, the Grams, V^+, the pseudo-inverse's scratch, the scalars and the
+// counter, bf16 copies of the factors and the MTTKRPs' workspace: byte offsets.
+struct AlsMemory {
+  size_t grams, vinv, scratch, scalars, half, half_bytes, work, work_bytes = 0, total = 0;
+  AlsMemory(const blco_tensor* t, int R, int dtype) {
+    uint64_t most = 0, sum = 0;
+    for (int m = 0; m < t->lay.N; ++m) {
+      most = std::max<uint64_t>(most, t->lay.dims[m]);
+      sum += t->lay.dims[m];
+      work_bytes = std::max(work_bytes, blco::mttkrp_workspace(t, m, R, dtype));
+    }
+    half_bytes = dtype == BLCO_BF16 ? (size_t)sum * R * sizeof(uint16_t) : 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = total;
+      total += (bytes + 255) / 256 * 256;
+      return at;
+    };
+    const size_t square = (size_t)R * R * sizeof(double);
+    take((size_t)most * R * sizeof(float));
+    grams = take(t->lay.N * square);
+    vinv = take(square);
+    scratch = take(3 * square);
+    scalars = take(5 * sizeof(double));
+    half = take(half_bytes);
+    work = take(work_bytes);
+  }
+};
 
 struct DevBuf {
   void* p = nullptr;
@@ -405,9 +446,27 @@ extern "C" int blco_gram(const void* A, int dtype, int64_t rows, int rank, doubl
   return launch_gram(A, dtype, rows, rank, G, static_cast<hipStream_t>(stream));
 }
 
+extern "C" int blco_cp_als_size(const blco_tensor* t, int rank, int factor_dtype, size_t* bytes) {
+  clear_error();
+  if (!t || !bytes) return set_error(BLCO_EINVAL, "tensor or bytes is NULL");
+  if (rank < 1 || rank > kMaxRank)
+    return set_error(BLCO_EINVAL, "rank %d outside 1..%d", rank, kMaxRank);
+  if (factor_dtype != BLCO_F32 && factor_dtype != BLCO_BF16)
+    return set_error(BLCO_EINVAL, "factor dtype %d", factor_dtype);
+  *bytes = AlsMemory(t, rank, factor_dtype).total;
+  return BLCO_OK;
+}
+
 extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
                            const blco_cpals_opts* opts, double* fits, blco_cpals_report* report,
                            void* stream) {
+  return blco_cp_als_in(t, factors, rank, opts, fits, report, nullptr, 0, stream);
+}
+
+extern "C" int blco_cp_als_in(blco_tensor* t, float* const* factors, int rank,
+                              const blco_cpals_opts* opts, double* fits,
+                              blco_cpals_report* report, void* ws, size_t ws_bytes,
+                              void* stream) {
   clear_error();
   if (!t) return set_error(BLCO_EINVAL, "tensor is NULL");
   if (t->placement != BLCO_PLACE_DEVICE)
@@ -427,40 +486,23 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
   if (t->nnz == 0) return set_error(BLCO_EINVAL, "the tensor has no non-zeros");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int R = rank;
-  uint64_t maxI = 0, sumI = 0;
-  for (int m = 0; m < N; ++m) {
-    maxI = std::max<uint64_t>(maxI, t->lay.dims[m]);
-    sumI += t->lay.dims[m];
+  if (ws && (reinterpret_cast<uintptr_t>(ws) & 255))
+    return set_error(BLCO_EINVAL, "workspace is not 256-byte aligned");
+  const AlsMemory mem(t, R, o.factor_dtype);
+  DevBuf own;
+  if (!ws || ws_bytes < mem.total) {
+    HIPCHK(hipMalloc(&own.p, mem.total));
+    ws = own.p;
   }
-  // workspace: M, Grams, V^+, pseudo-inverse scratch, scalars, counter, bf16 copies
-  const size_t bytes_M = (size_t)maxI * R * sizeof(float);
-  const size_t bytes_G = (size_t)N * R * R * sizeof(double);
-  const size_t bytes_V = (size_t)R * R * sizeof(double);
-  const size_t bytes_S = 3 * bytes_V;
-  const size_t bytes_sc = 4 * sizeof(double) + sizeof(int) * 2;
-  size_t bytes_w = 0;   // the MTTKRPs' workspace
-  for (int m = 0; m < N; ++m)
-    bytes_w = std::max(bytes_w, blco::mttkrp_workspace(t, m, R, o.factor_dtype));
-  const size_t bytes_h = o.factor_dtype == BLCO_BF16 ? (size_t)sumI * R * sizeof(uint16_t) : 0;
-  auto align = [](size_t b) { return (b + 255) / 256 * 256; };
-  const size_t total = align(bytes_M) + align(bytes_G) + align(bytes_V) + align(bytes_S) +
-                       align(bytes_sc) + align(bytes_h) + align(bytes_w);
-  DevBuf ws;
-  HIPCHK(hipMalloc(&ws.p, total));
-  char* base = static_cast<char*>(ws.p);
+  char* base = static_cast<char*>(ws);
   float* dM = reinterpret_cast<float*>(base);
-  base += align(bytes_M);
-  double* dG = reinterpret_cast<double*>(base);
-  base += align(bytes_G);
-  double* dV = reinterpret_cast<double*>(base);
-  base += align(bytes_V);
-  double* dS = reinterpret_cast<double*>(base);
-  base += align(bytes_S);
-  double* dsc = reinterpret_cast<double*>(base);
+  double* dG = reinterpret_cast<double*>(base + mem.grams);
+  double* dV = reinterpret_cast<double*>(base + mem.vinv);
+  double* dS = reinterpret_cast<double*>(base + mem.scratch);
+  double* dsc = reinterpret_cast<double*>(base + mem.scalars);
   int* dfb = reinterpret_cast<int*>(dsc + 4);
-  base += align(bytes_sc);
-  uint16_t* dh = bytes_h ? reinterpret_cast<uint16_t*>(base) : nullptr;
-  char* dw = bytes_w ? base + align(bytes_h) : nullptr;
+  uint16_t* dh = mem.half_bytes ? reinterpret_cast<uint16_t*>(base + mem.half) : nullptr;
+  char* dw = mem.work_bytes ? base + mem.work : nullptr;
   std::vector<const void*> mt(N);
   std::vector<uint16_t*> half(N, nullptr);
   {
@@ -476,14 +518,14 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
   const int mdt = o.factor_dtype;
   int rc;
   // ||X||^2, the Grams, the bf16 copies
-  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(64), 0, s, dsc, 4);
+  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(64), 0, s, dsc, 5);   // the counter with them
   HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, dfb, 2);
+  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(1024), 0, s, dG, N * R * R);
   HIPCHK(hipGetLastError());
   if ((rc = launch_dot(t->d_vals, t->d_vals, t->nnz, dsc, s)) != BLCO_OK) return rc;
   for (int m = 0; m < N; ++m) {
-    if ((rc = launch_gram(factors[m], BLCO_F32, (int64_t)t->lay.dims[m], R,
-                          dG + (size_t)m * R * R, s)) != BLCO_OK)
+    if ((rc = add_gram(factors[m], BLCO_F32, (int64_t)t->lay.dims[m], R, dG + (size_t)m * R * R,
+                       s)) != BLCO_OK)
       return rc;
     if (dh && (rc = blco_cast_bf16(factors[m], half[m], (int64_t)t->lay.dims[m] * R, s)) != BLCO_OK)
       return rc;
@@ -493,21 +535,22 @@ extern "C" int blco_cp_als(blco_tensor* t, float* const* factors, int rank,
   for (; it < o.max_iters; ++it) {
     for (int n = 0; n < N; ++n) {
       const int64_t In = (int64_t)t->lay.dims[n];
-      hipLaunchKernelGGL(k_pinv_v, dim3(1), dim3(kSolveThreads), 0, s, dG, N, n, R, dV, dS, dfb);
+      hipLaunchKernelGGL(k_pinv_v, dim3(1), dim3(solve_threads(R)), 0, s, dG, N, n, R, dV, dS, dfb,
+                         dsc + 1);
       HIPCHK(hipGetLastError());
-      if ((rc = blco::mttkrp_careful(t, n, mt.data(), mdt, R, dM, dw, bytes_w, s)) != BLCO_OK) return rc;
+      if ((rc = blco::mttkrp_careful(t, n, mt.data(), mdt, R, dM, dw,
+                                     mem.work_bytes, s)) != BLCO_OK)
+        return rc;
       const int per = 256 / R;
       const int64_t blocks = std::min<int64_t>((In + per - 1) / per, 4096);
       hipLaunchKernelGGL(k_apply_vinv, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(256), 0,
                          s, dM, In, R, dV, factors[n]);
       HIPCHK(hipGetLastError());
-      if ((rc = launch_gram(factors[n], BLCO_F32, In, R, dG + (size_t)n * R * R, s)) != BLCO_OK)
+      if ((rc = add_gram(factors[n], BLCO_F32, In, R, dG + (size_t)n * R * R, s)) != BLCO_OK)
         return rc;
       if (dh && (rc = blco_cast_bf16(factors[n], half[n], In * R, s)) != BLCO_OK) return rc;
     }
     // <X, Xhat> from the last mode's MTTKRP (still in dM) and its new factor
-    hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(64), 0, s, dsc + 1, 1);
-    HIPCHK(hipGetLastError());
     const int64_t Il = (int64_t)t->lay.dims[N - 1];
     if ((rc = launch_dot(dM, factors[N - 1], Il * R, dsc + 1, s)) != BLCO_OK) return rc;
     hipLaunchKernelGGL(k_fit, dim3(1), dim3(1024), 0, s, dG, N, R, dsc);

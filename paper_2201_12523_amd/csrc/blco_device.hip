@@ -5,9 +5,9 @@
 // computing split of Section 5.1 (Figure 7), re-designed for wave64 and the
 // memory-side atomics of MI355X:
 //   k_mttkrp_win (register-based resolution, Section 5.2): one 1024-thread
-//     workgroup per window of 1024 consecutive non-zeros (2048 or 4096 on modes
-//     without frequent rows).  Processing: each thread loads one, two or four
-//     (key, value) pairs (coalesced), decodes the coordinates
+//     workgroup per window of 256 to 4096 consecutive non-zeros (blco_win.h,
+//     win_wpt).  Processing: each thread loads up to four (key, value) pairs
+//     (coalesced), decodes the coordinates
 //     by shift and mask (Figure 6b), and the window is grouped by target row
 //     with a counting sort on a hash of the target (LDS histogram, workgroup
 //     scan, scatter), so each target forms one segment; every grouped position
@@ -16,8 +16,10 @@
 //     gather the factor rows with raw buffer loads, sum the scaled Hadamard
 //     products in registers while the target repeats, and add each finished
 //     segment to the output with one atomic per rank.  A mode's frequent rows
-//     (found at build time) are summed in an LDS stash instead and flushed
-//     once per persistent workgroup.
+//     (found at build time) go to copies in the call's workspace instead, or,
+//     without one, to an LDS stash flushed once per persistent workgroup.
+//     The workspace also holds padded factors and output rows, and the
+//     non-zeros of a flat mode moved to buckets of target rows (plan_call).
 //   k_mttkrp_short (hierarchical resolution, Section 5.1), which the Section
 //     5.3 heuristic picks for modes shorter than the compute-unit count: each
 //     workgroup keeps a private LDS copy of all target rows (a rank slice) and
