@@ -144,3 +144,25 @@ def test_streams_and_graphs():
         graph.replay()
         torch.cuda.synchronize()
         assert float(((out - want).abs() - 2.1e-5 * S).max()) <= 0, k
+
+
+# added to an output, and into one that starts between 16-byte units
+@pytest.mark.parametrize("R", [10, 16, 35, 97])
+def test_added_and_misaligned_outputs(R):
+    dims = (3000, 2000, 900)
+    coords, vals, g, t = tensors(dims, (1 << 18) + 3, R)
+    F = [torch.randn(d, R, generator=g, device=DEV) for d in dims]
+    for m, d in enumerate(dims):
+        want = plain(t, m, F)
+        S = plain(t, m, [f.abs() for f in F], values=vals.abs().max().expand(vals.numel()).contiguous())
+        first = torch.randn(d, R, generator=g, device=DEV)
+        # one rounding of the sum either way
+        eps = 2.0 ** -23 * (first.abs() + S)
+        got = blco.mttkrp_acc(t, m, F, first.clone())
+        assert float(((got - (first + want)).abs() - 2.1e-5 * S - eps).max()) <= 0
+        for off in (1, 3):
+            buf = torch.full((d * R + 8,), 7.0, device=DEV)
+            out = buf[off:off + d * R].view(d, R)
+            blco.mttkrp(t, m, F, out=out)
+            assert float(((out - want).abs() - 2.1e-5 * S).max()) <= 0
+            assert bool((buf[:off] == 7).all()) and bool((buf[off + d * R:] == 7).all())
