@@ -389,6 +389,33 @@ int blco_gather_probe(const float* table, int64_t nrows, int rank, const uint32_
    Errors: EINVAL. */
 int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int* rows);
 
+/* How a launch of mode `mode` at rank `rank` runs (inspection: nothing is launched, and a tensor
+   of any placement will do).  use: the call it belongs to; nnz: the non-zeros of the launch (0:
+   the tensor's); workspace_bytes: what it is lent.  Errors: EINVAL, EUNSUPPORTED (the fused
+   walk does not take this mode, or HIERARCHICAL is forced on a mode too long). */
+#define BLCO_USE_MTTKRP 0   /* an MTTKRP call, or an unfused mode of the CP gradient */
+#define BLCO_USE_RESIDUAL 1 /* the CP gradient's fused residual walk */
+#define BLCO_USE_ALS 2      /* a CP-ALS update */
+typedef struct {
+  int resolution;          /* BLCO_RES_REGISTER or BLCO_RES_HIERARCHICAL */
+  int lanes;               /* lanes per non-zero */
+  int ranks_per_lane;
+  int window;              /* non-zeros per window, or per batch of the hierarchical kernel */
+  int wpt;                 /* the window as the kernel's template argument has it: non-zeros per
+                              thread, or minus the threads per non-zero */
+  int stash_rows;          /* frequent rows in the full LDS stash */
+  int copies;              /* copies of each frequent row in the workspace */
+  int wide;                /* 64-bit gather addresses and output indices */
+  int vector_gathers;      /* bf16 rows an even number of elements apart */
+  int factor_stride;       /* elements between factor rows: the rank, or more where padded */
+  int out_stride;          /* elements between output rows: the rank, or more where padded */
+  int grouped;             /* non-zeros moved to buckets of target rows first */
+  int64_t workgroups;      /* of the window kernel */
+  size_t workspace_bytes;  /* used of what it is lent */
+} blco_plan_t;
+int blco_plan(const blco_tensor* t, int mode, int rank, int factor_dtype, int use, int64_t nnz,
+              size_t workspace_bytes, blco_plan_t* plan);
+
 /* dst[i] = bf16(src[i]), round to nearest even (NaN stays NaN); device arrays. */
 int blco_cast_bf16(const float* src, uint16_t* dst, int64_t n, void* stream);
 

@@ -34,7 +34,7 @@ EXPORTED = ["blco_build", "blco_mttkrp", "blco_mttkrp_acc", "blco_mttkrp_v", "bl
             "blco_mttkrp_stream_all", "blco_mttkrp_ws", "blco_mttkrp_stream_all_ws",
             "blco_cp_grad_ws", "blco_workspace", "blco_build_device_in", "blco_build_device_sizes",
             "blco_sampled_loss", "blco_cp_grad", "blco_cp_grad_noalloc", "blco_scale", "blco_cast_bf16", "blco_set_resolution", "blco_resolution",
-            "blco_scale_all", "blco_cast_bf16_all", "blco_cp_als_in", "blco_cp_als_size",
+            "blco_plan", "blco_scale_all", "blco_cast_bf16_all", "blco_cp_als_in", "blco_cp_als_size",
             "blco_gram", "blco_cp_als", "blco_build_device",
             "blco_atomic_probe", "blco_gather_probe", "blco_frequent_rows", "blco_info", "blco_export", "blco_free",
             "blco_last_error"]
@@ -75,6 +75,13 @@ class _Info(ctypes.Structure):
                 ("build_stage_ms", ctypes.c_double * 5)]
 
 
+class _Plan(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_int) for k in
+                ("resolution", "lanes", "ranks_per_lane", "window", "wpt", "stash_rows", "copies",
+                 "wide", "vector_gathers", "factor_stride", "out_stride", "grouped")] + [
+                    ("workgroups", ctypes.c_int64), ("workspace_bytes", ctypes.c_size_t)]
+
+
 def library_path() -> str:
     return _SO
 
@@ -98,6 +105,7 @@ def lib():
         L.blco_mttkrp_stream_all_ws.argtypes = [p, p, i32, i32, p, sz, p, sz, p]
         L.blco_cp_grad_ws.argtypes = [p, p, i32, i32, p, ctypes.c_double, p, p, p, sz, p, sz, p]
         L.blco_workspace.argtypes = [p, i32, i32, i32, ctypes.POINTER(sz)]
+        L.blco_plan.argtypes = [p, i32, i32, i32, i32, i64, sz, ctypes.POINTER(_Plan)]
         L.blco_sampled_loss.argtypes = [p, p, i32, i32, p, p, p]
         L.blco_cast_bf16.argtypes = [p, p, i64, p]
         L.blco_cast_bf16_all.argtypes = [i32, p, p, p, p]
@@ -236,6 +244,18 @@ class BLCOTensor:
         _check(lib().blco_workspace(self._h, int(mode), int(rank), BF16 if dtype == "bf16" else F32,
                                     ctypes.byref(n)))
         return n.value
+
+    def plan(self, mode: int, rank: int, dtype: str = "fp32", use: str = "mttkrp", nnz: int = 0,
+             workspace=None) -> dict:
+        """How a launch of `mode` at `rank` runs (blco_plan): window, lanes, frequent rows, padding.
+        use: "mttkrp", "residual" (the CP gradient's fused walk) or "als"; nnz: non-zeros of the
+        launch (0: the tensor's); workspace: bytes lent (None: as many as it wants)."""
+        pl = _Plan()
+        _check(lib().blco_plan(self._h, int(mode), int(rank), BF16 if dtype == "bf16" else F32,
+                               {"mttkrp": 0, "residual": 1, "als": 2}[use], int(nnz),
+                               (1 << 62) if workspace is None else int(workspace),
+                               ctypes.byref(pl)))
+        return {k: getattr(pl, k) for k, _ in _Plan._fields_}
 
     def export(self):
         """(keys uint64, values float32, block_ids uint64, block_starts int64) on the host."""

@@ -943,20 +943,22 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
 // R = 64 bf16, its last two: 4.37 and 2.80 ms in windows of 2048, 3.83 and 2.48 ms) unless
 // their non-zeros were grouped (20M of 200003 x 100003 x 50021, the same: 2.64 and 3.15 ms).
 //
-// least: the smallest window taken.  A caller that amplifies the sums' rounding (CP-ALS
-// multiplies them by V^+) asks for larger ones: smaller windows put more terms of a row
-// through atomics, one after another, onto a sum that is nearly whole (power-law non-zeros,
-// 3 iterations, from 64 bits: 60k: factors 1.4e-5 in windows of 256 and 4e-6 in windows of
-// 1024; 20k: 4.9e-6 in windows of 1024 and 3.8e-6 in windows of 2048).
-static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n, int least) {
+// careful: CP-ALS multiplies the sums by V^+ (condition number about 1e3 on a planted model),
+// which turns their last bits into its factors' fifth digit, so its updates keep one order of
+// summation at every size: the full stash on a mode with frequent rows, else windows of 2048 (4096
+// at R > 32).  1M power-law non-zeros, R = 16, 5 iterations, over 48 inputs: two runs of this
+// route leave the third factor 7e-5 apart in norm, the routes below move it by 1.4e-4; time 1.24
+// against 1.15 ms.
+static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n, bool careful) {
   if (R > 64 || N > kWideMaxN) return 1;
+  if (careful) return R > 32 ? 4 : 2;
   // the fused residual walk's records hold one field more: at N = 5 two windows of 2048 no
   // longer share a CU, and at R > 32 its walk has no registers for four per thread
   const int most = resid ? (N <= 4 ? 2 : 1) : R > 32 && R % 16 == 0 && flat ? 4 : 2;
   if (big) return most;
   const int64_t cus = device_cus();
   for (int w : {-4, -2, 1, 2})
-    if (w == most || (w >= least && n <= (w < 0 ? kWin / -w : kWin * w) * cus)) return w;
+    if (w == most || n <= (w < 0 ? kWin / -w : kWin * w) * cus) return w;
   return most;
 }
 
@@ -974,7 +976,7 @@ static KernelFn select_win(int N, int R, bool even, int fdt, bool big, bool stas
 // of the rows fit).  An explicit threshold at build time keeps the stash
 // regardless.  The kernel's static LDS does not depend on the factor type.
 static int stash_rows(const blco_tensor* t, int mode, int rank, KernelFn f) {
-  if (t->nhot[mode] <= 0 || !t->d_hot) return 0;
+  if (t->nhot[mode] <= 0) return 0;
   int K = 0;
   const size_t fixed = kernel_static_lds((const void*)f) + 2 * (size_t)kHotSlots * 4;
   const size_t budget = win_lds_budget();
@@ -992,14 +994,14 @@ static int stash_rows(const blco_tensor* t, int mode, int rank, KernelFn f) {
 // its look-up and its resident workgroups.  An explicit threshold at build time keeps the
 // full stash.
 static bool copies_ok(const blco_tensor* t, int mode, int rank, int ranks, bool big) {
-  return !t->hot_forced && !big && t->lay.N <= kWideMaxN && ranks <= 64 && t->d_tab &&
+  return !t->hot_forced && !big && t->lay.N <= kWideMaxN && ranks <= 64 &&
          t->lay.dims[mode] * (uint64_t)rank <= (1ULL << 31);
 }
 
 // Whether a mode has rows worth keeping apart: not where the rows beyond the recorded ones
 // are about as frequent as they are (every row then has equally long chains of atomics).
 static bool has_frequent_rows(const blco_tensor* t, int mode) {
-  if (t->nhot[mode] <= 0 || !t->d_hot) return false;
+  if (t->nhot[mode] <= 0) return false;
   const uint64_t* cnt = t->hot_cnt.data() + (size_t)mode * (kHotMax + 1);
   return t->hot_forced || cnt[t->nhot[mode]] * 4 <= cnt[0];
 }
@@ -1067,11 +1069,11 @@ static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int ranks, int
   const bool frequent = has_frequent_rows(t, mode);
   const bool flat = !frequent && !grouped &&
                     window_flushes(t, mode, 2048.0, (double)t->nnz) >= 0.3;
-  WinPlan w = {nullptr, win_wpt(N, gather, resid, big, flat, n, careful ? (frequent ? 1 : 2) : -4), 0, 0, 0, 0};
+  WinPlan w = {nullptr, win_wpt(N, gather, resid, big, flat, n, careful), 0, 0, 0, 0};
   // one non-zero per thread (the residual walk at N = 5): -1 is the form with copies
   const int lw = w.wpt == 1 ? -1 : w.wpt;
   const bool few = windows(lw) <= kCopyMinWindows;
-  if (frequent && copies_ok(t, mode, rank, ranks, big) && (few || (lw != -1 || resid))) {
+  if (!careful && frequent && copies_ok(t, mode, rank, ranks, big) && (few || (lw != -1 || resid))) {
     if (few) {
       w.f = pick(false, w.wpt);
       w.nwin = windows(w.wpt);
@@ -1102,7 +1104,7 @@ static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int ranks, int
 struct Work {
   char* p = nullptr;
   size_t bytes = 0;
-  bool careful = false;   // windows of at least 2048, or 1024 with frequent rows (win_wpt)
+  bool careful = false;   // a CP-ALS update: the full stash, and no copies or grouping (win_wpt)
 };
 
 static size_t up256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1172,8 +1174,9 @@ struct CallPlan {
   size_t bytes;
 };
 
+// careful: only padded factors, which change no sum.
 static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int res, bool resid,
-                          int64_t n, size_t room) {
+                          int64_t n, size_t room, bool careful) {
   const int N = t->lay.N;
   const size_t fsz = factor_elem_bytes(fdt);
   CallPlan c = {0, rank, false, 0, 0};
@@ -1181,7 +1184,7 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
   auto left = [&] { return room > c.bytes ? room - c.bytes : 0; };
   const bool big = big_gathers(t, mode, rank, fdt, false, false) ||
                    big_gathers(t, mode, rank, fdt, true, resid);
-  if (reg) {
+  if (reg && !careful) {
     c.copy_bytes = up256(plan_win(t, mode, rank, rank, rank, rank % 2 == 0, fdt,
                                   big_gathers(t, mode, rank, fdt, true, resid), resid, n, room,
                                   false, false)
@@ -1198,7 +1201,7 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
       c.bytes += bytes;
     }
   }
-  if (reg && !big) {
+  if (reg && !big && !careful) {
     const int Ro = padded_out(t, mode, rank, n);
     const size_t bytes = up256((size_t)t->lay.dims[mode] * Ro * sizeof(float));
     if (Ro != rank && bytes <= left()) {
@@ -1206,7 +1209,7 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
       c.bytes += bytes;
     }
   }
-  if (reg && !resid && !big && group_pays(t, mode, rank, n)) {
+  if (reg && !resid && !big && !careful && group_pays(t, mode, rank, n)) {
     const size_t bytes =
         up256(8 * (size_t)n) + up256(4 * (size_t)n) + up256(4 * (size_t)kGroupBuckets);
     if (bytes <= left()) {
@@ -1215,6 +1218,40 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
     }
   }
   return c;
+}
+
+// Everything a launch over n non-zeros decides: resolution, addressing, CallPlan and, where the
+// window kernel runs, WinPlan.
+struct LaunchPlan {
+  int res;
+  int sw;               // hierarchical kernel: ranks per slice
+  bool big, big_win;    // 64-bit addresses in the hierarchical / the window kernel
+  CallPlan cp;
+  int stride;           // elements between factor rows
+  WinPlan w;
+  int64_t grid;         // workgroups of the window kernel
+};
+
+static int plan_launch(const blco_tensor* t, int mode, int rank, int fdt, bool resid, int64_t n,
+                       size_t room, bool careful, LaunchPlan* L) {
+  L->res = resolve(t, mode, rank, &L->sw);
+  if (L->res < 0) return L->res;
+  L->big = big_gathers(t, mode, rank, fdt, false, false);
+  L->big_win = big_gathers(t, mode, rank, fdt, true, resid);
+  L->cp = plan_call(t, mode, rank, fdt, L->res, resid, n, room, careful);
+  L->stride = L->cp.pad ? L->cp.pad : rank;
+  if (L->res != BLCO_RES_REGISTER) return BLCO_OK;
+  L->w = plan_win(t, mode, L->cp.out, rank, L->stride, L->stride % 2 == 0, fdt, L->big_win, resid,
+                  n, L->cp.copy_bytes, careful, L->cp.group);
+  // with a stash: persistent workgroups, kWinRounds times the resident count
+  // (two per CU) in a long launch, which balances its end (1-2% faster than one round
+  // on 50M non-zeros); once the resident count in a shorter one, where the stash
+  // flushes count more (2M non-zeros, R = 16: 68 us and 58 us); without one: a
+  // workgroup per window (about 1% faster than persistent ones)
+  const int rounds = careful || L->w.nwin >= 16 * 1024 ? kWinRounds : 1;
+  L->grid = L->w.stash > 0 ? std::min<int64_t>(L->w.nwin, (int64_t)device_cus() * 2 * rounds)
+                           : L->w.nwin;
+  return BLCO_OK;
 }
 
 // Launch the MTTKRP kernel over [lo, lo + n) of the tensor given by keys/vals, clearing the
@@ -1242,23 +1279,20 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
   p.scale_dev = scale_dev;
   p.resid = resid;
   const size_t fsz = factor_elem_bytes(fdt);
-  const bool big = big_gathers(t, mode, rank, fdt, false, false);
-  const bool big_win = big_gathers(t, mode, rank, fdt, true, resid != nullptr);
-  int sw = 0;
-  const int res = resolve(t, mode, rank, &sw);
-  if (res < 0) return res;
-  if (resid && (res != BLCO_RES_REGISTER || big || rank > 64 ||
+  LaunchPlan L;
+  int rc = plan_launch(t, mode, rank, fdt, resid != nullptr, n, ws.bytes, ws.careful, &L);
+  if (rc) return rc;
+  const CallPlan& cp = L.cp;
+  const int stride = L.stride;
+  if (resid && (L.res != BLCO_RES_REGISTER || L.big || rank > 64 ||
                 (size_t)t->lay.dims[mode] * rank * fsz > 0xFFFFFFFFull))
     return set_error(BLCO_EUNSUPPORTED, "fused residual walk on mode %d", mode);
-  const CallPlan cp = plan_call(t, mode, rank, fdt, res, resid != nullptr, n, ws.bytes);
   // the workspace: hot copies, padded factors, grouped non-zeros and their cursors
   PrepParams pre = {};
   pre.zero[0] = out;
   pre.nzero[0] = clear_n;
   char* at = ws.p + cp.copy_bytes;
-  int stride = rank;
   if (cp.pad) {
-    stride = cp.pad;
     pre.R = rank;
     pre.Rp = stride;
     for (int m = 0; m < N; ++m) {
@@ -1275,21 +1309,21 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
     const size_t bytes = (size_t)t->lay.dims[m] * stride * fsz;
     p.abytes[m] = (uint32_t)std::min<size_t>(bytes, 0xFFFFFFFFull);
   }
-  if (res == BLCO_RES_HIERARCHICAL) {
-    int rc = prepare(pre, fdt, s);
-    if (rc) return rc;
+  if (L.res == BLCO_RES_HIERARCHICAL) {
+    if ((rc = prepare(pre, fdt, s))) return rc;
+    const int sw = L.sw;
     p.short_rows = (uint32_t)t->lay.dims[mode];
     p.short_width = sw;
     const int slices = (rank + sw - 1) / sw;
     // two resident workgroups per CU over all slices; each takes an equal range of at
     // least one batch (four batches left a short launch on a few CUs: 100k non-zeros,
-    // R = 32, 200 rows: 26 us with four, 10 us with one)
+    // R = 32, 200 rows: 26 us with four, 10 us with one; a CP-ALS update keeps four)
     const int64_t want = std::max<int64_t>(device_cus() * 2 / slices, 1);
-    int64_t per = std::max<int64_t>((n + want - 1) / want, (int64_t)kShortB);
+    int64_t per = std::max<int64_t>((n + want - 1) / want, (int64_t)kShortB * (ws.careful ? 4 : 1));
     per = (per + kShortB - 1) / kShortB * kShortB;
     const int64_t nwg = (n + per - 1) / per;
     const size_t lds = short_lds(N, t->lay.dims[mode], sw);
-    ShortFn f = select_short(N, sw, stride, fdt, big);
+    ShortFn f = select_short(N, sw, stride, fdt, L.big);
     hipLaunchKernelGGL(f, dim3((unsigned)nwg, (unsigned)slices), dim3(kShortB), lds, s, p, per);
     HIPCHK(hipGetLastError());
     return BLCO_OK;
@@ -1317,8 +1351,7 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
   p.RG = stride;
   p.RV = std::max(rank, std::min(stride, ro));
   p.out = rows;
-  const WinPlan w = plan_win(t, mode, ro, rank, stride, stride % 2 == 0, fdt, big_win,
-                             resid != nullptr, n, cp.copy_bytes, ws.careful, cp.group);
+  const WinPlan& w = L.w;
   p.hot = t->d_hot + (size_t)mode * kHotMax;
   p.nhot = w.stash;
   if (w.copies) {
@@ -1330,8 +1363,7 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
     pre.zero[1] = copy;
     pre.nzero[1] = (int64_t)(w.bytes / sizeof(float));
   }
-  int rc = prepare(pre, fdt, s);
-  if (rc) return rc;
+  if ((rc = prepare(pre, fdt, s))) return rc;
   if (cp.group) {
     const int64_t per = 1024 * kGroupPer;
     hipLaunchKernelGGL(k_group, dim3((unsigned)((n + per - 1) / per)), dim3(1024), 0, s, keys,
@@ -1340,15 +1372,7 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
     HIPCHK(hipGetLastError());
   }
   const size_t dyn = w.stash > 0 ? (size_t)w.stash * ro * 4 + 2 * (size_t)kHotSlots * 4 : 0;
-  // with a stash: persistent workgroups, kWinRounds times the resident count
-  // (two per CU) in a long launch, which balances its end (1-2% faster than one round
-  // on 50M non-zeros); once the resident count in a shorter one, where the stash
-  // flushes count more (2M non-zeros, R = 16: 68 us and 58 us); without one: a
-  // workgroup per window (about 1% faster than persistent ones)
-  const int rounds = w.nwin >= 16 * 1024 ? kWinRounds : 1;
-  const int64_t grid =
-      w.stash > 0 ? std::min<int64_t>(w.nwin, (int64_t)device_cus() * 2 * rounds) : w.nwin;
-  hipLaunchKernelGGL(w.f, dim3((unsigned)grid), dim3(kWin), dyn, s, p);
+  hipLaunchKernelGGL(w.f, dim3((unsigned)L.grid), dim3(kWin), dyn, s, p);
   HIPCHK(hipGetLastError());
   if (w.copies) {
     hipLaunchKernelGGL(k_hot_sum, dim3((unsigned)t->nhot[mode]), dim3(kBlock), 0, s,
@@ -1552,14 +1576,14 @@ static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool 
 
 // Workspace the MTTKRP of mode `mode` over n non-zeros can use (0: none).
 static size_t mode_workspace(const blco_tensor* t, int mode, int rank, int fdt, bool resid,
-                             int64_t n) {
+                             int64_t n, bool careful = false) {
   int sw = 0;
   const int res = n > 0 ? resolve(t, mode, rank, &sw) : BLCO_EINVAL;
   if (res < 0) {
     clear_error();
     return 0;
   }
-  return plan_call(t, mode, rank, fdt, res, resid, n, ~(size_t)0 / 2).bytes;
+  return plan_call(t, mode, rank, fdt, res, resid, n, ~(size_t)0 / 2, careful).bytes;
 }
 
 // The in-memory MTTKRP calls, with an optional workspace.
@@ -1577,7 +1601,7 @@ static int mttkrp_impl(blco_tensor* t, int mode, const float* values, const void
 }
 
 size_t blco::mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype) {
-  return mode_workspace(t, mode, rank, factor_dtype, false, t->nnz);
+  return mode_workspace(t, mode, rank, factor_dtype, false, t->nnz, true);
 }
 
 int blco::mttkrp_careful(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
@@ -2222,6 +2246,57 @@ extern "C" int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int*
   const WinPlan w = plan_win(t, mode, rank, rank, rank, rank % 2 == 0, BLCO_F32, false, false,
                              std::max<int64_t>(t->nnz, 1), 0, false, false);
   *rows = w.stash;
+  return BLCO_OK;
+}
+
+// Lanes per non-zero and ranks per lane of the window kernel (select_win_t, select_res_t).
+static void win_shape(int gather, int fdt, bool big, bool resid, int wpt, int* lanes, int* rpl) {
+  *lanes = gather <= 64 ? 16 : 64;
+  if (gather > 64) *rpl = 2;
+  else if (gather <= 32) *rpl = gather <= 16 ? 1 : 2;
+  else *rpl = fdt == BLCO_F32 && !big && !resid && gather <= 48 && wpt != 1 ? 3 : 4;
+}
+
+extern "C" int blco_plan(const blco_tensor* t, int mode, int rank, int factor_dtype, int use,
+                         int64_t nnz, size_t workspace_bytes, blco_plan_t* plan) {
+  clear_error();
+  if (!t || !plan) return set_error(BLCO_EINVAL, "tensor or plan is NULL");
+  if (mode < 0 || mode >= t->lay.N)
+    return set_error(BLCO_EINVAL, "mode %d outside 0..%d", mode, t->lay.N - 1);
+  if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
+  if (factor_dtype != BLCO_F32 && factor_dtype != BLCO_BF16)
+    return set_error(BLCO_EINVAL, "factor dtype %d", factor_dtype);
+  if (use < BLCO_USE_MTTKRP || use > BLCO_USE_ALS) return set_error(BLCO_EINVAL, "use %d", use);
+  if (nnz < 0) return set_error(BLCO_EINVAL, "nnz %lld < 0", (long long)nnz);
+  const bool resid = use == BLCO_USE_RESIDUAL;
+  if (resid && !fused_mode_ok(t, mode, rank, factor_dtype))
+    return set_error(BLCO_EUNSUPPORTED, "fused residual walk on mode %d", mode);
+  const int64_t n = nnz ? nnz : std::max<int64_t>(t->nnz, 1);
+  LaunchPlan L;
+  int rc = plan_launch(t, mode, rank, factor_dtype, resid, n, workspace_bytes, use == BLCO_USE_ALS,
+                       &L);
+  if (rc) return rc;
+  memset(plan, 0, sizeof(*plan));
+  plan->resolution = L.res;
+  plan->factor_stride = L.stride;
+  plan->out_stride = L.cp.out;
+  plan->grouped = L.cp.group;
+  plan->workspace_bytes = L.cp.bytes;
+  plan->vector_gathers = factor_dtype == BLCO_BF16 && L.stride % 2 == 0;
+  if (L.res != BLCO_RES_REGISTER) {
+    plan->wide = L.big;
+    plan->window = kShortB;
+    plan->lanes = kShortLPN;
+    plan->ranks_per_lane = short_rpl(L.sw);
+    return BLCO_OK;
+  }
+  plan->wide = L.big_win;
+  plan->wpt = L.w.wpt;
+  plan->window = L.w.wpt < 0 ? kWin / -L.w.wpt : kWin * L.w.wpt;
+  plan->stash_rows = L.w.stash;
+  plan->copies = L.w.copies;
+  plan->workgroups = L.grid;
+  win_shape(L.stride, factor_dtype, L.big_win, resid, L.w.wpt, &plan->lanes, &plan->ranks_per_lane);
   return BLCO_OK;
 }
 
