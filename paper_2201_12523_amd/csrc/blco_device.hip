@@ -1025,6 +1025,11 @@ static int copy_stride(int rank) { return (rank + 15) / 16 * 16; }   // whole 64
 static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool window,
                         bool resid);
 
+// Most elements of an output that the window kernel addresses in 32 bits: its records hold a
+// row's first element, and a flush adds a lane number of up to 15 to it before it takes the row's
+// distance from a 64-byte line off (flush_row), so the last row has to end 16 before 2^32.
+constexpr uint64_t kIndexMax = (1ULL << 32) - 16;
+
 // Expected row flushes per non-zero of mode `mode` in windows of W of n non-zeros, taken as
 // spread evenly over the index space: the window covers the index's lowest
 // log2(W * cells / n) bits, so mode m moves over 2^(its bits among them) rows.
@@ -1560,8 +1565,7 @@ extern "C" int blco_build(int nmodes, const uint64_t* dims, int64_t nnz,
 // factors below 4 GiB are gathered with 32-bit byte offsets, larger ones with 64-bit
 // addresses; the window kernel's fp32 gathers at 33-64 ranks (ld_base; not the fused
 // residual walk) also take a factor of exactly 4 GiB with 32-bit offsets.  An output of more
-// than 2^32 elements takes the window kernel's 64-bit form too (its records hold the output
-// row's first element in 32 bits).
+// than kIndexMax elements takes the window kernel's 64-bit form too.
 static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool window,
                         bool resid) {
   const size_t fsz = factor_elem_bytes(fdt);
@@ -1571,7 +1575,7 @@ static bool big_gathers(const blco_tensor* t, int mode, int rank, int fdt, bool 
     if (m != mode &&
         (size_t)t->lay.dims[m] * rank * fsz > (base32 ? (1ULL << 32) : 0xFFFFFFFFull))
       return true;
-  return window && (uint64_t)t->lay.dims[mode] * (uint64_t)rank > (1ULL << 32);
+  return window && (uint64_t)t->lay.dims[mode] * (uint64_t)rank > kIndexMax;
 }
 
 // Workspace the MTTKRP of mode `mode` over n non-zeros can use (0: none).
