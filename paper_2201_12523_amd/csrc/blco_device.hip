@@ -1127,7 +1127,7 @@ static size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 // and 1060; R = 60: 1282 and 1127; 200000 x 100000 x 20000, R = 17: 553 and 482; R = 31: 635
 // and 490; bf16 R = 35: 952, to 40 712 and to 48 780; fp32 R = 50: 842, to 52 869 and to 64
 // 898.  The copy reads and writes every row once (about 0.06 us per thousand rows at R = 32).
-constexpr size_t kPadMax = (size_t)1 << 30;   // bytes of padded factors
+constexpr size_t kPadMax = (size_t)1 << 30;   // bytes of padded factors, and of a padded output
 static int padded_rank(const blco_tensor* t, int mode, int rank, int fdt, bool all, int64_t n) {
   uint64_t rows = 0;
   for (int m = 0; m < t->lay.N; ++m)
@@ -1145,10 +1145,16 @@ static int padded_rank(const blco_tensor* t, int mode, int rank, int fdt, bool a
 // non-zeros of 200000 x 100000 x 20000, all modes: R = 10: 502 and 371 us; R = 31: 635 and
 // 532; R = 97: 1594 and 1530.  Clearing and copying pay where the rows are few against the
 // non-zeros: R = 50 on the same tensor took 841 us, with all modes padded 870.
+//
+// The kernel's 32-bit element indices address the padded rows, so these are bounded, as the padded
+// factors are: kPadMax bytes (16M rows of 16 elements) of workspace.
 static int padded_out(const blco_tensor* t, int mode, int rank, int64_t n) {
-  if (n < (1 << 18) || t->lay.dims[mode] * (rank > 32 ? 32 : 8) > (uint64_t)n) return rank;
-  return (rank + 15) / 16 * 16;
+  const uint64_t rows = t->lay.dims[mode];
+  if (n < (1 << 18) || rows * (rank > 32 ? 32 : 8) > (uint64_t)n) return rank;
+  const int Ro = (rank + 15) / 16 * 16;
+  return rows * Ro * sizeof(float) > kPadMax ? rank : Ro;
 }
+static_assert(kPadMax / sizeof(float) <= kIndexMax, "padded outputs keep 32-bit indices");
 
 // Whether a launch over n non-zeros moves them to buckets of target rows first (k_group):
 // where the row flushes that saves, at the memory side's rate (about 52 ps per 64-byte line),

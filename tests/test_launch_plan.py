@@ -40,3 +40,20 @@ def test_output_index_width(rows, R):
         assert not p["wide"]
         for row in (rows - 1, rows - 2, rows - 3):
             assert flushed(row * R, R, True) == list(range(row * R, row * R + R))
+
+
+# padded output rows: their elements fit 32-bit indices, and they take a bounded workspace, however
+# many rows and non-zeros there are
+@pytest.mark.parametrize("R", [1, 7, 10, 17, 31, 33, 50, 63, 97])
+def test_padded_output_is_bounded(R):
+    padded = 0
+    for rows in (3000, 1 << 20, 8_000_000, 16_777_216, 16_777_217, 140_000_000, 1 << 28):
+        t = host_tensor((rows, 3, 5))
+        for n in (8 * rows - 1, 8 * rows, 32 * rows):
+            p = t.plan(0, R, nnz=n)
+            if p["out_stride"] != R:
+                padded += 1
+                assert p["out_stride"] == -(-R // 16) * 16 and not p["wide"]
+                assert rows * p["out_stride"] <= (1 << 32) - 16
+                assert p["workspace_bytes"] <= 2 << 30
+    assert padded
