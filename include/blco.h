@@ -91,7 +91,8 @@ typedef struct {
   int placement;
   size_t device_bytes;       /* device memory held by the tensor itself */
   size_t host_bytes;         /* host memory held by the tensor */
-  size_t stream_peak_bytes;  /* last blco_mttkrp_stream call: factors + out + staging + tables */
+  size_t stream_peak_bytes;  /* last blco_mttkrp_stream call: factors + out + staging + tables +
+                                workspace used */
   int64_t stream_chunks;     /* last blco_mttkrp_stream call: chunks transferred */
   int64_t stream_chunk_nnz;  /* last blco_mttkrp_stream call: non-zeros per staging buffer */
   double stream_copy_ms;     /* last streaming call: host-to-device copy time, summed over chunks */
@@ -208,7 +209,7 @@ int blco_mttkrp_ws(blco_tensor* t, int mode, const float* values, const void* co
                    float* out, void* workspace, size_t workspace_bytes, void* stream);
 
 /* The most workspace bytes a blco_mttkrp_ws call of mode `mode` at rank `rank` uses, or with
-   mode -1 a blco_cp_grad_ws or blco_mttkrp_stream_all_ws call (0: none).  Errors: EINVAL. */
+   mode -1 a blco_cp_grad_ws call on a DEVICE tensor (0: none).  Errors: EINVAL. */
 int blco_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype, size_t* bytes);
 
 /*
@@ -244,8 +245,16 @@ int blco_mttkrp_stream_all(blco_tensor* t, const void* const* factors, int facto
 
 /*
  * blco_mttkrp_stream_all with a workspace as in blco_mttkrp_ws.  The workspace counts
- * against the budget, and is not used where the budget leaves no room for it.
+ * against the budget.  The staging buffers come first: a workspace is used (in full or in part)
+ * where they leave room for it, or where it takes at most an eighth of the memory for both.
+ * blco_stream_plan gives, for a budget and the bytes a caller could lend, those the call uses
+ * (lend no more) and the non-zeros of a chunk (0: a DEVICE tensor, computed in memory): modes: a
+ * bit per mode whose output is given; gradient != 0: a blco_cp_grad_ws call on a PINNED tensor.
+ * Errors: EINVAL, ENOMEM (as the call itself).
  */
+int blco_stream_plan(const blco_tensor* t, unsigned modes, int gradient, int rank,
+                     int factor_dtype, size_t device_budget_bytes, size_t workspace_bytes,
+                     size_t* used, int64_t* chunk_nnz);
 int blco_mttkrp_stream_all_ws(blco_tensor* t, const void* const* factors, int factor_dtype,
                               int rank, float* const* outs, size_t device_budget_bytes,
                               void* workspace, size_t workspace_bytes, void* stream);
@@ -296,7 +305,7 @@ int blco_cp_grad(blco_tensor* t, const void* const* factors, int factor_dtype, i
                  float* const* grads, size_t device_budget_bytes, void* stream);
 
 /* blco_cp_grad with a workspace as in blco_mttkrp_ws (PINNED placement: it counts against
-   the budget). */
+   the budget, as in blco_mttkrp_stream_all_ws). */
 int blco_cp_grad_ws(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
                     const double* scale, double alpha, float* residual, double* loss,
                     float* const* grads, size_t device_budget_bytes, void* workspace,

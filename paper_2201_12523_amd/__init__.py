@@ -34,7 +34,7 @@ EXPORTED = ["blco_build", "blco_mttkrp", "blco_mttkrp_acc", "blco_mttkrp_v", "bl
             "blco_mttkrp_stream_all", "blco_mttkrp_ws", "blco_mttkrp_stream_all_ws",
             "blco_cp_grad_ws", "blco_workspace", "blco_build_device_in", "blco_build_device_sizes",
             "blco_sampled_loss", "blco_cp_grad", "blco_cp_grad_noalloc", "blco_scale", "blco_cast_bf16", "blco_set_resolution", "blco_resolution",
-            "blco_plan", "blco_scale_all", "blco_cast_bf16_all", "blco_cp_als_in", "blco_cp_als_size",
+            "blco_plan", "blco_stream_plan", "blco_scale_all", "blco_cast_bf16_all", "blco_cp_als_in", "blco_cp_als_size",
             "blco_gram", "blco_cp_als", "blco_build_device",
             "blco_atomic_probe", "blco_gather_probe", "blco_frequent_rows", "blco_info", "blco_export", "blco_free",
             "blco_last_error"]
@@ -106,6 +106,8 @@ def lib():
         L.blco_cp_grad_ws.argtypes = [p, p, i32, i32, p, ctypes.c_double, p, p, p, sz, p, sz, p]
         L.blco_workspace.argtypes = [p, i32, i32, i32, ctypes.POINTER(sz)]
         L.blco_plan.argtypes = [p, i32, i32, i32, i32, i64, sz, ctypes.POINTER(_Plan)]
+        L.blco_stream_plan.argtypes = [p, ctypes.c_uint, i32, i32, i32, sz, sz, ctypes.POINTER(sz),
+                                       ctypes.POINTER(i64)]
         L.blco_sampled_loss.argtypes = [p, p, i32, i32, p, p, p]
         L.blco_cast_bf16.argtypes = [p, p, i64, p]
         L.blco_cast_bf16_all.argtypes = [i32, p, p, p, p]
@@ -402,6 +404,22 @@ def _workspace(t, mode, R, dt, device, stream):
         need = ctypes.c_size_t()
         _check(lib().blco_workspace(t.handle, mode, R, dt, ctypes.byref(need)))
         bytes_ = t._need[(mode, R, dt)] = need.value
+    return _lend(bytes_, device, stream)
+
+
+def _stream_workspace(t, modes, gradient, R, dt, budget, device, stream):
+    """The workspace a call under a device budget uses; none where the budget has no room, and
+    where the call itself will say what is wrong with its arguments."""
+    used, chunk = ctypes.c_size_t(), ctypes.c_int64()
+    bits = sum(1 << m for m in set(modes) if 0 <= m < len(t.dims))
+    if lib().blco_stream_plan(t.handle, bits, gradient, R, dt, int(budget), 1 << 62,
+                              ctypes.byref(used), ctypes.byref(chunk)) != 0:
+        return None, None, 0
+    return _lend(used.value, device, stream)
+
+
+def _lend(bytes_, device, stream):
+    """(tensor or None, pointer, bytes) of a block from the pool of the stream a call runs on."""
     if bytes_ == 0:
         return None, None, 0
     try:
@@ -464,8 +482,8 @@ def mttkrp_stream(t, mode, factors, out=None, device_budget=8_000_000_000, strea
     """MTTKRP of a tensor in pinned host memory, streamed under a device-memory budget."""
     arr, dt, R, _keep = _factor_args(t, factors, mode)
     out = _out(t, mode, R, out, _device_of(factors))
-    ws, wp, wb = _workspace(t, mode, R, dt, out.device, stream)
-    if wb == 0 or mode < 0:
+    ws, wp, wb = _stream_workspace(t, [mode], 0, R, dt, device_budget, out.device, stream)
+    if wb == 0:
         _check(lib().blco_mttkrp_stream(t.handle, mode, arr, dt, R, out.data_ptr(),
                                         int(device_budget), _stream(stream, t)))
         return out
@@ -489,7 +507,7 @@ def mttkrp_stream_all(t, factors, outs=None, device_budget=8_000_000_000, modes=
         outs[m] = _out(t, m, R, outs[m], dev)
     ptrs = (ctypes.c_void_p * len(t.dims))(*[outs[m].data_ptr() if m in modes else None
                                                for m in range(len(t.dims))])
-    ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
+    ws, wp, wb = _stream_workspace(t, modes, 0, R, dt, device_budget, dev, stream)
     _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, ptrs, int(device_budget), wp, wb,
                                            _stream(stream, t)))
     return [outs[m] if m in modes else None for m in range(len(t.dims))]
@@ -533,7 +551,10 @@ def cp_grad(t, factors, grads=None, residual=None, loss=None, scale=None, alpha=
             raise ValueError("scale must be a one-element float64 device tensor")
         sp = scale.data_ptr()
     ptrs = (ctypes.c_void_p * N)(*[g.data_ptr() for g in grads])
-    ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
+    if pinned:
+        ws, wp, wb = _stream_workspace(t, range(N), 1, R, dt, device_budget, dev, stream)
+    else:
+        ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
     _check(lib().blco_cp_grad_ws(t.handle, arr, dt, R, sp, float(alpha),
                                  None if pinned else residual.data_ptr(), loss.data_ptr(), ptrs,
                                  int(device_budget), wp, wb, _stream(stream, t)))

@@ -1662,10 +1662,6 @@ extern "C" int blco_mttkrp_ws(blco_tensor* t, int mode, const float* values,
                      rank, scale, alpha, accumulate != 0, out, ws, (hipStream_t)stream);
 }
 
-// Stream the pinned non-zeros once through two reused staging buffers and,
-// for every chunk, run the MTTKRP of each selected mode (outs[m] != NULL) while
-// the chunk is resident.  Device bytes: factors read + selected outputs +
-// tensor tables + two staging buffers <= budget.
 // Whether the fused residual walk can serve mode m: register-based resolution,
 // one rank slice of 16-lane groups (R <= 64) and 32-bit gather offsets.
 static bool fused_mode_ok(const blco_tensor* t, int m, int rank, int fdt) {
@@ -1780,24 +1776,90 @@ static int64_t grad_parts(int64_t n) {
   return std::max<int64_t>((n + kSqPer - 1) / kSqPer, loss_blocks(n));
 }
 
+// First mode whose MTTKRP can carry the gradient's fused residual walk, or -1.
+static int fused_mode(const blco_tensor* t, int rank, int fdt) {
+  for (int m = 0; m < t->lay.N; ++m)
+    if (fused_mode_ok(t, m, rank, fdt)) return m;
+  return -1;
+}
+
+// Device memory of a call over the selected modes (one bit each) under a budget: what it cannot do
+// without, the non-zeros per staging buffer and the bytes of workspace it uses of those lent.
+struct StreamPlan {
+  size_t fixed;     // factors read + selected outputs + the tensor's own arrays
+  size_t per_nnz;   // staging: key and value, and the chunk's residual for the gradient
+  int64_t cap;      // non-zeros per staging buffer
+  size_t ws;
+};
+
+// The staging comes first: the workspace has what the staging leaves over (the staging ends at
+// the tensor's size or its blocks'), or takes at most an eighth of the memory for both, and only
+// as much as launches over a chunk of that size use.  Streaming is bound by the host link, so
+// larger chunks cost nothing that a workspace could give back, while chunks of 64 non-zeros
+// cost four events and every mode's launches each.
+static int plan_stream(const blco_tensor* t, unsigned modes, bool grad, int rank, int fdt,
+                       size_t budget, size_t lent, StreamPlan* p) {
+  const Layout& L = t->lay;
+  bool need[BLCO_MAX_MODES] = {};
+  p->fixed = t->device_bytes;
+  for (int m = 0; m < L.N; ++m) {
+    if (!(modes >> m & 1)) continue;
+    p->fixed += (size_t)L.dims[m] * rank * sizeof(float);
+    for (int j = 0; j < L.N; ++j)
+      if (j != m || grad) need[j] = true;   // the residual reads every factor
+  }
+  for (int m = 0; m < L.N; ++m)
+    if (need[m]) p->fixed += (size_t)L.dims[m] * rank * factor_elem_bytes(fdt);
+  const int m0 = grad ? fused_mode(t, rank, fdt) : -1;
+  auto used = [&](int64_t n) {
+    size_t most = 0;
+    if (lent > 0)
+      for (int m = 0; m < L.N; ++m)
+        if (modes >> m & 1) most = std::max(most, mode_workspace(t, m, rank, fdt, m == m0, n));
+    return std::min(most, lent);
+  };
+  p->cap = 0;
+  p->per_nnz = 0;
+  if (t->placement == BLCO_PLACE_DEVICE) {
+    if (p->fixed > budget)
+      return set_error(BLCO_ENOMEM, "budget %zu below factors + outputs + tensor = %zu", budget,
+                       p->fixed);
+    const size_t ws = used(t->nnz);
+    p->ws = ws <= budget - p->fixed ? ws : 0;
+    return BLCO_OK;
+  }
+  p->per_nnz = sizeof(uint64_t) + sizeof(float) + (grad ? sizeof(float) : 0);
+  if (budget < p->fixed + 2 * 64 * p->per_nnz)
+    return set_error(BLCO_ENOMEM, "budget %zu cannot hold factors + outputs + tables (%zu) and "
+                                  "two staging buffers", budget, p->fixed);
+  auto staged = [&](size_t room) {
+    int64_t cap = (int64_t)(room / 2 / p->per_nnz);
+    cap = std::min(cap, ((t->max_block_nnz + 63) / 64) * 64);
+    cap = std::min(cap, ((t->nnz + 63) / 64) * 64);
+    return std::max<int64_t>(cap / 64 * 64, 64);
+  };
+  const size_t room = budget - p->fixed;
+  p->cap = staged(room);
+  p->ws = used(p->cap);
+  if (p->ws <= room - 2 * (size_t)p->cap * p->per_nnz) return BLCO_OK;
+  const int64_t less = p->ws <= room / 8 ? staged(room - p->ws) : 0;
+  p->ws = less ? std::min(p->ws, used(less)) : 0;
+  if (p->ws) p->cap = less;
+  return BLCO_OK;
+}
+
+// Stream the pinned non-zeros once through two reused staging buffers and,
+// for every chunk, run the MTTKRP of each selected mode (outs[m] != NULL) while
+// the chunk is resident.  Device bytes: factors read + selected outputs +
+// tensor tables + two staging buffers + workspace used <= budget.
 static int stream_modes(blco_tensor* t, const void* const* factors, int factor_dtype, int rank,
                         float* const* outs, size_t device_budget_bytes, hipStream_t s,
                         Work ws, const GradArgs* grad = nullptr) {
   const Layout& L = t->lay;
-  bool need[BLCO_MAX_MODES] = {};
-  int nsel = 0;
+  unsigned modes = 0;
   for (int m = 0; m < L.N; ++m)
-    if (outs[m]) {
-      ++nsel;
-      for (int j = 0; j < L.N; ++j)
-        if (j != m || grad) need[j] = true;   // the residual reads every factor
-    }
-  if (nsel == 0) return set_error(BLCO_EINVAL, "no output given");
-  size_t fixed = t->device_bytes;
-  for (int m = 0; m < L.N; ++m) {
-    if (outs[m]) fixed += (size_t)L.dims[m] * rank * sizeof(float);
-    if (need[m]) fixed += (size_t)L.dims[m] * rank * factor_elem_bytes(factor_dtype);
-  }
+    if (outs[m]) modes |= 1u << m;
+  if (!modes) return set_error(BLCO_EINVAL, "no output given");
   int rc;
   if (t->placement == BLCO_PLACE_DEVICE && grad) {
     double* part = grad->partials;
@@ -1812,42 +1874,34 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     hipLaunchKernelGGL(k_reduce_loss, dim3(1), dim3(1024), 0, s, (const double*)part, np,
                        grad->loss);
     HIPCHK(hipGetLastError());
-    t->stream_peak_bytes = fixed;
+    t->stream_peak_bytes = t->device_bytes + ws.bytes;
+    for (int m = 0; m < L.N; ++m)
+      t->stream_peak_bytes +=
+          (size_t)L.dims[m] * rank * (sizeof(float) + factor_elem_bytes(factor_dtype));
     t->stream_chunks = 0;
     t->st.timed_chunks = 0;
     return BLCO_OK;
   }
+  if (t->placement != BLCO_PLACE_DEVICE && t->placement != BLCO_PLACE_PINNED)
+    return set_error(BLCO_EINVAL, "streaming needs a tensor in pinned host memory");
+  StreamPlan sp;
+  if ((rc = plan_stream(t, modes, grad != nullptr, rank, factor_dtype, device_budget_bytes,
+                        ws.bytes, &sp)))
+    return rc;
+  ws.bytes = sp.ws;
   if (t->placement == BLCO_PLACE_DEVICE) {
-    if (fixed > device_budget_bytes)
-      return set_error(BLCO_ENOMEM, "budget %zu below factors + outputs + tensor = %zu",
-                       device_budget_bytes, fixed);
     for (int m = 0; m < L.N; ++m) {
       if (!outs[m]) continue;
       if ((rc = launch_mttkrp(t, t->d_keys, t->d_vals, 0, t->nnz, m, factors, factor_dtype, rank,
                               1.0f, nullptr, outs[m], s, ws, true)))
         return rc;
     }
-    t->stream_peak_bytes = fixed;
+    t->stream_peak_bytes = sp.fixed + ws.bytes;
     t->stream_chunks = 0;
     t->st.timed_chunks = 0;
     return BLCO_OK;
   }
-  if (t->placement != BLCO_PLACE_PINNED)
-    return set_error(BLCO_EINVAL, "streaming needs a tensor in pinned host memory");
-  // staging per non-zero: key and value, and the chunk's residual for the gradient
-  const size_t per_nnz = sizeof(uint64_t) + sizeof(float) + (grad ? sizeof(float) : 0);
-  // a workspace counts against the budget, and is left out where the budget has no room
-  if (device_budget_bytes < fixed + ws.bytes + 2 * 64 * per_nnz) ws = Work();
-  fixed += ws.bytes;
-  if (device_budget_bytes < fixed + 2 * 64 * per_nnz)
-    return set_error(BLCO_ENOMEM, "budget %zu cannot hold factors + outputs + tables (%zu) and "
-                                  "two staging buffers", device_budget_bytes, fixed);
-  int64_t cap = (int64_t)((device_budget_bytes - fixed) / 2 / per_nnz);
-  int64_t blk_cap = ((t->max_block_nnz + 63) / 64) * 64;
-  cap = std::min(cap, blk_cap);
-  cap = std::min(cap, ((t->nnz + 63) / 64) * 64);
-  cap = (cap / 64) * 64;
-  if (cap < 64) cap = 64;
+  const int64_t cap = sp.cap;
   StreamState& st = t->st;
   if (!st.copy_stream) {
     hipStream_t cs;
@@ -1939,7 +1993,7 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     HIPCHK(hipGetLastError());
   }
   st.timed_chunks = chunks;
-  t->stream_peak_bytes = fixed + 2 * (size_t)cap * per_nnz;
+  t->stream_peak_bytes = sp.fixed + ws.bytes + 2 * (size_t)cap * sp.per_nnz;
   t->stream_chunks = chunks;
   return BLCO_OK;
 }
@@ -2086,9 +2140,7 @@ static int cp_grad_impl(blco_tensor* t, const void* const* factors, int factor_d
     return BLCO_OK;
   }
   GradArgs g;
-  g.m0 = -1;
-  for (int m = 0; m < N && g.m0 < 0; ++m)
-    if (fused_mode_ok(t, m, rank, factor_dtype)) g.m0 = m;
+  g.m0 = fused_mode(t, rank, factor_dtype);
   g.scale = (float)(-alpha);
   g.scale_dev = scale;
   g.resid = residual;
@@ -2327,6 +2379,26 @@ extern "C" int blco_workspace(const blco_tensor* t, int mode, int rank, int fact
       most = std::max(most, mode_workspace(t, m, rank, factor_dtype, true, t->nnz));
   }
   *bytes = (most + 255) / 256 * 256;
+  return BLCO_OK;
+}
+
+extern "C" int blco_stream_plan(const blco_tensor* t, unsigned modes, int gradient, int rank,
+                                int factor_dtype, size_t device_budget_bytes,
+                                size_t workspace_bytes, size_t* used, int64_t* chunk_nnz) {
+  clear_error();
+  if (!t || !used || !chunk_nnz) return set_error(BLCO_EINVAL, "tensor, used or chunk_nnz is NULL");
+  if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
+  if (factor_dtype != BLCO_F32 && factor_dtype != BLCO_BF16)
+    return set_error(BLCO_EINVAL, "factor dtype %d", factor_dtype);
+  const unsigned all = (1u << t->lay.N) - 1;
+  if (gradient) modes = all;
+  if (!modes || (modes & ~all)) return set_error(BLCO_EINVAL, "modes 0x%x", modes);
+  StreamPlan p;
+  int rc = plan_stream(t, modes, gradient != 0, rank, factor_dtype, device_budget_bytes,
+                       workspace_bytes, &p);
+  if (rc) return rc;
+  *used = p.ws;
+  *chunk_nnz = p.cap;
   return BLCO_OK;
 }
 

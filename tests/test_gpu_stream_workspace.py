@@ -1,0 +1,66 @@
+"""Streamed calls whose launches use a workspace, under budgets around what it takes: the chunks are
+as large as without one (or an eighth smaller), the results are those of the call in memory, and
+what torch lends plus what the library holds stays within the budget."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2201_12523_amd as blco  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("kind", ["all", "one", "gradient"])
+@pytest.mark.parametrize("R", [10, 35])
+def test_budget(kind, R):
+    dims, nnz = (3000, 2000, 900), 1_500_000
+    g = torch.Generator(device=DEV)
+    g.manual_seed(R)
+    coords = [torch.randint(0, d, (nnz,), generator=g, device=DEV, dtype=torch.int32) for d in dims]
+    vals = torch.rand(nnz, generator=g, device=DEV)
+    F = [torch.rand(d, R, generator=g, device=DEV) for d in dims]
+    t = blco.build_device(coords, vals, dims, placement="pinned")
+    mem = blco.build_device(coords, vals, dims)
+    per = 16 if kind == "gradient" else 12
+    if kind == "gradient":
+        loss, want, _ = blco.cp_grad(mem, F)
+    else:
+        want = [blco.mttkrp(mem, m, F) for m in range(3)]
+    outs = [torch.empty(d, R, device=DEV) for d in dims]
+    fixed = t.info()["device_bytes"] + sum(dims) * R * 4 + (dims[0] if kind == "one" else sum(dims)) * R * 4
+    if kind == "one":
+        fixed -= dims[0] * R * 4        # its own factor is not read
+    most = max(t.plan(m, R, use=u)["workspace_bytes"] for m in range(3) for u in ("mttkrp", "residual"))
+    for extra in (2 * 300_000 * per, most + 2 * 64 * per + 1, most + 2 * 300_000 * per,
+                  2 * nnz * per, 1 << 30):
+        budget = fixed + extra
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_allocated()
+        torch.cuda.reset_peak_memory_stats()
+        if kind == "all":
+            got = blco.mttkrp_stream_all(t, F, outs=outs, device_budget=budget)
+        elif kind == "one":
+            got = [blco.mttkrp_stream(t, 0, F, out=outs[0], device_budget=budget)]
+        else:
+            l, got, _ = blco.cp_grad(t, F, grads=outs, device_budget=budget)
+            assert abs(float(l) - float(loss)) <= 1e-6 * float(loss)
+        lent = torch.cuda.max_memory_allocated() - before
+        inf = t.info()
+        chunk = inf["stream_chunk_nnz"]
+        alone = max(64, min(extra // 2 // per, -(-nnz // 64) * 64) // 64 * 64)
+        assert chunk >= alone * 7 // 8 - 64
+        # torch rounds a block up to 512 bytes, and the gradient's loss is one more
+        assert fixed + 2 * chunk * per + lent <= budget + 1024
+        assert inf["stream_peak_bytes"] <= budget
+        assert inf["stream_peak_bytes"] + 1024 >= fixed + 2 * chunk * per + lent
+        for a, b in zip(got, want[:1] if kind == "one" else want):
+            # positive terms: each side within the parity bound of 1e-5 of the sum; the gradient's
+            # terms change sign, so by the largest entry, with the residual's rounding
+            if kind == "gradient":
+                assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+            else:
+                assert float(((a - b).abs() - 2.1e-5 * b).max()) <= 0

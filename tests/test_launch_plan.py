@@ -57,3 +57,45 @@ def test_padded_output_is_bounded(R):
                 assert rows * p["out_stride"] <= (1 << 32) - 16
                 assert p["workspace_bytes"] <= 2 << 30
     assert padded
+
+
+# a call under a budget: the staging comes first, and the workspace fits what is left (or takes at
+# most an eighth), whatever the budget is over what the call cannot do without
+@pytest.mark.parametrize("gradient", [0, 1])
+@pytest.mark.parametrize("R", [10, 35, 64])
+def test_workspace_under_a_budget(R, gradient):
+    import ctypes
+
+    dims, nnz = (3000, 2000, 900), 1_500_000
+    t = host_tensor(dims, nnz)
+    fixed, per = sum(dims) * R * 8, 12 + 4 * gradient
+
+    def plan(extra, lent=1 << 62):
+        used, chunk = ctypes.c_size_t(), ctypes.c_int64()
+        rc = blco.lib().blco_stream_plan(t.handle, 7, gradient, R, blco.F32, fixed + extra, lent,
+                                         ctypes.byref(used), ctypes.byref(chunk))
+        return rc, used.value, chunk.value
+
+    whole = -(-nnz // 64) * 64
+    rc, most, chunk = plan(1 << 33)
+    assert rc == 0 and chunk == whole and (most > 0) == (R % 16 != 0)
+    rc, used, chunk = plan(1 << 33, 1000)
+    assert rc == 0 and used <= 1000 and chunk == whole
+    assert plan(2 * 64 * per - 1)[0] == -2
+    used_some = 0
+    for extra in ([2 * n * per for n in (64, 65, 1000, 1 << 17, 1 << 18, 300_000, 700_000, 1_200_000)]
+                  + [most + 2 * 64 * per - 1, most + 2 * 64 * per, most + 2 * 64 * per + 1]
+                  + [2 * whole * per + d for d in (-1, 0, most - 1, most, most + 1)]):
+        if extra < 2 * 64 * per:
+            continue
+        rc, used, chunk = plan(extra)
+        assert rc == 0 and used + 2 * chunk * per <= extra
+        alone = max(64, min(extra // 2 // per, whole) // 64 * 64)   # the staging without a workspace
+        assert chunk == alone or (used <= extra // 8 and chunk >= alone * 7 // 8 - 64)
+        if used:
+            # a launch over such a chunk uses it
+            assert max(t.plan(m, R, use=u, nnz=chunk)["workspace_bytes"] for m in range(3)
+                       for u in ("mttkrp", "residual")[:1 + gradient]) >= used
+            used_some += 1
+        assert plan(extra, used)[1] == used
+    assert used_some or R % 16 == 0
