@@ -1417,6 +1417,74 @@ static int upload(T** dst, const T* src, size_t count, size_t* acc) {
   return BLCO_OK;
 }
 
+// The copies of streamed calls queued on one stream follow one another: a call's copies start
+// after those of the call queued there before it.  Its kernels come after that call's anyway, so
+// nothing completes later for the wait; but where two tensors are streamed in turn, each through
+// its own copy stream, their copies otherwise share the host link, which then moves less, and the
+// first call's kernels start late (two tensors of 20M non-zeros, 240 MB each: 6.2 ms per copy
+// instead of 4.2, 4.44 instead of 4.36 ms per call).  The last copies of the streams most
+// recently used, kept while any tensor has been streamed.
+struct LastCopies {
+  struct Entry {
+    int dev;
+    hipStream_t s;
+    hipEvent_t done;
+    uint64_t used;
+  };
+  static constexpr size_t kMost = 16;
+  std::mutex mu;
+  std::vector<Entry> e;
+  uint64_t calls = 0;
+  int tensors = 0;
+
+  Entry* find(int dev, hipStream_t s) {
+    for (Entry& x : e)
+      if (x.dev == dev && x.s == s) return &x;
+    return nullptr;
+  }
+  // copies queued on cs from now on wait for the last ones of calls on s
+  hipError_t follow(int dev, hipStream_t s, hipStream_t cs) {
+    std::lock_guard<std::mutex> lock(mu);
+    const Entry* x = find(dev, s);
+    return x ? hipStreamWaitEvent(cs, x->done, 0) : hipSuccess;
+  }
+  // what has been queued on cs are the last copies of calls on s
+  hipError_t mark(int dev, hipStream_t s, hipStream_t cs) {
+    std::lock_guard<std::mutex> lock(mu);
+    Entry* x = find(dev, s);
+    if (!x) {
+      if (e.size() >= kMost) {
+        auto old = std::min_element(e.begin(), e.end(), [](const Entry& a, const Entry& b) {
+          return a.used < b.used;
+        });
+        (void)hipEventDestroy(old->done);
+        e.erase(old);
+      }
+      hipEvent_t ev;
+      hipError_t rc = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+      if (rc != hipSuccess) return rc;
+      e.push_back({dev, s, ev, 0});
+      x = &e.back();
+    }
+    x->used = ++calls;
+    return hipEventRecord(x->done, cs);
+  }
+  void add() {
+    std::lock_guard<std::mutex> lock(mu);
+    ++tensors;
+  }
+  void drop() {
+    std::lock_guard<std::mutex> lock(mu);
+    if (--tensors > 0) return;
+    for (Entry& x : e) (void)hipEventDestroy(x.done);
+    e.clear();
+  }
+};
+static LastCopies& last_copies() {
+  static LastCopies* l = new LastCopies;   // outlives every tensor freed at exit
+  return *l;
+}
+
 static void release_device(blco_tensor* t) {
   StreamState& st = t->st;
   if (st.copy_stream) {
@@ -1436,7 +1504,10 @@ static void release_device(blco_tensor* t) {
     if (st.ev_ready[i]) (void)hipEventDestroy((hipEvent_t)st.ev_ready[i]);
     if (st.ev_free[i]) (void)hipEventDestroy((hipEvent_t)st.ev_free[i]);
   }
-  if (st.copy_stream) (void)hipStreamDestroy((hipStream_t)st.copy_stream);
+  if (st.copy_stream) {
+    (void)hipStreamDestroy((hipStream_t)st.copy_stream);
+    last_copies().drop();
+  }
   st = StreamState();
   for (void* q : {(void*)t->d_keys, (void*)t->d_vals, (void*)t->d_run_start, (void*)t->d_run_base,
                   (void*)t->d_tile_run, (void*)t->d_partials, (void*)t->d_hot, (void*)t->d_tab,
@@ -1907,6 +1978,7 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     hipStream_t cs;
     HIPCHK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     st.copy_stream = cs;
+    last_copies().add();
     for (int i = 0; i < 2; ++i) {
       hipEvent_t e1, e2;
       HIPCHK(hipEventCreateWithFlags(&e1, hipEventDisableTiming));
@@ -1954,6 +2026,7 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     st.ev_t.push_back(e);
   }
   st.timed_chunks = 0;
+  HIPCHK(last_copies().follow(t->device, s, (hipStream_t)st.copy_stream));
   int64_t chunks = 0;
   for (int64_t lo = 0; lo < t->nnz; lo += cap, ++chunks) {
     const int b = (int)(chunks & 1);
@@ -1987,6 +2060,7 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     HIPCHK(hipEventRecord(ev[3], s));
     HIPCHK(hipEventRecord((hipEvent_t)st.ev_free[b], s));
   }
+  HIPCHK(last_copies().mark(t->device, s, (hipStream_t)st.copy_stream));
   if (grad) {
     hipLaunchKernelGGL(k_reduce_loss, dim3(1), dim3(1024), 0, s, (const double*)t->d_partials,
                        poff, grad->loss);
