@@ -79,7 +79,8 @@ class _Plan(ctypes.Structure):
     _fields_ = [(k, ctypes.c_int) for k in
                 ("resolution", "lanes", "ranks_per_lane", "window", "wpt", "stash_rows", "copies",
                  "wide", "vector_gathers", "factor_stride", "out_stride", "grouped")] + [
-                    ("workgroups", ctypes.c_int64), ("workspace_bytes", ctypes.c_size_t)]
+                    ("workgroups", ctypes.c_int64), ("workspace_bytes", ctypes.c_size_t),
+                    ("flushes", ctypes.c_double * 2)]
 
 
 def library_path() -> str:
@@ -257,7 +258,9 @@ class BLCOTensor:
                                {"mttkrp": 0, "residual": 1, "als": 2}[use], int(nnz),
                                (1 << 62) if workspace is None else int(workspace),
                                ctypes.byref(pl)))
-        return {k: getattr(pl, k) for k, _ in _Plan._fields_}
+        out = {k: getattr(pl, k) for k, _ in _Plan._fields_}
+        out["flushes"] = tuple(pl.flushes)
+        return out
 
     def export(self):
         """(keys uint64, values float32, block_ids uint64, block_starts int64) on the host."""

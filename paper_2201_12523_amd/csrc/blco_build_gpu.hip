@@ -291,15 +291,16 @@ struct StageEvents {
 
 // Device memory of one build: taken in turn from the block the caller lends, and
 // allocated where that has no room (released on every return path).  reuse() starts over
-// in the block: what was taken before is dead for work queued from then on.
+// in the block: what was taken since keep() is dead for work queued from then on.
 struct Pool {
   std::vector<void*> ptrs;
   char* block = nullptr;
-  size_t bytes = 0, at = 0;
+  size_t bytes = 0, at = 0, kept = 0;
   ~Pool() {
     for (void* p : ptrs) (void)hipFree(p);
   }
-  void reuse() { at = 0; }
+  void keep() { kept = at; }
+  void reuse() { at = kept; }
   template <typename T>
   int get(T** out, size_t count) {
     const size_t need = std::max<size_t>(count, 1) * sizeof(T);
@@ -462,6 +463,9 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
   uint32_t *h32 = nullptr, *h32s = nullptr, *h32f = nullptr, *vs = nullptr, *tv2 = nullptr;
   LinResult* res;
   uint64_t *d_dep, *d_enc;
+  uint32_t* counts;
+  if ((rc = pool.get(&counts, 2 * BLCO_MAX_MODES))) return rc;
+  pool.keep();
   if ((rc = pool.get(&res, 1)) || (rc = pool.get(&d_dep, (size_t)L.N * 4 * 256 * 2)) ||
       (rc = pool.get(&d_enc, (size_t)kEncBytes * 256)) || (rc = pool.get(&lo, nnz)) ||
       (rc = pool.get(&lo2, nnz)) || (blocked && (rc = pool.get(&bkey, nnz))))
@@ -590,6 +594,10 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
     HIPCHK(hipStreamSynchronize(s));
   }
   finish_runs(L, nnz, run_start, run_key, cap, t, false);
+  // the row flushes of sampled windows, where they need no run tables (a copy between pageable
+  // memory and the device waits for the stream: the tables go up, and the counts come back, after
+  // the frequent rows)
+  if (!blocked && (rc = count_flushes_device(t, counts, s))) return rc;
   // 5. frequent rows
   stage.mark(4, s);
   pool.reuse();
@@ -609,10 +617,13 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
                        t->d_tile_run);
     HIPCHK(hipGetLastError());
   }
+  if (blocked && (rc = count_flushes_device(t, counts, s))) return rc;
   if (t->placement == BLCO_PLACE_DEVICE &&
       (rc = home.get(&t->d_group, (size_t)L.N * kGroupBuckets, &acc)))
     return rc;
   t->device_bytes = acc;
+  if (nnz > 0)
+    HIPCHK(hipMemcpyAsync(t->flush_rows, counts, sizeof(t->flush_rows), hipMemcpyDeviceToHost, s));
   if (t->placement == BLCO_PLACE_DEVICE && (rc = make_groups(t, s))) return rc;
   HIPCHK(hipStreamSynchronize(s));
   stage.read(t->build_stage_ms);
@@ -626,7 +637,7 @@ size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 size_t build_workspace(const Layout& L, int64_t nnz) {
   const size_t n = (size_t)std::max<int64_t>(nnz, 1);
   const bool wide = L.T > 64, mid = wide && L.T <= 96;
-  size_t a = 1024 + up256((size_t)L.N * 4 * 256 * 16) + up256((size_t)kEncBytes * 256 * 8);
+  size_t a = 2048 + up256((size_t)L.N * 4 * 256 * 16) + up256((size_t)kEncBytes * 256 * 8);
   a += 2 * up256(8 * n);                                     // lo, lo2
   a += up256(8 * n) + up256(4 * n) + up256(4 * sort_workspace_words(nnz));   // spares
   if (wide) a += 2 * up256(4 * n);
@@ -638,7 +649,7 @@ size_t build_workspace(const Layout& L, int64_t nnz) {
   const size_t b = 8 * up256(4 * smp) + up256(smp) + up256(8 * smp) +
                    up256(4 * std::max(sort_workspace_words((int64_t)smp),
                                       select_workspace_words((int64_t)smp)));
-  return std::max(a, b);
+  return std::max(a, b + 256);   // the flush counts are kept through both
 }
 
 // Storage of a tensor's arrays (the run tables of a blocked tensor, whose size the data
@@ -724,6 +735,7 @@ static int build_device_impl(int nmodes, const uint64_t* dims, int64_t nnz,
     }
   }
   if (rc != BLCO_OK) {
+    (void)hipStreamSynchronize(s);   // copies into the tensor may be under way
     release_tensor_arrays(t);
     delete t;
     return rc;

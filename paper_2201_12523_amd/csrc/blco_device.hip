@@ -121,6 +121,45 @@ __global__ __launch_bounds__(256) void k_unpad(const float* __restrict__ src, in
   }
 }
 
+// Distinct rows of mode blockIdx.y in sampled window blockIdx.x (flush_start), into counts[m][0] (the
+// window's first half) and counts[m][1]: a set of rows in LDS, at most half full.
+__global__ __launch_bounds__(1024) void k_flushes(KParams p, uint32_t* __restrict__ counts) {
+  constexpr uint32_t kSlots = 2 * kFlushWindow;
+  __shared__ uint32_t s_slot[kSlots];
+  __shared__ uint32_t s_n[2];
+  const int m = (int)blockIdx.y, N = (int)gridDim.y;
+  const int64_t k0 = flush_start(p.n, (int)blockIdx.x);
+  for (uint32_t i = threadIdx.x; i < kSlots; i += 1024) s_slot[i] = 0xFFFFFFFFu;
+  if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    for (int i = threadIdx.x; i < kFlushWindow / 2; i += 1024) {
+      const int64_t k = k0 + half * (kFlushWindow / 2) + i;
+      if (k >= p.n) break;
+      uint32_t row = (uint32_t)(p.keys[k] >> p.shift[m]) & p.mask[m];
+      if (p.multi) {
+        int run = p.tile_run[k >> 6];
+        while (k >= p.run_start[run + 1]) ++run;
+        row |= p.run_base[(size_t)run * N + m];
+      }
+      if (row == 0xFFFFFFFFu) row = 0xFFFFFFFEu;   // the empty slot's mark
+      uint32_t h = (row * 0x9E3779B1u) >> 19;      // 13 bits: kSlots
+      for (uint32_t probe = 0; probe < kSlots; ++probe) {
+        const uint32_t was = atomicCAS(&s_slot[h], 0xFFFFFFFFu, row);
+        if (was == 0xFFFFFFFFu) {
+          if (half == 0) atomicAdd(&s_n[0], 1u);
+          atomicAdd(&s_n[1], 1u);
+        }
+        if (was == 0xFFFFFFFFu || was == row) break;
+        h = (h + 1) & (kSlots - 1);
+      }
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x < 2) atomicAdd(&counts[2 * m + threadIdx.x], s_n[threadIdx.x]);
+}
+
 // Bucket of a target row: equal ranges of rows.
 __device__ __forceinline__ uint32_t group_bucket(uint32_t row, uint32_t mul) {
   return (uint32_t)(((uint64_t)row * mul) >> 32);
@@ -936,12 +975,16 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
 // save, in row flushes and in the chain of same-row flushes of a skewed mode: 250k power-law
 // non-zeros at R = 16 take 23, 17, 13 and 18 us in windows of 256, 512, 1024 and 2048.
 //
-// At R > 32 a window of 2048 leaves two workgroups per CU and is the faster where rows
-// repeat (5M non-zeros of 2000 x 1000 x 500, R = 64: 0.13 and 0.18 ms per mode; 5 modes,
-// R = 35: 0.30 and 0.41 ms); one of 4096 merges more where they do not, on flat modes with an
-// expected 0.3 flushes per non-zero or more (50M non-zeros of 2^24 x 2^22 x 2^20 x 2^10,
-// R = 64 bf16, its last two: 4.37 and 2.80 ms in windows of 2048, 3.83 and 2.48 ms) unless
-// their non-zeros were grouped (20M of 200003 x 100003 x 50021, the same: 2.64 and 3.15 ms).
+// At R > 32 a window of 2048 leaves two workgroups per CU; one of 4096 merges more.  It pays on a
+// mode without frequent rows where it saves wide_saves(N) row flushes per non-zero (counted at
+// construction: the rows a window holds follow from how the non-zeros lie, and an estimate from
+// the mode lengths was several times off on skewed tensors).  Windows of 2048 and 4096, us per mode,
+// by the flushes saved.  8M non-zeros of 21007 x 9001 x 1501 x 367, R = 64: 0.079: 575 and 509;
+// 0.096: 517 and 455; 0.105: 473 and 429; 0.075: 383 and 379; 50M of 2^24 x 2^22 x 2^20 x 2^10, R =
+// 64 bf16: 0.073: 4370 and 3830; 0.101: 2800 and 2480; 2000 x 1000 x 500: 0.024: 188 and 258; 0.012:
+// 164 and 233.  Five modes, whose records are half as long again, 8M, R = 64: 0.091: 447 and 449;
+// 0.068: 374 and 401; 0.059: 360 and 388; 2M: 0.100: 159 and 144.  Grouped non-zeros repeat their
+// rows in 2048 already (20M of 200003 x 100003 x 50021, R = 64 bf16: 2.64 and 3.15 ms).
 //
 // careful: CP-ALS multiplies the sums by V^+ (condition number about 1e3 on a planted model),
 // which turns their last bits into its factors' fifth digit, so its updates keep one order of
@@ -949,6 +992,7 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
 // at R > 32).  1M power-law non-zeros, R = 16, 5 iterations, over 48 inputs: two runs of this
 // route leave the third factor 7e-5 apart in norm, the routes below move it by 1.4e-4; time 1.24
 // against 1.15 ms.
+static double wide_saves(int N) { return N <= 4 ? 0.05 : 0.095; }
 static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n, bool careful) {
   if (R > 64 || N > kWideMaxN) return 1;
   if (careful) return R > 32 ? 4 : 2;
@@ -1044,6 +1088,12 @@ static double window_flushes(const blco_tensor* t, int mode, double W, double n)
   return rows * -expm1(-W / rows) / W;
 }
 
+// Row flushes per non-zero of mode `mode` in windows of kFlushWindow / 2 (half 0) and kFlushWindow
+// (half 1) non-zeros, as counted at construction.
+static double flushes(const blco_tensor* t, int mode, int half) {
+  return t->flush_nnz[half] > 0 ? (double)t->flush_rows[mode][half] / (double)t->flush_nnz[half] : 0;
+}
+
 // The window kernel a launch over n non-zeros takes: its instantiation, windows, frequent
 // rows in LDS and the slots of their look-up table.
 struct WinPlan {
@@ -1073,7 +1123,7 @@ static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int ranks, int
   };
   const bool frequent = has_frequent_rows(t, mode);
   const bool flat = !frequent && !grouped &&
-                    window_flushes(t, mode, 2048.0, (double)t->nnz) >= 0.3;
+                    flushes(t, mode, 0) - flushes(t, mode, 1) >= wide_saves(N);
   WinPlan w = {nullptr, win_wpt(N, gather, resid, big, flat, n, careful), 0, 0, 0, 0};
   // one non-zero per thread (the residual walk at N = 5): -1 is the form with copies
   const int lw = w.wpt == 1 ? -1 : w.wpt;
@@ -1163,16 +1213,26 @@ static_assert(kPadMax / sizeof(float) <= kIndexMax, "padded outputs keep 32-bit 
 // 200003 x 100003, all modes, as they lie and moved: R = 32: 1164 and 575 us; R = 48: 1747 and
 // 990; R = 100: 4459 and 2106, bf16 4396 and 1561; R = 16 is left as it is (flushes of one
 // line: 0.19 ms per mode).  20M of 200003 x 100003 x 50021, bf16 R = 64: 9144 and 2638.
+//
+// That is asked of the flushes non-zeros spread evenly would make; those counted at construction
+// have to be worth the move too (1.2 times), since skewed modes beside a flat one keep its windows
+// on few rows: 30M of 50000 x 30000 x 20000, the uniform mode beside two power-law ones, make 0.16
+// flushes per non-zero, not 0.5: R = 32: 610 us as they lie and 650 moved; R = 64: 1205 and 918;
+// R = 128: 2648 and 1492.
 static bool group_pays(const blco_tensor* t, int mode, int rank, int64_t n) {
   if (!t->d_group || !t->grouped[mode] || n != t->nnz) return false;
   const double W = rank > 64 ? 1024 : 2048, N = (double)n;
   const double lines = ceil(rank / 16.0) + (rank % 16 ? 0.5 : 0.0);
-  const double now = window_flushes(t, mode, rank > 32 && rank <= 64 ? 4096 : W, N);
+  const double even = window_flushes(t, mode, rank > 32 && rank <= 64 ? 4096 : W, N);
+  const double half = flushes(t, mode, 0), whole = flushes(t, mode, 1);
+  const double now = rank > 32 && rank <= 64 && half - whole >= wide_saves(t->lay.N) ? whole : half;
   // in bucket order: W non-zeros of the rows of W / (n / buckets) buckets, at least one
   const double per = N / kGroupBuckets, I = (double)t->lay.dims[mode];
   const double rows = std::max(1.0, I / kGroupBuckets * std::max(1.0, W / per));
-  const double then = std::min(now, rows * -expm1(-W / rows) / W + 1.0 / per);
-  return N * (now - then) * lines * 52e-12 > 2 * (20e-6 + N * 18e-12);
+  const double then = rows * -expm1(-W / rows) / W + 1.0 / per;
+  const double move = 20e-6 + N * 18e-12;
+  return N * (even - std::min(even, then)) * lines * 52e-12 > 2 * move &&
+         N * (now - std::min(now, then)) * lines * 52e-12 > 1.2 * move;
 }
 
 // How a call runs: padded factors (their row stride, 0: as they are) and output rows,
@@ -1524,6 +1584,23 @@ static void release_device(blco_tensor* t) {
   t->d_partials = nullptr;
 }
 
+int blco::count_flushes_device(blco_tensor* t, uint32_t* counts, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  memset(t->flush_rows, 0, sizeof(t->flush_rows));
+  flush_sizes(t->nnz, t->flush_nnz);
+  if (t->nnz <= 0) return BLCO_OK;
+  int rc = fill_zero(reinterpret_cast<float*>(counts), 2 * BLCO_MAX_MODES, s);
+  if (rc) return rc;
+  KParams p;
+  fill_params(t, &p);
+  p.keys = t->d_keys;
+  p.n = t->nnz;
+  hipLaunchKernelGGL(k_flushes, dim3((unsigned)flush_windows(t->nnz), (unsigned)t->lay.N), dim3(1024), 0,
+                     s, p, counts);
+  HIPCHK(hipGetLastError());
+  return BLCO_OK;
+}
+
 // Counts the buckets of the modes k_group may serve: flat modes of a device tensor of one run
 // without block-key bits, long enough to have several rows per bucket, whose windows hardly
 // repeat a row.
@@ -1532,14 +1609,21 @@ int blco::make_groups(blco_tensor* t, void* stream) {
   if (!t->d_keys || t->nnz < kGroupMinNnz || t->nnz >= ((int64_t)1 << 32) ||
       t->run_start.size() != 2 || L.S > 0)
     return BLCO_OK;
+  auto flat = [&](int m) {
+    return L.dims[m] >= 4 * (uint64_t)kGroupBuckets && !has_frequent_rows(t, m) &&
+           window_flushes(t, m, 2048.0, (double)t->nnz) >= 0.4;
+  };
   bool any = false;
+  for (int m = 0; m < L.N; ++m) any = any || flat(m);
+  if (!any) return BLCO_OK;
+  hipStream_t s = (hipStream_t)stream;
+  HIPCHK(hipStreamSynchronize(s));   // the counted flushes
+  any = false;
   for (int m = 0; m < L.N; ++m) {
-    t->grouped[m] = L.dims[m] >= 4 * (uint64_t)kGroupBuckets && !has_frequent_rows(t, m) &&
-                    window_flushes(t, m, 2048.0, (double)t->nnz) >= 0.4;
+    t->grouped[m] = flat(m) && flushes(t, m, 0) >= 0.1;   // fewer never pay (group_pays)
     any = any || t->grouped[m];
   }
   if (!any) return BLCO_OK;
-  hipStream_t s = (hipStream_t)stream;
   if (!t->d_group) {
     const size_t bytes = sizeof(uint32_t) * (size_t)L.N * kGroupBuckets;
     HIPCHK(hipMalloc((void**)&t->d_group, bytes));
@@ -1600,6 +1684,7 @@ extern "C" int blco_build(int nmodes, const uint64_t* dims, int64_t nnz,
   }
   find_hot_rows(coords, nnz, hot_min, t);
   make_row_tables(t);
+  count_flushes(t);
   t->hot_forced = hot_forced;
   if (placement == BLCO_PLACE_HOST) {
     *out = t;
@@ -2418,6 +2503,7 @@ extern "C" int blco_plan(const blco_tensor* t, int mode, int rank, int factor_dt
   plan->out_stride = L.cp.out;
   plan->grouped = L.cp.group;
   plan->workspace_bytes = L.cp.bytes;
+  for (int h = 0; h < 2; ++h) plan->flushes[h] = flushes(t, mode, h);
   plan->vector_gathers = factor_dtype == BLCO_BF16 && L.stride % 2 == 0;
   if (L.res != BLCO_RES_REGISTER) {
     plan->wide = L.big;

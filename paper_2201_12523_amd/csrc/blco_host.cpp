@@ -432,6 +432,35 @@ void make_row_tables(blco_tensor* t) {
   }
 }
 
+void count_flushes(blco_tensor* t) {
+  const Layout& L = t->lay;
+  memset(t->flush_rows, 0, sizeof(t->flush_rows));
+  flush_sizes(t->nnz, t->flush_nnz);
+  constexpr uint32_t kSlots = 2 * kFlushWindow;
+  std::vector<uint64_t> slot(kSlots);
+  for (int i = 0; i < flush_windows(t->nnz); ++i) {
+    const int64_t k0 = flush_start(t->nnz, i);
+    const int64_t k1 = std::min<int64_t>(t->nnz, k0 + kFlushWindow);
+    for (int m = 0; m < L.N; ++m) {
+      const uint64_t mask = (1ULL << L.w[m]) - 1;
+      std::fill(slot.begin(), slot.end(), ~0ULL);
+      size_t r = std::upper_bound(t->run_start.begin(), t->run_start.end(), k0) -
+                 t->run_start.begin() - 1;
+      for (int64_t k = k0; k < k1; ++k) {
+        while (k >= t->run_start[r + 1]) ++r;
+        const uint64_t row =
+            (L.w[m] ? (t->h_keys[k] >> L.s[m]) & mask : 0) | t->run_base[r * L.N + m];
+        uint32_t h = ((uint32_t)row * 0x9E3779B1u) >> 19;   // 13 bits: kSlots
+        while (slot[h] != ~0ULL && slot[h] != row) h = (h + 1) & (kSlots - 1);
+        if (slot[h] == row) continue;
+        slot[h] = row;
+        if (k - k0 < kFlushWindow / 2) ++t->flush_rows[m][0];
+        ++t->flush_rows[m][1];
+      }
+    }
+  }
+}
+
 void free_host_arrays(blco_tensor* t) {
   if (t->host_free) {
     if (t->h_keys) t->host_free(t->h_keys);

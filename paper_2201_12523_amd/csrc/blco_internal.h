@@ -20,6 +20,10 @@ constexpr int64_t kGroupMinNnz = 1 << 20;      // fewer non-zeros are never grou
 constexpr int kTabBits = 9;
 constexpr int kTabSlots = 1 << kTabBits;
 constexpr int kTabWords = 1 + kTabSlots + kTabSlots / 4;
+// Windows sampled for a mode's row flushes: at most this many, evenly spaced, of kFlushWindow
+// non-zeros each; their first halves give the flushes of windows half as long.
+constexpr int kFlushSamples = 64;
+constexpr int kFlushWindow = 4096;
 constexpr int64_t kHotMinCount = 2048;  // default: a frequent row holds at least this many non-zeros
 
 // The bit map of a tensor (Sections 4.1-4.2).
@@ -97,6 +101,10 @@ struct blco_tensor {
   uint32_t* d_hot = nullptr;
   std::vector<uint32_t> tab;         // N * kTabWords: row tables of the frequent rows
   uint32_t* d_tab = nullptr;
+  // distinct rows of each mode over the sampled windows of kFlushWindow / 2 and kFlushWindow
+  // non-zeros, and the non-zeros in them
+  uint32_t flush_rows[BLCO_MAX_MODES][2] = {};
+  int64_t flush_nnz[2] = {0, 0};
   // grouped MTTKRP: first non-zero of each bucket of a mode (N * kGroupBuckets), and the
   // multiplier that gives a row's bucket
   uint32_t* d_group = nullptr;
@@ -147,7 +155,31 @@ int mttkrp_careful(blco_tensor* t, int mode, const void* const* factors, int fac
                    int rank, float* out, void* ws, size_t ws_bytes, void* stream);
 size_t mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype);
 
-// Bucket counts for the grouped MTTKRP, queued on `stream` (a hipStream_t).
+// Sampled windows of n non-zeros: their number and the first non-zero of the i-th (whole windows;
+// a shorter tensor is one).
+constexpr int flush_windows(int64_t n) {
+  return n < kFlushWindow ? (n > 0 ? 1 : 0)
+                          : n / kFlushWindow < kFlushSamples ? (int)(n / kFlushWindow) : kFlushSamples;
+}
+constexpr int64_t flush_start(int64_t n, int i) {
+  return flush_windows(n) > 1
+             ? (n / kFlushWindow - 1) * i / (flush_windows(n) - 1) * kFlushWindow : 0;
+}
+inline void flush_sizes(int64_t n, int64_t (&nnz)[2]) {
+  for (int h = 0; h < 2; ++h) {
+    const int64_t w = kFlushWindow / (2 - h);
+    nnz[h] = flush_windows(n) * (n < w ? n : w);
+  }
+}
+
+// Counts the distinct rows of the sampled windows (t->flush_rows): on the host from the host
+// arrays, or on the device from d_keys and the run tables there, into `counts` (device,
+// sizeof(flush_rows) bytes), queued on `stream`.
+void count_flushes(blco_tensor* t);
+int count_flushes_device(blco_tensor* t, uint32_t* counts, void* stream);
+
+// Bucket counts for the grouped MTTKRP, queued on `stream` (a hipStream_t), which it waits for
+// first where the counted flushes decide.
 int make_groups(blco_tensor* t, void* stream);
 
 // Device sorting and compaction of the GPU builder (blco_sort.hip), ordered on

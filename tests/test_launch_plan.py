@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2201_12523_amd as blco
+from oracle import encode
 
 u64 = np.uint64
 
@@ -99,3 +100,28 @@ def test_workspace_under_a_budget(R, gradient):
             used_some += 1
         assert plan(extra, used)[1] == used
     assert used_some or R % 16 == 0
+
+
+def counted(t, dims, key_bits):
+    """Distinct rows per non-zero over the sampled windows, from the exported tensor as the oracle
+    decodes it."""
+    keys, _, ids, starts = t.export()
+    coords = encode.decode(keys, ids, starts, encode.layout(dims, key_bits))
+    n = keys.size
+    k = max(1, min(64, n // 4096))
+    first = [0] if k == 1 else [(n // 4096 - 1) * i // (k - 1) * 4096 for i in range(k)]
+    return [tuple(sum(np.unique(c[a:min(n, a + W)]).size for a in first) /
+                  sum(min(n, a + W) - a for a in first) for W in (2048, 4096)) for c in coords]
+
+
+@pytest.mark.parametrize("dims,nnz,key_bits", [((300, 200, 70), 1, 64), ((300, 200, 70), 2047, 64),
+                                               ((300, 200, 70), 4097, 64), ((3000, 2000, 900), 100_000, 64),
+                                               ((3000, 2000, 900, 5), 600_000, 64), ((7, 5), 30, 64),
+                                               ((3000, 2000, 900), 300_000, 31)])
+def test_counted_flushes(dims, nnz, key_bits):
+    rng = np.random.default_rng(nnz)
+    coords = [np.minimum(rng.zipf(1.5, nnz) - 1, d - 1).astype(np.uint32) if m == 0 else
+              rng.integers(0, d, nnz).astype(np.uint32) for m, d in enumerate(dims)]
+    t = blco.build(coords, np.ones(nnz, np.float32), dims, placement="host", key_bits=key_bits)
+    for m, want in enumerate(counted(t, dims, key_bits)):
+        assert t.plan(m, 32)["flushes"] == pytest.approx(want, abs=1e-12), m
