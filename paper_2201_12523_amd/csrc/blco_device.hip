@@ -1055,12 +1055,16 @@ static bool has_frequent_rows(const blco_tensor* t, int mode) {
 constexpr int64_t kCopyMinWindows = 2048;
 constexpr int kCopyMax = 64;   // most copies of a row
 
-// Copies of each frequent row: at most about 4096 additions to one (the sums are then no
-// further from 64 bits than with the full stash, measured on the 50M- and 200M-non-zero
-// power-law tensors; more copies cost more to clear and add up).
+// Copies of each frequent row: at most about kChain additions to one, up to kCopyMax copies (launches
+// of 67M non-zeros; 200M put 1526 additions on a copy).  The full stash made a chain of 512 to
+// 2048 additions of a row, one per workgroup.  Error from 64 bits of a mode's output (norm), 3-mode
+// power-law non-zeros, R = 16, with the stash, at most 4096 additions and at most 512: 8M: 6.2e-7,
+// 6.6e-7, 3.1e-7; 16M: 6.1e-7, 6.6e-7, 3.3e-7; 50M, the last two: 6.1e-7, 4.2e-7; and 8M take 141
+// us per mode instead of 157, as same-row atomics wait for each other.
+constexpr int64_t kChain = 512;
 static int copy_count(int64_t nwin) {
   int c = 1;
-  while (c < kCopyMax && (int64_t)c * 4096 < nwin) c *= 2;
+  while (c < kCopyMax && c * kChain < nwin) c *= 2;
   return c;
 }
 

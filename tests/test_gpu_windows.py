@@ -121,3 +121,22 @@ def test_workspace_errors():
     assert L.blco_mttkrp_ws(*args(ws.data_ptr(), 4096)) == 0
     M, S = oracle.mttkrp(coords, vals, A, 0)
     check(out, M, S, "workspace")
+
+
+def test_copies_keep_chains_short():
+    # a frequent row's copies take at most 512 windows' sums each (the full stash took one per
+    # workgroup, 512 to 2048), so that long launches stay as near 64 bits as with the stash
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    dims, nnz = (1 << 18, 1 << 17, 1 << 16), 6_000_000
+    coords = []
+    for d in dims:
+        w = torch.arange(1, d + 1, dtype=torch.float64, device=DEV).pow(-1.1).cumsum(0)
+        u = torch.rand(nnz, generator=g, device=DEV, dtype=torch.float64) * w[-1]
+        coords.append(torch.searchsorted(w, u).clamp_(max=d - 1).to(torch.int32))
+    t = blco.build_device(coords, torch.ones(nnz, device=DEV), dims)
+    for m in range(3):
+        for n in (5_000_000, 6_000_000, 16_000_000, 60_000_000, 200_000_000):
+            p = t.plan(m, 32, nnz=n)
+            windows = -(-n // p["window"])
+            assert p["copies"] and (p["copies"] * 512 >= windows or p["copies"] == 64)
