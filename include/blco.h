@@ -418,6 +418,7 @@ typedef struct {
   int vector_gathers;      /* bf16 rows an even number of elements apart */
   int factor_stride;       /* elements between factor rows: the rank, or more where padded */
   int out_stride;          /* elements between output rows: the rank, or more where padded */
+  int out_copies;          /* copies of the whole output in the workspace */
   int grouped;             /* non-zeros moved to buckets of target rows first */
   int64_t workgroups;      /* of the window kernel */
   size_t workspace_bytes;  /* used of what it is lent */

@@ -78,7 +78,7 @@ class _Info(ctypes.Structure):
 class _Plan(ctypes.Structure):
     _fields_ = [(k, ctypes.c_int) for k in
                 ("resolution", "lanes", "ranks_per_lane", "window", "wpt", "stash_rows", "copies",
-                 "wide", "vector_gathers", "factor_stride", "out_stride", "grouped")] + [
+                 "wide", "vector_gathers", "factor_stride", "out_stride", "out_copies", "grouped")] + [
                     ("workgroups", ctypes.c_int64), ("workspace_bytes", ctypes.c_size_t),
                     ("flushes", ctypes.c_double * 2)]
 

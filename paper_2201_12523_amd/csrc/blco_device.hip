@@ -110,13 +110,20 @@ __global__ __launch_bounds__(256) void k_prep(PrepParams p, int bf16) {
   if (p.starts && i < kGroupBuckets) p.cursor[i] = p.starts[i];
 }
 
-// out (+)= the first R elements of every row of a padded output.
+// out (+)= the first R elements of every row of a padded output, or the sum of its copies (in fp64).
 __global__ __launch_bounds__(256) void k_unpad(const float* __restrict__ src, int64_t rows, int R,
-                                               int Rp, int add, float* __restrict__ out) {
+                                               int Rp, int copies, int64_t step, int add,
+                                               float* __restrict__ out) {
   const int64_t n = rows * R, stride = (int64_t)gridDim.x * 256;
   for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += stride) {
     const int64_t row = j / R;
-    const float v = src[row * Rp + (j - row * R)];
+    const float* at = src + row * Rp + (j - row * R);
+    float v = at[0];
+    if (copies > 1) {
+      double a = (double)v;
+      for (int c = 1; c < copies; ++c) a += (double)at[c * step];
+      v = (float)a;
+    }
     out[j] = add ? out[j] + v : v;
   }
 }
@@ -965,6 +972,9 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
   return res < 0 ? res : BLCO_OK;
 }
 
+// Row flushes per non-zero that windows of 4096 have to save over windows of 2048 (win_wpt).
+static double wide_saves(int N) { return N <= 4 ? 0.05 : 0.095; }
+
 // Window of the window kernel over n non-zeros without a stash, as k_mttkrp_win's WPT:
 // the smallest window that needs no more windows than the device has compute units, up
 // to the largest that pays in a long launch (2048 non-zeros; 4096 at R > 32, where four
@@ -992,13 +1002,14 @@ static int check_factor_args(const blco_tensor* t, int mode, const void* const* 
 // at R > 32).  1M power-law non-zeros, R = 16, 5 iterations, over 48 inputs: two runs of this
 // route leave the third factor 7e-5 apart in norm, the routes below move it by 1.4e-4; time 1.24
 // against 1.15 ms.
-static double wide_saves(int N) { return N <= 4 ? 0.05 : 0.095; }
-static int win_wpt(int N, int R, bool resid, bool big, bool flat, int64_t n, bool careful) {
+//
+// wide: whether windows of 4096 pay, or are wanted for their shorter chains (out_copies).
+static int win_wpt(int N, int R, bool resid, bool big, bool wide, int64_t n, bool careful) {
   if (R > 64 || N > kWideMaxN) return 1;
   if (careful) return R > 32 ? 4 : 2;
   // the fused residual walk's records hold one field more: at N = 5 two windows of 2048 no
   // longer share a CU, and at R > 32 its walk has no registers for four per thread
-  const int most = resid ? (N <= 4 ? 2 : 1) : R > 32 && R % 16 == 0 && flat ? 4 : 2;
+  const int most = resid ? (N <= 4 ? 2 : 1) : R > 32 && wide ? 4 : 2;
   if (big) return most;
   const int64_t cus = device_cus();
   for (int w : {-4, -2, 1, 2})
@@ -1098,6 +1109,30 @@ static double flushes(const blco_tensor* t, int mode, int half) {
   return t->flush_nnz[half] > 0 ? (double)t->flush_rows[mode][half] / (double)t->flush_nnz[half] : 0;
 }
 
+// Whether windows of 4096 pay on mode `mode` (win_wpt).
+static bool wide_pays(const blco_tensor* t, int mode, int gather, bool grouped) {
+  return !grouped && gather % 16 == 0 && !has_frequent_rows(t, mode) &&
+         flushes(t, mode, 0) - flushes(t, mode, 1) >= wide_saves(t->lay.N);
+}
+
+// Copies of the output that a launch in windows of 2048 at R > 32 adds to in turn (1: the output
+// itself).  A row's sum is a chain of fp32 additions, one per window that holds it, and twice as
+// many as in windows of 4096, the only ones there were at R > 32: 1.35 times their error on a mode
+// that every window holds whole.  Copies shorten the chains; they are taken where clearing and
+// adding them up is nothing against the launch (dims x copies x 128 <= n: under 2% of it), which
+// is where chains are long.  8M non-zeros of 21007 x 9001 x 1501 x 367 x 301, R = 35, the mode of
+// 367 rows: 1.01e-6 from 64 bits without copies, 7.6e-7 in windows of 4096, 2.6e-7 with 16 copies;
+// all five modes 1693 us without and 1680 with, as same-row atomics wait for each other less.
+// Without room for them such a launch takes windows of 4096.
+static int out_copies(const blco_tensor* t, int mode, int rank, int gather, bool grouped, int64_t n) {
+  if (rank <= 32 || rank > 64 || t->lay.N > kWideMaxN || n < (1 << 20) || grouped ||
+      has_frequent_rows(t, mode) || wide_pays(t, mode, gather, grouped))
+    return 1;
+  int c = 1;
+  while (c < 16 && t->lay.dims[mode] * 128 * 2 * (uint64_t)c <= (uint64_t)n) c *= 2;
+  return c;
+}
+
 // The window kernel a launch over n non-zeros takes: its instantiation, windows, frequent
 // rows in LDS and the slots of their look-up table.
 struct WinPlan {
@@ -1113,9 +1148,10 @@ struct WinPlan {
 // where factors are padded); even: factor rows an even number of elements
 // apart.  room: bytes of workspace there are; copies that do not fit it are not taken, and
 // the mode falls back to the full stash where that applies.
+// wide: windows of 4096 where they are built, whatever they save.
 static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int ranks, int gather, bool even,
                         int fdt, bool big, bool resid, int64_t n, size_t room, bool careful,
-                        bool grouped) {
+                        bool grouped, bool wide) {
   const int N = t->lay.N;
   auto pick = [&](bool stash, int w) {
     return resid ? select_res(N, gather, even, fdt, stash, w)
@@ -1126,9 +1162,9 @@ static WinPlan plan_win(const blco_tensor* t, int mode, int rank, int ranks, int
     return (n + W - 1) / W;
   };
   const bool frequent = has_frequent_rows(t, mode);
-  const bool flat = !frequent && !grouped &&
-                    flushes(t, mode, 0) - flushes(t, mode, 1) >= wide_saves(N);
-  WinPlan w = {nullptr, win_wpt(N, gather, resid, big, flat, n, careful), 0, 0, 0, 0};
+  WinPlan w = {nullptr,
+               win_wpt(N, gather, resid, big, wide || wide_pays(t, mode, gather, grouped), n, careful),
+               0, 0, 0, 0};
   // one non-zero per thread (the residual walk at N = 5): -1 is the form with copies
   const int lw = w.wpt == 1 ? -1 : w.wpt;
   const bool few = windows(lw) <= kCopyMinWindows;
@@ -1247,6 +1283,8 @@ struct CallPlan {
   bool group;
   size_t copy_bytes;
   size_t bytes;
+  int outs;      // copies of the output
+  bool wide;     // windows of 4096 for want of room for those
 };
 
 // careful: only padded factors, which change no sum.
@@ -1254,7 +1292,7 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
                           int64_t n, size_t room, bool careful) {
   const int N = t->lay.N;
   const size_t fsz = factor_elem_bytes(fdt);
-  CallPlan c = {0, rank, false, 0, 0};
+  CallPlan c = {0, rank, false, 0, 0, 1, false};
   const bool reg = res == BLCO_RES_REGISTER;
   auto left = [&] { return room > c.bytes ? room - c.bytes : 0; };
   const bool big = big_gathers(t, mode, rank, fdt, false, false) ||
@@ -1262,7 +1300,7 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
   if (reg && !careful) {
     c.copy_bytes = up256(plan_win(t, mode, rank, rank, rank, rank % 2 == 0, fdt,
                                   big_gathers(t, mode, rank, fdt, true, resid), resid, n, room,
-                                  false, false)
+                                  false, false, false)
                              .bytes);
     c.bytes = c.copy_bytes;
   }
@@ -1292,6 +1330,21 @@ static CallPlan plan_call(const blco_tensor* t, int mode, int rank, int fdt, int
       c.bytes += bytes;
     }
   }
+  if (reg && !resid && !careful) {
+    const int outs = out_copies(t, mode, rank, c.pad ? c.pad : rank, c.group, n);
+    if (outs > 1) {
+      const int Ro = (rank + 15) / 16 * 16;
+      const size_t one = up256((size_t)t->lay.dims[mode] * Ro * sizeof(float));
+      const size_t bytes = one * (size_t)(c.out != rank ? outs - 1 : outs);
+      if (!big && one * (size_t)outs <= kPadMax && bytes <= left()) {
+        c.out = Ro;
+        c.outs = outs;
+        c.bytes += bytes;
+      } else {
+        c.wide = true;
+      }
+    }
+  }
   return c;
 }
 
@@ -1317,7 +1370,7 @@ static int plan_launch(const blco_tensor* t, int mode, int rank, int fdt, bool r
   L->stride = L->cp.pad ? L->cp.pad : rank;
   if (L->res != BLCO_RES_REGISTER) return BLCO_OK;
   L->w = plan_win(t, mode, L->cp.out, rank, L->stride, L->stride % 2 == 0, fdt, L->big_win, resid,
-                  n, L->cp.copy_bytes, careful, L->cp.group);
+                  n, L->cp.copy_bytes, careful, L->cp.group, L->cp.wide);
   // with a stash: persistent workgroups, kWinRounds times the resident count
   // (two per CU) in a long launch, which balances its end (1-2% faster than one round
   // on 50M non-zeros); once the resident count in a shorter one, where the stash
@@ -1406,11 +1459,15 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
   // flushed rows in the workspace: their padding takes the sums of padded gathers (zeros)
   float* rows = out;
   const int ro = cp.out;
-  if (ro != rank) {
+  const bool apart = ro != rank || cp.outs > 1;
+  p.out_copies = cp.outs;
+  if (apart) {
     rows = reinterpret_cast<float*>(at);
-    at += up256((size_t)t->lay.dims[mode] * ro * sizeof(float));
+    const size_t one = up256((size_t)t->lay.dims[mode] * ro * sizeof(float));
+    at += one * (size_t)cp.outs;
+    p.out_step = (int64_t)(one / sizeof(float));
     pre.zero[0] = rows;
-    pre.nzero[0] = (int64_t)t->lay.dims[mode] * ro;
+    pre.nzero[0] = p.out_step * cp.outs;
     p.R = ro;
   }
   if (cp.group) {
@@ -1454,11 +1511,11 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
                        (const float*)ws.p, p.hot, p.copies, p.copy_stride, rank, ro, rows);
     HIPCHK(hipGetLastError());
   }
-  if (ro != rank) {
+  if (apart) {
     const int64_t I = (int64_t)t->lay.dims[mode];
     const int64_t blocks = std::min<int64_t>((I * rank + 255) / 256, 8192);
     hipLaunchKernelGGL(k_unpad, dim3((unsigned)blocks), dim3(256), 0, s, (const float*)rows, I, rank,
-                       ro, clear ? 0 : 1, out);
+                       ro, cp.outs, p.out_step, clear ? 0 : 1, out);
     HIPCHK(hipGetLastError());
   }
   return BLCO_OK;
@@ -2469,7 +2526,7 @@ extern "C" int blco_frequent_rows(const blco_tensor* t, int mode, int rank, int*
     return set_error(BLCO_EINVAL, "mode %d outside 0..%d", mode, t->lay.N - 1);
   if (rank < 1) return set_error(BLCO_EINVAL, "rank %d < 1", rank);
   const WinPlan w = plan_win(t, mode, rank, rank, rank, rank % 2 == 0, BLCO_F32, false, false,
-                             std::max<int64_t>(t->nnz, 1), 0, false, false);
+                             std::max<int64_t>(t->nnz, 1), 0, false, false, false);
   *rows = w.stash;
   return BLCO_OK;
 }
@@ -2506,6 +2563,7 @@ extern "C" int blco_plan(const blco_tensor* t, int mode, int rank, int factor_dt
   plan->factor_stride = L.stride;
   plan->out_stride = L.cp.out;
   plan->grouped = L.cp.group;
+  plan->out_copies = L.cp.outs;
   plan->workspace_bytes = L.cp.bytes;
   for (int h = 0; h < 2; ++h) plan->flushes[h] = flushes(t, mode, h);
   plan->vector_gathers = factor_dtype == BLCO_BF16 && L.stride % 2 == 0;

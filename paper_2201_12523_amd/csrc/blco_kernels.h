@@ -37,6 +37,8 @@ struct KParams {
   int64_t copy_off;           // ... bytes from out to the copies: copies x copy_stride floats per row
   int copies;                 // ... copies of a row (a power of two)
   int copy_stride;            // ... floats of one copy
+  int out_copies;             // window kernel: copies of the output (a power of two)
+  int64_t out_step;           // ... elements from one to the next
   uint32_t short_rows;        // hierarchical kernel: target mode length
   int short_width;            // hierarchical kernel: ranks per slice
   uint32_t rowbytes;          // bytes between factor rows

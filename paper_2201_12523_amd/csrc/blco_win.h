@@ -353,6 +353,9 @@ __device__ __forceinline__ uint32_t tab_slot(uint32_t row, uint32_t mult) {
 // of kWin, kWin / 2 and kWin / 4 non-zeros; the walk of the last two has only 8 or 4
 // positions per lane group, all gathered at once.  win_wpt (blco_device.hip) chooses.
 //
+// Windows of 2048 at three or four ranks per lane, without a stash, add to p.out_copies copies of
+// the whole output by window number, which k_unpad adds up (out_copies, blco_device.hip).
+//
 // STASH with another WPT than 1: hot copies.  A frequent row (one LDS read per non-zero
 // finds it; the full stash probes its table) is flushed to one of p.copies copies of
 // it in a workspace, by window number, which k_hot_sum adds to the output afterwards.
@@ -439,6 +442,10 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
     return (i * (uint32_t)p.copies + (uint32_t)(blockIdx.x & (uint32_t)(p.copies - 1))) *
            (uint32_t)p.copy_stride;
   };
+  // the copy of the output that this window adds to
+  constexpr bool OUTS = !BIG && !RES && !STASH && LPN == 16 && RPL >= 3 && WPT == 2;
+  float* const out =
+      OUTS ? p.out + (int64_t)(blockIdx.x & (uint32_t)(p.out_copies - 1)) * p.out_step : p.out;
   const int R = p.R;
   const int RV = p.RV, RG = p.RG;
   float* s_stash = reinterpret_cast<float*>(s_dyn_win);   // K x R
@@ -622,7 +629,7 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
             reinterpret_cast<float*>(reinterpret_cast<char*>(p.out) + (hot ? p.copy_off : 0));
         flush_row<RPL, LPN, PACKED, WHOLE>(base, e + (uint32_t)r0, a, scale, rl, nv);
       } else if constexpr (IDX) {
-        flush_row<RPL, LPN, PACKED, WHOLE>(p.out, tf + (uint32_t)r0, a, scale, rl, nv);
+        flush_row<RPL, LPN, PACKED, WHOLE>(out, tf + (uint32_t)r0, a, scale, rl, nv);
       } else {
         flush_row<RPL, LPN, PACKED, WHOLE>(p.out, (size_t)tf * R + r0, a, scale, rl, nv);
       }
