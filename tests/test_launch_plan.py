@@ -79,7 +79,7 @@ def test_workspace_under_a_budget(R, gradient):
 
     whole = -(-nnz // 64) * 64
     rc, most, chunk = plan(1 << 33)
-    assert rc == 0 and chunk == whole and (most > 0) == (R % 16 != 0)
+    assert rc == 0 and chunk == whole and most > 0   # padding, or copies of the output
     rc, used, chunk = plan(1 << 33, 1000)
     assert rc == 0 and used <= 1000 and chunk == whole
     assert plan(2 * 64 * per - 1)[0] == -2
@@ -99,7 +99,7 @@ def test_workspace_under_a_budget(R, gradient):
                        for u in ("mttkrp", "residual")[:1 + gradient]) >= used
             used_some += 1
         assert plan(extra, used)[1] == used
-    assert used_some or R % 16 == 0
+    assert used_some
 
 
 def counted(t, dims, key_bits):
@@ -125,3 +125,4 @@ def test_counted_flushes(dims, nnz, key_bits):
     t = blco.build(coords, np.ones(nnz, np.float32), dims, placement="host", key_bits=key_bits)
     for m, want in enumerate(counted(t, dims, key_bits)):
         assert t.plan(m, 32)["flushes"] == pytest.approx(want, abs=1e-12), m
+
