@@ -176,7 +176,8 @@ int blco_mttkrp(blco_tensor* t, int mode, const void* const* factors, int factor
 /*
  * As blco_mttkrp but accumulating: out += MTTKRP_mode (out is not cleared).
  * For summing the MTTKRPs of several tensors that share factor matrices (for
- * instance one tensor split over several BLCO copies).
+ * instance one tensor split over several BLCO copies).  Every addition to out is
+ * atomic: calls on several streams may add to one output at the same time.
  */
 int blco_mttkrp_acc(blco_tensor* t, int mode, const void* const* factors, int factor_dtype,
                     int rank, float* out, void* stream);

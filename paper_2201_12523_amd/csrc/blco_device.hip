@@ -111,6 +111,7 @@ __global__ __launch_bounds__(256) void k_prep(PrepParams p, int bf16) {
 }
 
 // out (+)= the first R elements of every row of a padded output, or the sum of its copies (in fp64).
+// Added with atomics: calls on several streams may add to one output.
 __global__ __launch_bounds__(256) void k_unpad(const float* __restrict__ src, int64_t rows, int R,
                                                int Rp, int copies, int64_t step, int add,
                                                float* __restrict__ out) {
@@ -124,7 +125,10 @@ __global__ __launch_bounds__(256) void k_unpad(const float* __restrict__ src, in
       for (int c = 1; c < copies; ++c) a += (double)at[c * step];
       v = (float)a;
     }
-    out[j] = add ? out[j] + v : v;
+    if (add)
+      unsafeAtomicAdd(out + j, v);
+    else
+      out[j] = v;
   }
 }
 
@@ -263,7 +267,8 @@ __global__ __launch_bounds__(kBlock) void k_hot_sum(const float* __restrict__ co
   __syncthreads();
   if (q == 0 && r < RV) {
     const float v = (s_part[r] + s_part[64 + r]) + (s_part[128 + r] + s_part[192 + r]);
-    if (v != 0.f) out[(size_t)hot[blockIdx.x] * R + r] += v;
+    // atomic: calls on several streams may add to one output
+    if (v != 0.f) unsafeAtomicAdd(out + (size_t)hot[blockIdx.x] * R + r, v);
   }
 }
 
