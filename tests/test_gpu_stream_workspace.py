@@ -39,7 +39,7 @@ def test_budget(kind, R):
                   2 * nnz * per, 1 << 30):
         budget = fixed + extra
         torch.cuda.synchronize()
-        before = torch.cuda.memory_allocated()
+        before = torch.cuda.memory_stats()["requested_bytes.all.current"]
         torch.cuda.reset_peak_memory_stats()
         if kind == "all":
             got = blco.mttkrp_stream_all(t, F, outs=outs, device_budget=budget)
@@ -48,15 +48,16 @@ def test_budget(kind, R):
         else:
             l, got, _ = blco.cp_grad(t, F, grads=outs, device_budget=budget)
             assert abs(float(l) - float(loss)) <= 1e-6 * float(loss)
-        lent = torch.cuda.max_memory_allocated() - before
+        # what was asked for: a block of torch's may be larger, by what it does not split off
+        lent = torch.cuda.memory_stats()["requested_bytes.all.peak"] - before
         inf = t.info()
         chunk = inf["stream_chunk_nnz"]
         alone = max(64, min(extra // 2 // per, -(-nnz // 64) * 64) // 64 * 64)
         assert chunk >= alone * 7 // 8 - 64
-        # torch rounds a block up to 512 bytes, and the gradient's loss is one more
-        assert fixed + 2 * chunk * per + lent <= budget + 1024
+        # (the gradient's loss is one double more)
+        assert fixed + 2 * chunk * per + lent <= budget + 8
         assert inf["stream_peak_bytes"] <= budget
-        assert inf["stream_peak_bytes"] + 1024 >= fixed + 2 * chunk * per + lent
+        assert inf["stream_peak_bytes"] + 8 >= fixed + 2 * chunk * per + lent
         for a, b in zip(got, want[:1] if kind == "one" else want):
             # positive terms: each side within the parity bound of 1e-5 of the sum; the gradient's
             # terms change sign, so by the largest entry, with the residual's rounding
