@@ -164,11 +164,13 @@ def _stream(stream=None, t=None) -> int:
 
 def _with_memory(call):
     """call() again after torch has released its cached blocks, where device memory ran out
-    (the library's own allocations do not reach into torch's cache)."""
+    (the library's own allocations do not reach into torch's cache; it makes them before it
+    writes anything)."""
     rc = call()
-    if rc == -2 and torch.cuda.is_available():
-        torch.cuda.empty_cache()
-        rc = call()
+    if rc == -2 and not lib().blco_last_error().startswith(b"budget") and torch.cuda.is_available():
+        if not torch.cuda.is_current_stream_capturing():
+            torch.cuda.empty_cache()
+            rc = call()
     return rc
 
 
@@ -302,8 +304,8 @@ def build(coords, values, dims, key_bits=64, max_block_nnz=1 << 27, placement="d
     arr = (ctypes.c_void_p * N)(*[c.ctypes.data for c in cs])
     opts = _Opts(key_bits, max_block_nnz, PLACEMENTS[placement], int(hot_min_count))
     h = ctypes.c_void_p()
-    _check(lib().blco_build(N, d.ctypes.data, len(v), arr, v.ctypes.data, ctypes.byref(opts),
-                            ctypes.byref(h)))
+    _check(_with_memory(lambda: lib().blco_build(N, d.ctypes.data, len(v), arr, v.ctypes.data,
+                                                 ctypes.byref(opts), ctypes.byref(h))))
     return BLCOTensor(h.value, dims)
 
 
@@ -487,13 +489,13 @@ def mttkrp_stream(t, mode, factors, out=None, device_budget=8_000_000_000, strea
     out = _out(t, mode, R, out, _device_of(factors))
     ws, wp, wb = _stream_workspace(t, [mode], 0, R, dt, device_budget, out.device, stream)
     if wb == 0:
-        _check(lib().blco_mttkrp_stream(t.handle, mode, arr, dt, R, out.data_ptr(),
-                                        int(device_budget), _stream(stream, t)))
+        _check(_with_memory(lambda: lib().blco_mttkrp_stream(
+            t.handle, mode, arr, dt, R, out.data_ptr(), int(device_budget), _stream(stream, t))))
         return out
     outs = (ctypes.c_void_p * len(t.dims))()
     outs[mode] = out.data_ptr()
-    _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, outs, int(device_budget), wp, wb,
-                                           _stream(stream, t)))
+    _check(_with_memory(lambda: lib().blco_mttkrp_stream_all_ws(
+        t.handle, arr, dt, R, outs, int(device_budget), wp, wb, _stream(stream, t))))
     return out
 
 
@@ -511,8 +513,8 @@ def mttkrp_stream_all(t, factors, outs=None, device_budget=8_000_000_000, modes=
     ptrs = (ctypes.c_void_p * len(t.dims))(*[outs[m].data_ptr() if m in modes else None
                                                for m in range(len(t.dims))])
     ws, wp, wb = _stream_workspace(t, modes, 0, R, dt, device_budget, dev, stream)
-    _check(lib().blco_mttkrp_stream_all_ws(t.handle, arr, dt, R, ptrs, int(device_budget), wp, wb,
-                                           _stream(stream, t)))
+    _check(_with_memory(lambda: lib().blco_mttkrp_stream_all_ws(
+        t.handle, arr, dt, R, ptrs, int(device_budget), wp, wb, _stream(stream, t))))
     return [outs[m] if m in modes else None for m in range(len(t.dims))]
 
 
@@ -525,8 +527,8 @@ def sampled_loss(t, factors, residual=None, loss=None, stream=None):
         residual = torch.empty(n, dtype=torch.float32, device=dev)
     if loss is None:
         loss = torch.empty((), dtype=torch.float64, device=dev)
-    _check(lib().blco_sampled_loss(t.handle, arr, dt, R, residual.data_ptr(), loss.data_ptr(),
-                                   _stream(stream, t)))
+    _check(_with_memory(lambda: lib().blco_sampled_loss(
+        t.handle, arr, dt, R, residual.data_ptr(), loss.data_ptr(), _stream(stream, t))))
     return loss, residual
 
 
@@ -558,9 +560,9 @@ def cp_grad(t, factors, grads=None, residual=None, loss=None, scale=None, alpha=
         ws, wp, wb = _stream_workspace(t, range(N), 1, R, dt, device_budget, dev, stream)
     else:
         ws, wp, wb = _workspace(t, -1, R, dt, dev, stream)
-    _check(lib().blco_cp_grad_ws(t.handle, arr, dt, R, sp, float(alpha),
-                                 None if pinned else residual.data_ptr(), loss.data_ptr(), ptrs,
-                                 int(device_budget), wp, wb, _stream(stream, t)))
+    _check(_with_memory(lambda: lib().blco_cp_grad_ws(
+        t.handle, arr, dt, R, sp, float(alpha), None if pinned else residual.data_ptr(),
+        loss.data_ptr(), ptrs, int(device_budget), wp, wb, _stream(stream, t))))
     return loss, grads, (None if pinned else residual)
 
 

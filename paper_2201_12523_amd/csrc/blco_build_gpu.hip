@@ -310,8 +310,8 @@ struct Pool {
       return BLCO_OK;
     }
     void* p = nullptr;
-    if (hipMalloc(&p, need) != hipSuccess)
-      return set_error(BLCO_ENOMEM, "device allocation of %zu bytes failed", need);
+    int rc = device_alloc(&p, need);
+    if (rc) return rc;
     ptrs.push_back(p);
     *out = static_cast<T*>(p);
     return BLCO_OK;
@@ -329,7 +329,8 @@ struct Home {
       *dst = reinterpret_cast<T*>(t->storage + at);
       at += (need + 255) / 256 * 256;
     } else {
-      HIPCHK(hipMalloc((void**)dst, need));
+      int rc = device_alloc((void**)dst, need);
+      if (rc) return rc;
     }
     *acc += need;
     return BLCO_OK;
@@ -719,6 +720,7 @@ static int build_device_impl(int nmodes, const uint64_t* dims, int64_t nnz,
     const size_t n1 = (size_t)std::max<int64_t>(nnz, 1);
     if (hipHostMalloc((void**)&t->h_keys, n1 * 8, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&t->h_vals, n1 * 4, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
       rc = set_error(BLCO_ENOMEM, "pinned allocation of %lld non-zeros failed", (long long)nnz);
     } else {
       t->host_free = pinned_release;

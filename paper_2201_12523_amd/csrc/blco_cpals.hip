@@ -491,7 +491,8 @@ extern "C" int blco_cp_als_in(blco_tensor* t, float* const* factors, int rank,
   const AlsMemory mem(t, R, o.factor_dtype);
   DevBuf own;
   if (!ws || ws_bytes < mem.total) {
-    HIPCHK(hipMalloc(&own.p, mem.total));
+    int rc = blco::device_alloc(&own.p, mem.total);
+    if (rc) return rc;
     ws = own.p;
   }
   char* base = static_cast<char*>(ws);

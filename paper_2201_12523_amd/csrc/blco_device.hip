@@ -1530,9 +1530,22 @@ static int launch_mttkrp(const blco_tensor* t, const uint64_t* keys, const float
   return BLCO_OK;
 }
 
+int blco::device_alloc(void** p, size_t bytes) {
+  *p = nullptr;
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return BLCO_OK;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return set_error(e == hipErrorOutOfMemory ? BLCO_ENOMEM : BLCO_EDEVICE,
+                   "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+}
+
 static void* pinned_alloc(size_t n) {
   void* p = nullptr;
-  if (hipHostMalloc(&p, n, hipHostMallocDefault) != hipSuccess) return nullptr;
+  if (hipHostMalloc(&p, n, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
   return p;
 }
 static void pinned_free(void* p) { (void)hipHostFree(p); }
@@ -1541,7 +1554,8 @@ static void pinned_free(void* p) { (void)hipHostFree(p); }
 template <class T>
 static int upload(T** dst, const T* src, size_t count, size_t* acc) {
   size_t bytes = sizeof(T) * std::max<size_t>(count, 1);
-  HIPCHK(hipMalloc((void**)dst, bytes));
+  int rc = device_alloc((void**)dst, bytes);
+  if (rc) return rc;
   if (count) HIPCHK(hipMemcpy(*dst, src, sizeof(T) * count, hipMemcpyHostToDevice));
   *acc += bytes;
   return BLCO_OK;
@@ -1696,7 +1710,8 @@ int blco::make_groups(blco_tensor* t, void* stream) {
   if (!any) return BLCO_OK;
   if (!t->d_group) {
     const size_t bytes = sizeof(uint32_t) * (size_t)L.N * kGroupBuckets;
-    HIPCHK(hipMalloc((void**)&t->d_group, bytes));
+    int rc = device_alloc((void**)&t->d_group, bytes);
+    if (rc) return rc;
     t->device_bytes += bytes;
   }
   int rc = fill_zero(reinterpret_cast<float*>(t->d_group), (int64_t)L.N * kGroupBuckets, s);
@@ -1950,7 +1965,8 @@ static int ensure_partials(blco_tensor* t, int64_t count, hipStream_t s) {
     t->d_partials = nullptr;
     t->partials_cap = 0;
   }
-  HIPCHK(hipMalloc((void**)&t->d_partials, sizeof(double) * (size_t)count));
+  int rc = device_alloc((void**)&t->d_partials, sizeof(double) * (size_t)count);
+  if (rc) return rc;
   t->partials_cap = count;
   return BLCO_OK;
 }
@@ -2152,10 +2168,10 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
       st.d_vals[i] = nullptr;
     }
     st.cap_nnz = 0;
-    for (int i = 0; i < 2; ++i) {
-      HIPCHK(hipMalloc((void**)&st.d_keys[i], sizeof(uint64_t) * (size_t)cap));
-      HIPCHK(hipMalloc((void**)&st.d_vals[i], sizeof(float) * (size_t)cap));
-    }
+    for (int i = 0; i < 2; ++i)
+      if ((rc = device_alloc((void**)&st.d_keys[i], sizeof(uint64_t) * (size_t)cap)) ||
+          (rc = device_alloc((void**)&st.d_vals[i], sizeof(float) * (size_t)cap)))
+        return rc;
     st.cap_nnz = cap;
   }
   if (grad && st.res_cap != cap) {
@@ -2165,7 +2181,8 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
       st.d_res[i] = nullptr;
     }
     st.res_cap = 0;
-    for (int i = 0; i < 2; ++i) HIPCHK(hipMalloc((void**)&st.d_res[i], sizeof(float) * (size_t)cap));
+    for (int i = 0; i < 2; ++i)
+      if ((rc = device_alloc((void**)&st.d_res[i], sizeof(float) * (size_t)cap))) return rc;
     st.res_cap = cap;
   }
   for (int m = 0; m < L.N; ++m)

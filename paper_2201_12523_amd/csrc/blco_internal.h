@@ -117,6 +117,10 @@ namespace blco {
 int set_error(int code, const char* fmt, ...);
 void clear_error();
 
+// Device memory: ENOMEM where there is none (the HIP error is taken back, so that the caller may free
+// some and try again), EDEVICE for other failures.  Defined in blco_device.hip.
+int device_alloc(void** p, size_t bytes);
+
 typedef void* (*HostAlloc)(size_t);
 typedef void (*HostFree)(void*);
 
