@@ -459,15 +459,20 @@ def big_factors(dims, R, sf, n, window=True):
     return R * sf >= (1 << 31) or any(d * R * sf > lim for m, d in enumerate(dims) if m != n)
 
 
+def planned_kernel_name(p, N, ft):
+    """Template name of the MTTKRP kernel of a launch the library plans (BLCOTensor.plan)."""
+    b = lambda v: "true" if v else "false"
+    rpl, big = p["ranks_per_lane"], b(p["wide"])
+    vec = b(p["vector_gathers"] and rpl > 1)
+    if p["resolution"] == 2:
+        return f"k_mttkrp_short<{rpl}, {ft}, {N}, {big}, {vec}>"
+    return (f"k_mttkrp_win<{p['lanes']}, {rpl}, {ft}, {N}, {big}, "
+            f"{b(p['stash_rows'] or p['copies'])}, false, {vec}, {p['wpt']}>")
+
+
 def mode_kernel(T, n, R, N, ft, dims):
-    """The kernel one mode's MTTKRP launches (the library's rule, read back)."""
-    sf = 4 if ft == "float" else 2
-    if T.resolution(n, R) == "hierarchical":
-        return short_kernel_name(R, N, ft, big_factors(dims, R, sf, n, window=False))
-    dtype = "fp32" if ft == "float" else "bf16"
-    if T.workspace(n, R, dtype) > 0:
-        return win_kernel_name(R, N, ft, copies=True)
-    return win_kernel_name(R, N, ft, big_factors(dims, R, sf, n), stash=T.stash_rows(n, R) > 0)
+    """The kernel one mode's MTTKRP launches with the workspace the package lends it."""
+    return planned_kernel_name(T.plan(n, R, "fp32" if ft == "float" else "bf16"), N, ft)
 
 
 def describe(w, nnz):

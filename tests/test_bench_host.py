@@ -78,6 +78,38 @@ def test_kernel_names_exist_in_the_library(bench):
                 assert bench.short_kernel_name(R, N, ft) in names
 
 
+def test_planned_kernel_names_exist_in_the_library(bench):
+    """Whatever a launch plans (ranks, modes, sizes, workspace, a skewed mode), its kernel is there."""
+    import numpy as np
+
+    import paper_2201_12523_amd as blco
+
+    so = os.path.join(ROOT, "paper_2201_12523_amd", "libblco.so")
+    if not os.path.exists(so):
+        pytest.skip("library not built")
+    syms = subprocess.run(["nm", "-C", so], capture_output=True, text=True, check=True).stdout
+    names = {line.split(" ", 2)[2].removeprefix("void ").split("(")[0] for line in syms.splitlines()
+             if line.endswith("(blco::KParams)") or line.endswith("(blco::KParams, long)")}
+    rng = np.random.default_rng(4)
+    seen = set()
+    for N in (1, 3, 5, 6):
+        dims = (40_000, 3000, 900, 300, 40, 9)[:N]
+        for skew in (False, True):
+            nnz = 300_000
+            coords = [rng.integers(0, d, nnz).astype(np.uint32) for d in dims]
+            if skew:
+                coords[0] = np.minimum(rng.zipf(1.2, nnz) - 1, dims[0] - 1).astype(np.uint32)
+            t = blco.build(coords, np.ones(nnz, np.float32), dims, placement="host")
+            for R in (1, 16, 17, 33, 35, 48, 50, 64, 65, 100, 300):
+                for dtype, ft in (("fp32", "float"), ("bf16", "unsigned short")):
+                    for n in (1000, 50_000, 200_000, 600_000, 20_000_000):
+                        for ws in (0, None):
+                            for m in range(N):
+                                p = t.plan(m, R, dtype, nnz=n, workspace=ws)
+                                seen.add(bench.planned_kernel_name(p, N, ft))
+    assert len(seen) > 100 and seen <= names, sorted(seen - names)[:5]
+
+
 def test_counters_traffic_and_atomics(bench, tmp_path):
     """Per-dispatch means per kernel, the copy-calibrated HBM traffic and the row-ops derived
     from TCC_EA0_ATOMIC with the probe kernel as the per-row-op reference."""
