@@ -834,6 +834,15 @@ __global__ __launch_bounds__(kWin, (WPT >= 4 || WPT < -1) ? 4 : BLCO_WIN_OCC) vo
 constexpr int kWideMaxN = 5;
 
 template <int LPN, int RPL, typename FT, bool BIG, bool STASH, bool RES, bool VEC>
+static KernelFn pick_many_n(int N) {
+  switch (N) {
+    case 6: return k_mttkrp_win<LPN, RPL, FT, 6, BIG, STASH, RES, VEC>;
+    case 7: return k_mttkrp_win<LPN, RPL, FT, 7, BIG, STASH, RES, VEC>;
+    default: return k_mttkrp_win<LPN, RPL, FT, 8, BIG, STASH, RES, VEC>;
+  }
+}
+
+template <int LPN, int RPL, typename FT, bool BIG, bool STASH, bool RES, bool VEC>
 static KernelFn pick_any_n(int N) {
   switch (N) {
     case 1: return k_mttkrp_win<LPN, RPL, FT, 1, BIG, STASH, RES, VEC>;
@@ -841,9 +850,7 @@ static KernelFn pick_any_n(int N) {
     case 3: return k_mttkrp_win<LPN, RPL, FT, 3, BIG, STASH, RES, VEC>;
     case 4: return k_mttkrp_win<LPN, RPL, FT, 4, BIG, STASH, RES, VEC>;
     case 5: return k_mttkrp_win<LPN, RPL, FT, 5, BIG, STASH, RES, VEC>;
-    case 6: return k_mttkrp_win<LPN, RPL, FT, 6, BIG, STASH, RES, VEC>;
-    case 7: return k_mttkrp_win<LPN, RPL, FT, 7, BIG, STASH, RES, VEC>;
-    default: return k_mttkrp_win<LPN, RPL, FT, 8, BIG, STASH, RES, VEC>;
+    default: return pick_many_n<LPN, RPL, FT, BIG, STASH, RES, VEC>(N);
   }
 }
 
@@ -862,13 +869,13 @@ static KernelFn pick_wide_n(int N) {
   return nullptr;
 }
 
-// 16-lane groups of RPL ranks per lane; wpt as win_wpt gives it
+// 16-lane groups of RPL ranks per lane; wpt as win_wpt gives it.  Three ranks per lane have no
+// full stash and no windows of 1024 (select_win_t); 64-bit addresses no small windows and, up to
+// kWideMaxN modes, none of 1024 without a stash (win_wpt); copies have windows of 2048 (wide_pays).
 template <int RPL, typename FT, bool BIG, bool VEC>
 static KernelFn pick_win16(int N, bool stash, int wpt) {
   if constexpr (!BIG) {
     if (stash && wpt == 2) return pick_wide_n<RPL, FT, BIG, false, VEC, 2, true>(N);
-    if constexpr (RPL >= 3)
-      if (stash && wpt == 4) return pick_wide_n<RPL, FT, BIG, false, VEC, 4, true>(N);
   }
   if constexpr (RPL != 3)
     if (stash) return pick_any_n<16, RPL, FT, BIG, true, false, VEC>(N);
@@ -879,7 +886,12 @@ static KernelFn pick_win16(int N, bool stash, int wpt) {
   if (wpt == 2) return pick_wide_n<RPL, FT, BIG, false, VEC, 2>(N);
   if constexpr (RPL >= 3)
     if (wpt == 4) return pick_wide_n<RPL, FT, BIG, false, VEC, 4>(N);
-  return pick_any_n<16, RPL, FT, BIG, false, false, VEC>(N);
+  if constexpr (RPL == 3)
+    return nullptr;
+  else if constexpr (BIG)
+    return pick_many_n<16, RPL, FT, BIG, false, false, VEC>(N);
+  else
+    return pick_any_n<16, RPL, FT, BIG, false, false, VEC>(N);
 }
 
 // Window kernel shape (lanes per non-zero x ranks per lane), chosen by measurement on
@@ -910,7 +922,8 @@ static KernelFn select_win_t(int N, int R, bool even, bool stash, int wpt) {
 template <int RPL, typename FT, bool VEC>
 static KernelFn pick_res(int N, bool stash, int wpt) {
   if (stash && wpt == 2) return pick_wide_n<RPL, FT, false, true, VEC, 2, true>(N);
-  if (stash && wpt == -1) return pick_wide_n<RPL, FT, false, true, VEC, -1, true>(N);
+  // one non-zero per thread with copies: the walk's only long window at five modes (win_wpt)
+  if (stash && wpt == -1) return k_mttkrp_win<16, RPL, FT, 5, false, true, true, VEC, -1>;
   if (stash) return pick_any_n<16, RPL, FT, false, true, true, VEC>(N);
   if (wpt == 2) return pick_wide_n<RPL, FT, false, true, VEC, 2>(N);
   if (wpt == -4) return pick_wide_n<RPL, FT, false, true, VEC, -4>(N);
