@@ -150,6 +150,14 @@ def _check(rc):
         raise BLCOError(rc, lib().blco_last_error().decode())
 
 
+def _torch_stream(stream):
+    """A caller's stream as torch takes it (None stays None): anything with a `cuda_stream` handle
+    is a stream to this package."""
+    if stream is None or isinstance(stream, torch.cuda.Stream):
+        return stream
+    return torch.cuda.ExternalStream(int(stream.cuda_stream))
+
+
 def _stream(stream=None, t=None) -> int:
     """The stream handle of a call.  A tensor whose arrays live in a torch allocation made on
     another stream is recorded on this one, so that its memory is not reused before the
@@ -158,7 +166,7 @@ def _stream(stream=None, t=None) -> int:
         stream = torch.cuda.current_stream()
     h = int(stream.cuda_stream)
     if t is not None and t._storage is not None and h != t._storage_stream:
-        t._storage.record_stream(stream)
+        t._storage.record_stream(_torch_stream(stream))
     return h
 
 
@@ -346,7 +354,7 @@ def build_device(coords, values, dims, key_bits=64, max_block_nnz=1 << 27, place
     # the arrays and the workspace from the pool of the stream the build runs on
     sh = _stream(stream)
     storage = ws = None
-    with torch.cuda.stream(stream):
+    with torch.cuda.stream(_torch_stream(stream)):
         try:
             if need_s.value:
                 storage = torch.empty(need_s.value, dtype=torch.uint8, device=dev)
@@ -432,7 +440,7 @@ def _lend(bytes_, device, stream):
         if stream is None:
             ws = torch.empty(bytes_, dtype=torch.uint8, device=device)
         else:
-            with torch.cuda.stream(stream):
+            with torch.cuda.stream(_torch_stream(stream)):
                 ws = torch.empty(bytes_, dtype=torch.uint8, device=device)
     except torch.cuda.OutOfMemoryError:
         return None, None, 0
@@ -690,7 +698,7 @@ def cp_als(t, factors, max_iters=25, tol=1e-5, storage="fp32", stream=None):
         # from the pool of the stream the call runs on; the call itself says what is wrong
         # with its arguments, and allocates where this cannot
         try:
-            with torch.cuda.stream(stream):
+            with torch.cuda.stream(_torch_stream(stream)):
                 ws = torch.empty(need.value, dtype=torch.uint8, device=factors[0].device)
         except torch.cuda.OutOfMemoryError:
             pass
