@@ -1562,12 +1562,15 @@ static int upload(T** dst, const T* src, size_t count, size_t* acc) {
 }
 
 // The copies of streamed calls queued on one stream follow one another: a call's copies start
-// after those of the call queued there before it.  Its kernels come after that call's anyway, so
-// nothing completes later for the wait; but where two tensors are streamed in turn, each through
-// its own copy stream, their copies otherwise share the host link, which then moves less, and the
-// first call's kernels start late (two tensors of 20M non-zeros, 240 MB each: 6.2 ms per copy
-// instead of 4.2, 4.44 instead of 4.36 ms per call).  The last copies of the streams most
-// recently used, kept while any tensor has been streamed.
+// when kCopyLead bytes are left of those of the call queued there before it.  Its kernels come
+// after that call's anyway, so nothing completes later for the wait; but where tensors are
+// streamed in turn, each through its own copy stream, their copies otherwise share the host link,
+// which then moves less, and the first call's kernels start late.  The lead covers what a wait
+// between streams costs.  Three tensors in turn, us per call without waiting, waiting for all, and
+// for all but 64 MiB: 20M non-zeros (240 MB) 4570, 4385 and 4340; 10.6M in two chunks 2295, 2357 and
+// 2288; 7.7M (R = 64) 2207, 2082 and 2101; 3.7M 812, 843 and 811; 2.1M 470, 508 and 470.  The
+// streams most recently used, kept while any tensor has been streamed.
+constexpr int64_t kCopyLead = (int64_t)64 << 20;
 struct LastCopies {
   struct Entry {
     int dev;
@@ -1592,7 +1595,7 @@ struct LastCopies {
     const Entry* x = find(dev, s);
     return x ? hipStreamWaitEvent(cs, x->done, 0) : hipSuccess;
   }
-  // what has been queued on cs are the last copies of calls on s
+  // the next call on s starts its copies behind what has been queued on cs
   hipError_t mark(int dev, hipStream_t s, hipStream_t cs) {
     std::lock_guard<std::mutex> lock(mu);
     Entry* x = find(dev, s);
@@ -2200,17 +2203,33 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
   st.timed_chunks = 0;
   HIPCHK(last_copies().follow(t->device, s, (hipStream_t)st.copy_stream));
   int64_t chunks = 0;
+  hipStream_t cs = (hipStream_t)st.copy_stream;
+  bool marked = false;
+  // before a copy with `left` bytes of the call still to be queued
+  auto lead = [&](int64_t left) {
+    if (marked || left > kCopyLead) return hipSuccess;
+    marked = true;
+    return last_copies().mark(t->device, s, cs);
+  };
   for (int64_t lo = 0; lo < t->nnz; lo += cap, ++chunks) {
     const int b = (int)(chunks & 1);
     const int64_t cnt = std::min(cap, t->nnz - lo);
-    hipStream_t cs = (hipStream_t)st.copy_stream;
+    const int64_t key = sizeof(uint64_t), val = sizeof(float);
+    const int64_t after = (t->nnz - lo - cnt) * (key + val);   // bytes of later chunks
     hipEvent_t* ev = reinterpret_cast<hipEvent_t*>(&st.ev_t[4 * chunks]);
     HIPCHK(hipStreamWaitEvent(cs, (hipEvent_t)st.ev_free[b], 0));
     HIPCHK(hipEventRecord(ev[0], cs));
-    HIPCHK(hipMemcpyAsync(st.d_keys[b], t->h_keys + lo, sizeof(uint64_t) * (size_t)cnt,
-                          hipMemcpyHostToDevice, cs));
-    HIPCHK(hipMemcpyAsync(st.d_vals[b], t->h_vals + lo, sizeof(float) * (size_t)cnt,
-                          hipMemcpyHostToDevice, cs));
+    HIPCHK(lead(after + cnt * (key + val)));
+    HIPCHK(hipMemcpyAsync(st.d_keys[b], t->h_keys + lo, (size_t)(cnt * key), hipMemcpyHostToDevice, cs));
+    HIPCHK(lead(after + cnt * val));
+    // (the last values in two pieces where they are more than the lead)
+    const int64_t head = marked || after ? cnt : cnt - kCopyLead / val;
+    HIPCHK(hipMemcpyAsync(st.d_vals[b], t->h_vals + lo, (size_t)(head * val), hipMemcpyHostToDevice, cs));
+    if (head < cnt) {
+      HIPCHK(lead((cnt - head) * val));
+      HIPCHK(hipMemcpyAsync(st.d_vals[b] + head, t->h_vals + lo + head, (size_t)((cnt - head) * val),
+                            hipMemcpyHostToDevice, cs));
+    }
     HIPCHK(hipEventRecord(ev[1], cs));
     HIPCHK(hipEventRecord((hipEvent_t)st.ev_ready[b], cs));
     HIPCHK(hipStreamWaitEvent(s, (hipEvent_t)st.ev_ready[b], 0));
@@ -2232,7 +2251,6 @@ static int stream_modes(blco_tensor* t, const void* const* factors, int factor_d
     HIPCHK(hipEventRecord(ev[3], s));
     HIPCHK(hipEventRecord((hipEvent_t)st.ev_free[b], s));
   }
-  HIPCHK(last_copies().mark(t->device, s, (hipStream_t)st.copy_stream));
   if (grad) {
     hipLaunchKernelGGL(k_reduce_loss, dim3(1), dim3(1024), 0, s, (const double*)t->d_partials,
                        poff, grad->loss);
