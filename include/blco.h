@@ -424,7 +424,8 @@ typedef struct {
   int64_t workgroups;      /* of the window kernel */
   size_t workspace_bytes;  /* used of what it is lent */
   double flushes[2];       /* distinct target rows per non-zero in windows of 2048 and of 4096
-                              non-zeros, counted at construction over at most 64 windows */
+                              non-zeros, counted at construction over 64 windows (0 below 2^19
+                              non-zeros) */
 } blco_plan_t;
 int blco_plan(const blco_tensor* t, int mode, int rank, int factor_dtype, int use, int64_t nnz,
               size_t workspace_bytes, blco_plan_t* plan);

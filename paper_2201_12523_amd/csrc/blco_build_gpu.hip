@@ -59,13 +59,15 @@ struct LinResult {
 
 constexpr int kEncBytes = 8;   // K <= 64
 
-// Byte tables of the bit map, and the cleared LinResult.  dep[((m * 4 + k) * 256 + v) * 2 +
+// Byte tables of the bit map, the cleared LinResult and the cleared flush counts.  dep[((m * 4 + k) * 256 + v) * 2 +
 // {0, 1}]: the (lo, hi) index bits of byte k of a mode-m coordinate holding v;
 // enc[k * 256 + v]: key bits of byte k of an index holding v.
 __global__ __launch_bounds__(256) void k_tables(LinParams p, uint64_t* __restrict__ dep,
                                                 uint64_t* __restrict__ enc,
-                                                LinResult* __restrict__ res) {
+                                                LinResult* __restrict__ res,
+                                                uint32_t* __restrict__ counts) {
   const int v = threadIdx.x;
+  if (blockIdx.x == 0 && v < 2 * BLCO_MAX_MODES) counts[v] = 0;
   if (blockIdx.x == 0 && v == 0) *res = LinResult{~0ull, ~0ull, 0ull, ~0ull, 0ull};
   const int nd = p.N * 4;
   if ((int)blockIdx.x < nd) {
@@ -480,7 +482,8 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
                        (rc = pool.get(&hif, nnz))))
     return rc;
   // 1. linearize, through per-byte deposit tables
-  hipLaunchKernelGGL(k_tables, dim3(L.N * 4 + kEncBytes), dim3(256), 0, s, lp, d_dep, d_enc, res);
+  hipLaunchKernelGGL(k_tables, dim3(L.N * 4 + kEncBytes), dim3(256), 0, s, lp, d_dep, d_enc, res,
+                     counts);
   HIPCHK(hipGetLastError());
   if (nnz > 0)
     hipLaunchKernelGGL(k_linearize, dim3(std::min<unsigned>(grid_of(nnz), kStrideGrid)), dim3(256),
@@ -623,7 +626,7 @@ int build_on_device(int nmodes, const uint64_t* dims, int64_t nnz, const uint32_
       (rc = home.get(&t->d_group, (size_t)L.N * kGroupBuckets, &acc)))
     return rc;
   t->device_bytes = acc;
-  if (nnz > 0)
+  if (nnz >= kFlushMin)
     HIPCHK(hipMemcpyAsync(t->flush_rows, counts, sizeof(t->flush_rows), hipMemcpyDeviceToHost, s));
   if (t->placement == BLCO_PLACE_DEVICE && (rc = make_groups(t, s))) return rc;
   HIPCHK(hipStreamSynchronize(s));

@@ -147,7 +147,6 @@ __global__ __launch_bounds__(1024) void k_flushes(KParams p, uint32_t* __restric
   for (int half = 0; half < 2; ++half) {
     for (int i = threadIdx.x; i < kFlushWindow / 2; i += 1024) {
       const int64_t k = k0 + half * (kFlushWindow / 2) + i;
-      if (k >= p.n) break;
       uint32_t row = (uint32_t)(p.keys[k] >> p.shift[m]) & p.mask[m];
       if (p.multi) {
         int run = p.tile_run[k >> 6];
@@ -1113,9 +1112,9 @@ static double window_flushes(const blco_tensor* t, int mode, double W, double n)
 }
 
 // Row flushes per non-zero of mode `mode` in windows of kFlushWindow / 2 (half 0) and kFlushWindow
-// (half 1) non-zeros, as counted at construction.
+// (half 1) non-zeros, as counted at construction (0 below kFlushMin non-zeros).
 static double flushes(const blco_tensor* t, int mode, int half) {
-  return t->flush_nnz[half] > 0 ? (double)t->flush_rows[mode][half] / (double)t->flush_nnz[half] : 0;
+  return (double)t->flush_rows[mode][half] / (kFlushSamples * (kFlushWindow / (2 - half)));
 }
 
 // Whether windows of 4096 pay on mode `mode` (win_wpt).
@@ -1672,18 +1671,14 @@ static void release_device(blco_tensor* t) {
 }
 
 int blco::count_flushes_device(blco_tensor* t, uint32_t* counts, void* stream) {
+  if (t->nnz < kFlushMin) return BLCO_OK;
   hipStream_t s = (hipStream_t)stream;
-  memset(t->flush_rows, 0, sizeof(t->flush_rows));
-  flush_sizes(t->nnz, t->flush_nnz);
-  if (t->nnz <= 0) return BLCO_OK;
-  int rc = fill_zero(reinterpret_cast<float*>(counts), 2 * BLCO_MAX_MODES, s);
-  if (rc) return rc;
   KParams p;
   fill_params(t, &p);
   p.keys = t->d_keys;
   p.n = t->nnz;
-  hipLaunchKernelGGL(k_flushes, dim3((unsigned)flush_windows(t->nnz), (unsigned)t->lay.N), dim3(1024), 0,
-                     s, p, counts);
+  hipLaunchKernelGGL(k_flushes, dim3((unsigned)kFlushSamples, (unsigned)t->lay.N), dim3(1024), 0, s, p,
+                     counts);
   HIPCHK(hipGetLastError());
   return BLCO_OK;
 }

@@ -435,12 +435,11 @@ void make_row_tables(blco_tensor* t) {
 void count_flushes(blco_tensor* t) {
   const Layout& L = t->lay;
   memset(t->flush_rows, 0, sizeof(t->flush_rows));
-  flush_sizes(t->nnz, t->flush_nnz);
+  if (t->nnz < kFlushMin) return;
   constexpr uint32_t kSlots = 2 * kFlushWindow;
   std::vector<uint64_t> slot(kSlots);
-  for (int i = 0; i < flush_windows(t->nnz); ++i) {
-    const int64_t k0 = flush_start(t->nnz, i);
-    const int64_t k1 = std::min<int64_t>(t->nnz, k0 + kFlushWindow);
+  for (int i = 0; i < kFlushSamples; ++i) {
+    const int64_t k0 = flush_start(t->nnz, i), k1 = k0 + kFlushWindow;
     for (int m = 0; m < L.N; ++m) {
       const uint64_t mask = (1ULL << L.w[m]) - 1;
       std::fill(slot.begin(), slot.end(), ~0ULL);

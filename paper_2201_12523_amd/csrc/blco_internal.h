@@ -22,8 +22,11 @@ constexpr int kTabSlots = 1 << kTabBits;
 constexpr int kTabWords = 1 + kTabSlots + kTabSlots / 4;
 // Windows sampled for a mode's row flushes: at most this many, evenly spaced, of kFlushWindow
 // non-zeros each; their first halves give the flushes of windows half as long.
+// Nothing asks for them in a launch of fewer than kFlushMin (win_wpt, group_pays), so a smaller
+// tensor has none counted: a build of 100k took 30 us longer for them.
 constexpr int kFlushSamples = 64;
 constexpr int kFlushWindow = 4096;
+constexpr int64_t kFlushMin = 1 << 19;
 constexpr int64_t kHotMinCount = 2048;  // default: a frequent row holds at least this many non-zeros
 
 // The bit map of a tensor (Sections 4.1-4.2).
@@ -102,9 +105,8 @@ struct blco_tensor {
   std::vector<uint32_t> tab;         // N * kTabWords: row tables of the frequent rows
   uint32_t* d_tab = nullptr;
   // distinct rows of each mode over the sampled windows of kFlushWindow / 2 and kFlushWindow
-  // non-zeros, and the non-zeros in them
+  // non-zeros
   uint32_t flush_rows[BLCO_MAX_MODES][2] = {};
-  int64_t flush_nnz[2] = {0, 0};
   // grouped MTTKRP: first non-zero of each bucket of a mode (N * kGroupBuckets), and the
   // multiplier that gives a row's bucket
   uint32_t* d_group = nullptr;
@@ -159,25 +161,13 @@ int mttkrp_careful(blco_tensor* t, int mode, const void* const* factors, int fac
                    int rank, float* out, void* ws, size_t ws_bytes, void* stream);
 size_t mttkrp_workspace(const blco_tensor* t, int mode, int rank, int factor_dtype);
 
-// Sampled windows of n non-zeros: their number and the first non-zero of the i-th (whole windows;
-// a shorter tensor is one).
-constexpr int flush_windows(int64_t n) {
-  return n < kFlushWindow ? (n > 0 ? 1 : 0)
-                          : n / kFlushWindow < kFlushSamples ? (int)(n / kFlushWindow) : kFlushSamples;
-}
+// First non-zero of the i-th sampled window of n >= kFlushMin non-zeros.
 constexpr int64_t flush_start(int64_t n, int i) {
-  return flush_windows(n) > 1
-             ? (n / kFlushWindow - 1) * i / (flush_windows(n) - 1) * kFlushWindow : 0;
-}
-inline void flush_sizes(int64_t n, int64_t (&nnz)[2]) {
-  for (int h = 0; h < 2; ++h) {
-    const int64_t w = kFlushWindow / (2 - h);
-    nnz[h] = flush_windows(n) * (n < w ? n : w);
-  }
+  return (n / kFlushWindow - 1) * i / (kFlushSamples - 1) * kFlushWindow;
 }
 
 // Counts the distinct rows of the sampled windows (t->flush_rows): on the host from the host
-// arrays, or on the device from d_keys and the run tables there, into `counts` (device,
+// arrays, or on the device from d_keys and the run tables there, into `counts` (device, cleared,
 // sizeof(flush_rows) bytes), queued on `stream`.
 void count_flushes(blco_tensor* t);
 int count_flushes_device(blco_tensor* t, uint32_t* counts, void* stream);

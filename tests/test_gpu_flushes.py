@@ -14,10 +14,11 @@ import paper_2201_12523_amd as blco  # noqa: E402
 DEV = torch.device("cuda:0")
 
 
-@pytest.mark.parametrize("dims,nnz,key_bits", [((300, 200, 70), 1, 64), ((300, 200, 70), 4097, 64),
+@pytest.mark.parametrize("dims,nnz,key_bits", [((300, 200, 70), 1, 64), ((300, 200, 70), 524_287, 64),
+                                               ((300, 200, 70), 524_288, 64),
                                                ((3000, 2000, 900, 5), 600_000, 64),
-                                               ((30_011, 12_007, 4_001), 300_000, 30),
-                                               ((1 << 24, 1 << 22, 1 << 20, 1 << 10), 500_000, 64)])
+                                               ((30_011, 12_007, 4_001), 700_001, 30),
+                                               ((1 << 24, 1 << 22, 1 << 20, 1 << 10), 800_000, 64)])
 def test_counts(dims, nnz, key_bits):
     rng = np.random.default_rng(nnz)
     coords = [np.minimum(rng.zipf(1.3, nnz) - 1, d - 1).astype(np.uint32) if m == 0 else

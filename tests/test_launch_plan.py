@@ -104,20 +104,21 @@ def test_workspace_under_a_budget(R, gradient):
 
 def counted(t, dims, key_bits):
     """Distinct rows per non-zero over the sampled windows, from the exported tensor as the oracle
-    decodes it."""
+    decodes it; none below 2^19 non-zeros."""
     keys, _, ids, starts = t.export()
-    coords = encode.decode(keys, ids, starts, encode.layout(dims, key_bits))
     n = keys.size
-    k = max(1, min(64, n // 4096))
-    first = [0] if k == 1 else [(n // 4096 - 1) * i // (k - 1) * 4096 for i in range(k)]
-    return [tuple(sum(np.unique(c[a:min(n, a + W)]).size for a in first) /
-                  sum(min(n, a + W) - a for a in first) for W in (2048, 4096)) for c in coords]
+    if n < 1 << 19:
+        return [(0, 0)] * len(dims)
+    coords = encode.decode(keys, ids, starts, encode.layout(dims, key_bits))
+    first = [(n // 4096 - 1) * i // 63 * 4096 for i in range(64)]
+    return [tuple(sum(np.unique(c[a:a + W]).size for a in first) / (64 * W) for W in (2048, 4096))
+            for c in coords]
 
 
-@pytest.mark.parametrize("dims,nnz,key_bits", [((300, 200, 70), 1, 64), ((300, 200, 70), 2047, 64),
-                                               ((300, 200, 70), 4097, 64), ((3000, 2000, 900), 100_000, 64),
-                                               ((3000, 2000, 900, 5), 600_000, 64), ((7, 5), 30, 64),
-                                               ((3000, 2000, 900), 300_000, 31)])
+@pytest.mark.parametrize("dims,nnz,key_bits", [((300, 200, 70), 1, 64), ((300, 200, 70), 524_287, 64),
+                                               ((300, 200, 70), 524_288, 64), ((70_000, 20_000), 524_289, 64),
+                                               ((3000, 2000, 900, 5), 600_000, 64), ((9000,), 700_001, 64),
+                                               ((3000, 2000, 900), 600_000, 31)])
 def test_counted_flushes(dims, nnz, key_bits):
     rng = np.random.default_rng(nnz)
     coords = [np.minimum(rng.zipf(1.5, nnz) - 1, d - 1).astype(np.uint32) if m == 0 else
