@@ -988,9 +988,10 @@ static double wide_saves(int N) { return N <= 4 ? 0.05 : 0.095; }
 // take 6 us (9 us) in windows of 256.  More windows than compute units cost more than they
 // save, in row flushes and in the chain of same-row flushes of a skewed mode: 250k power-law
 // non-zeros at R = 16 take 23, 17, 13 and 18 us in windows of 256, 512, 1024 and 2048.  Windows of
-// 256 end at half as many windows: 60k non-zeros take 11.5 us in 235 of them and 10.8 in 118 of 512
-// (uniform indices: 8.3 and 8.9), and the longer chains put a skewed mode 1.46 times as far from
-// 64 bits as in windows of 2048 (1.8e-7 and 1.25e-7; 1.45e-7 in windows of 512).
+// 256 end at three quarters as many windows: 60k non-zeros take 11.5 us in 235 of them and 10.8 in
+// 118 of 512 (uniform indices: 8.3 and 8.9; R = 64: 16.1 and 14.9), and the longer chains put a
+// skewed mode 1.46 times as far from 64 bits as in windows of 2048 (1.8e-7 and 1.25e-7; 1.45e-7 in
+// windows of 512).  38k at R = 64 take 14 us in 148 of them and 15 in 74.
 //
 // At R > 32 a window of 2048 leaves two workgroups per CU; one of 4096 merges more.  It pays on a
 // mode without frequent rows where it saves wide_saves(N) row flushes per non-zero (counted at
@@ -1019,7 +1020,7 @@ static int win_wpt(int N, int R, bool resid, bool big, bool wide, int64_t n, boo
   const int most = resid ? (N <= 4 ? 2 : 1) : R > 32 && wide ? 4 : 2;
   if (big) return most;
   const int64_t cus = device_cus();
-  if (n <= kWin / 4 * cus / 2) return -4;
+  if (n <= kWin / 4 * cus * 3 / 4) return -4;
   for (int w : {-2, 1, 2})
     if (w == most || n <= (w < 0 ? kWin / -w : kWin * w) * cus) return w;
   return most;

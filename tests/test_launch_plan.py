@@ -129,11 +129,11 @@ def test_counted_flushes(dims, nnz, key_bits):
 
 
 def test_windows_of_short_launches():
-    # no more windows than compute units (256 where there is no device), and half as many of the
-    # smallest, whose chains of additions are the longest
+    # no more windows than compute units (256 where there is no device), and three quarters as many
+    # of the smallest, whose chains of additions are the longest
     t = host_tensor((20_000, 8000, 600), 1000)
     for R in (8, 16, 32, 64):
-        for n, window in ((1, 256), (20_000, 256), (32_768, 256), (32_769, 512), (60_000, 512),
+        for n, window in ((1, 256), (20_000, 256), (49_152, 256), (49_153, 512), (60_000, 512),
                           (131_072, 512), (131_073, 1024), (262_144, 1024), (262_145, 2048)):
             p = t.plan(0, R, nnz=n)
             assert p["window"] == window and p["workgroups"] == -(-n // window)
