@@ -268,8 +268,9 @@ def summarize_stats(out, title, stats_csv, command):
 def summarize_overlap(out, title, copy_csv, kernel_csv, per_call_copies, command):
     """Copy/compute overlap of streamed MTTKRP calls from a rocprofv3 --kernel-trace
     --memory-copy-trace run: the host-to-device copies of the library's copy stream (the
-    stream with the most copy time) taken in groups of per_call_copies (2 per chunk: keys
-    and values), the MTTKRP kernels between one group's first copy and the next group's;
+    stream with the most copy time) taken in groups of per_call_copies (2 per chunk, keys and
+    values, and one more where the last chunk has more than 64 MiB of values), the MTTKRP
+    kernels between one group's first copy and the next group's;
     per call t_copy = sum of its copy times, t_comp = sum of its kernel times, t_total =
     last end - first copy start, overlap = (t_copy + t_comp - t_total) / min(t_copy, t_comp)."""
     import csv

@@ -198,9 +198,15 @@ int blco_mttkrp_v(blco_tensor* t, int mode, const float* values, const void* con
  * The three calls above with a workspace: device memory the caller lends the call
  * (256-byte aligned, not overlapping anything else, contents undefined before and after,
  * in use until the call's work on `stream` has run).  With the bytes blco_workspace gives
- * for the mode, a long MTTKRP of a mode with frequent rows runs faster: it flushes those
- * rows to copies in the workspace, which are then added to the output, instead of summing
- * them in LDS.  A smaller or empty workspace (NULL, 0) is fine: what does not fit is not
+ * for the mode, a long MTTKRP runs faster; blco_plan says what of it a launch takes:
+ *   copies of a mode's frequent rows, flushed to instead of summed in LDS and added to the
+ *     output afterwards (up to 64 copies of 256 rows);
+ *   factors and output rows padded to whole 64-byte lines, from 2^18 non-zeros on where the
+ *     rows are few against them (up to 1 GiB for the factors and 1 GiB for the output);
+ *   2 to 16 copies of the output at ranks 33-64, from 2^20 non-zeros on (up to 1 GiB);
+ *   the non-zeros of a flat mode moved to buckets of target rows, from 2^20 on (12 bytes per
+ *     non-zero).
+ * A smaller or empty workspace (NULL, 0) is fine: what does not fit is not
  * used.  values: as blco_mttkrp_v, or NULL for the tensor's own; scale, alpha: as
  * blco_mttkrp_v (NULL and 1 for blco_mttkrp); accumulate != 0: out += the result.
  * Errors: as the calls above, EINVAL (workspace NULL with bytes > 0, or misaligned).

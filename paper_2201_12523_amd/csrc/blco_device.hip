@@ -18,8 +18,9 @@
 //     segment to the output with one atomic per rank.  A mode's frequent rows
 //     (found at build time) go to copies in the call's workspace instead, or,
 //     without one, to an LDS stash flushed once per persistent workgroup.
-//     The workspace also holds padded factors and output rows, and the
-//     non-zeros of a flat mode moved to buckets of target rows (plan_call).
+//     The workspace also holds padded factors and output rows, copies of the
+//     output, and the non-zeros of a flat mode moved to buckets of target rows
+//     (plan_call).
 //   k_mttkrp_short (hierarchical resolution, Section 5.1), which the Section
 //     5.3 heuristic picks for modes shorter than the compute-unit count: each
 //     workgroup keeps a private LDS copy of all target rows (a rank slice) and
@@ -656,7 +657,6 @@ __global__ __launch_bounds__(1024) void k_reduce_loss(const double* __restrict__
   if (threadIdx.x == 0) loss[0] = 0.5 * sh[0];
 }
 
-// fp32 -> bf16, round to nearest even; NaN stays a (quiet) NaN.
 // Arrays of one launch of an element-wise kernel: row blockIdx.y of the grid takes one.  A
 // training step casts and scales one array per mode; a launch of its own for each took 4 us
 // of host time and 2-5 us of an otherwise idle device.
@@ -666,6 +666,7 @@ struct Arrays {
   int64_t n[BLCO_MAX_MODES];
 };
 
+// fp32 -> bf16, round to nearest even; NaN stays a (quiet) NaN.
 __global__ __launch_bounds__(256) void k_cast_bf16(Arrays a) {
   const float* __restrict__ src = a.src[blockIdx.y];
   uint16_t* __restrict__ dst = static_cast<uint16_t*>(a.dst[blockIdx.y]);

@@ -59,6 +59,22 @@ def test_sums_of_terms(dims, nnz, skew, R, dtype):
         assert float(((a - b).abs() - 2.1e-5 * S).max()) <= 0, m
 
 
+# an explicit threshold keeps the full LDS stash, beside padded factors and output rows
+@pytest.mark.parametrize("R", [10, 17, 35, 50, 100])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_stash_and_padding(R, dtype):
+    dims = (3000, 2000, 900)
+    t, vals, g = tensor(dims, 400_001, R, 1.1, hot_min_count=50)
+    F = [torch.randn(d, R, generator=g, device=DEV).to(dtype) for d in dims]
+    name = "bf16" if dtype == torch.bfloat16 else "fp32"
+    for m in range(3):
+        p = t.plan(m, R, name)
+        assert p["stash_rows"] > 0 and p["copies"] == 0 and p["factor_stride"] != R
+        S = plain(t, m, [f.abs() for f in F], vals.abs())
+        a, b = blco.mttkrp(t, m, F), plain(t, m, F, vals)
+        assert float(((a - b).abs() - 2.1e-5 * S).max()) <= 0, m
+
+
 @pytest.mark.parametrize("dims,nnz,skew", SHAPES)
 @pytest.mark.parametrize("R", [10, 35, 100])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
