@@ -37,6 +37,7 @@ Single legs: ``--workload zipf3|zipf4|uniform3|short4|small|oom3|cpgrad4|cpals4`
 Prints one JSON line on stdout; progress goes to stderr.
 """
 import argparse
+import ctypes
 import hashlib
 import json
 import os
@@ -391,8 +392,9 @@ def summarize_sweep(out, json_path, command):
           "3-mode 2^21 x 2^17 x I tensors, 50M distinct non-zeros (Zipf(1.1) indices on the two "
           "long modes, uniform on the short one, U(0,1) values), rank "
           f"{d['rank']} fp32 factors; kernel time of the mode-3 (length I) MTTKRP, output "
-          "accumulated. The register-based path includes its frequent-row stash (all I rows fit "
-          f"for I <= 255). The device reports {d['cus']} compute units; `auto` is the Section 5.3 "
+          "accumulated. The register-based path adds frequent rows to copies in a workspace "
+          f"(all I rows for I <= 255). The device reports {d['cus']} compute units; `auto` is "
+          "the Section 5.3 "
           "choice (hierarchical when I is below the compute-unit count).", "",
           "| I | register ms | hierarchical ms | register / hierarchical | auto |",
           "|---:|---:|---:|---:|---|"]
@@ -916,7 +918,14 @@ def leg_cpals(args, torch, blco, synth, w):
          for m, d in enumerate(w.dims)]
     F = [torch.from_numpy(a).to(dev) for a in A]
     outs = [torch.empty((d, R), dtype=torch.float32, device=dev) for d in w.dims]
-    mk = [timer(lambda n=n: blco.mttkrp_acc(T, n, F, outs[n]), args.steps) for n in range(N)]
+
+    def update_mttkrp(n):
+        # CP-ALS sums as a call without a workspace does (the full stash, no copies)
+        ptrs = (ctypes.c_void_p * N)(*[f.data_ptr() for f in F])
+        rc = blco.lib().blco_mttkrp_acc(T.handle, n, ptrs, blco.F32, R, outs[n].data_ptr(),
+                                        torch.cuda.current_stream().cuda_stream)
+        assert rc == 0, rc
+    mk = [timer(lambda n=n: update_mttkrp(n), args.steps) for n in range(N)]
     blco.cp_als(T, [f.clone() for f in F], max_iters=max(args.warmup, 1), tol=-1.0)
     torch.cuda.synchronize()
     iters = max(args.steps, 2)
